@@ -54,6 +54,26 @@ static int check_desc(const cagq_grid_desc* d) {
     return CAGQ_OK;
 }
 
+// log2 of the occupancy words per brick: the fewest words (kMinBrickW on)
+// that give at most 1024 bricks a cloud and 4096 in the batch, with a
+// histogram that its scatter tiles scan themselves and that stays within 2^22
+// entries, else kBrickW.
+// Small bricks keep a brick within one wave (a dense 84 x 84 x 34 grid of
+// 81920 points: up to 7800 points in 2048 voxels, 1200 in 256) and give a
+// single cloud enough waves; more of them lengthen every tile's histogram
+// columns and every brick's sum over the bricks before it.
+static int32_t brick_wshift(int32_t B, int32_t N, int64_t W) {
+    int32_t sh = 0;
+    while ((1 << sh) < kMinBrickW) ++sh;
+    for (; (1 << sh) < kBrickW; ++sh) {
+        const int64_t q = (W + (1 << sh) - 1) >> sh;
+        if (q <= 1024 && q * B <= 4096 && (N / kSortTile + 2) * q <= kTileScanCap &&
+            ((int64_t)B * N / kSortTile + 1) * q * B <= (int64_t(1) << 22))
+            break;
+    }
+    return sh;
+}
+
 bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     if (B < 1 || N < 1 || (int64_t)B * N > 2147483647LL) return false;
     memset(L, 0, sizeof(*L));
@@ -65,7 +85,8 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->tiles_s = ((int64_t)N + kScanTile - 1) / kScanTile;
     L->big_cap = (int64_t)B * N / (kBigVoxel + 1) + 1;
     const size_t BN = (size_t)B * N;
-    L->Q = (int32_t)((L->W + kBrickW - 1) / kBrickW);
+    L->wshift = brick_wshift(B, N, L->W);
+    L->Q = (int32_t)((L->W + (1 << L->wshift) - 1) >> L->wshift);
     L->T = (int32_t)(((int64_t)B * N + kSortTile - 1) / kSortTile);
     // the histogram matrix (B * Q by T entries) stays within 2^24 entries
     L->bricks = (int64_t)B * L->Q <= kMaxBricks && (int64_t)B * L->Q * L->T <= (int64_t(1) << 24);
@@ -73,8 +94,9 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->tile_scan = L->bricks && ((int64_t)(N + kSortTile - 1) / kSortTile + 1) * L->Q <= kTileScanCap;
     const size_t BQ = L->bricks ? (size_t)B * L->Q : 0;
     const size_t hist_n = BQ * (size_t)L->T;
-    L->items_max = L->bricks ? (int64_t)BQ + ((int64_t)BN + kBrickCap - 1) / kBrickCap : 0;
+    L->items_max = L->bricks ? (int64_t)BN / (kWavePts + 1) : 0;
     L->heavy_max = L->bricks ? (int64_t)BN / (kBrickCap + 1) : 0;
+    L->rows_max = L->bricks ? 2 * (int64_t)BN / kBrickCap + L->heavy_max : 0;
     const size_t H = (size_t)L->heavy_max;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -93,7 +115,7 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->sel_cnt = take(4 * (size_t)B);
     L->clear_small = off;
     L->desc_h = take(8 * ((BQ + 63) / 64));
-    L->hdone = take(4 * (L->bricks ? (size_t)BN / (kBrickCap + 1) : 0));
+    L->hdone = take(4 * H);
     L->clear_brick = off;
     // the occupancy bytes and rank descriptors serve the many-kernel build of
     // grids too large for the bricks only
@@ -104,22 +126,21 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->bitmap = take(8 * (size_t)B * L->W);
     L->word_rank = take(4 * (size_t)B * L->W);
     L->pt_slot = take(4 * BN);
-    L->pt_pos = take(4 * BN);
+    L->pt_pos = take(L->bricks ? 0 : 4 * BN);
     L->hist = take(4 * hist_n);
     L->bstart = take(4 * BQ);
-    L->brick_hb = take(4 * BQ);
-    L->item_extra = take(8 * ((size_t)L->items_max - BQ));
+    L->item = take(16 * (size_t)L->items_max);
     L->agg = take(8 * BQ);
-    L->hlist = take(4 * H);
-    L->hebase = take(4 * H);
-    L->pcnt = take(4 * ((size_t)L->items_max - BQ) * kBrickV);
-
-    L->hfo = take(4 * H * (kBrickV + 1));
-    L->hso = take(4 * H * kBrickV);
-    L->hpre = take(8 * H);
+    L->hfirst = take(4 * H);
+    L->hparts = take(4 * H);
+    const size_t bv = (size_t)64 << L->wshift;
+    L->pcnt = take(4 * (size_t)L->rows_max * bv);
+    L->htot = take(4 * H * bv);
+    L->hso = take(4 * H * bv);
     L->sorted = take(L->bricks ? 16 * BN : 0);
+    L->svox = take(L->bricks ? 2 * BN : 0);
     L->full_off = take(L->bricks ? 0 : 4 * (size_t)B * (N + 1));
-    L->bucket = take(4 * BN);
+    L->bucket = take(L->bricks ? 0 : 4 * BN);
     L->pt4 = take(16 * BN);
     L->big = take(L->bricks ? 0 : 4 * (size_t)L->big_cap);
     L->cas_cover = take(4 * BN);

@@ -300,26 +300,30 @@ __global__ __launch_bounds__(256) void k_finalize(
 }
 
 // ---- larger clouds: sort the points into bricks, then build each brick.
-// A brick is a run of kBrickV consecutive linear voxel ids (kBrickW occupancy
-// words) of one cloud; the batch holds B * Q of them. The points are grouped
+// A brick is a run of consecutive linear voxel ids (2^wshift occupancy words,
+// at most kBrickW: brick_wshift) of one cloud; the batch holds B * Q of them. The points are grouped
 // by brick with a counting sort: a histogram per tile of points (one row per
 // tile), a scan of each brick's column and of the bricks' totals (by each
 // scatter tile itself, or by a launch of its own when a tile would read too
-// many entries), a scatter that carries each point's coordinates and index. Then one workgroup per
-// brick marks its occupancy words in LDS, ranks its occupied voxels by
-// popcount, counts their points, and places the n_v lowest point indices of
-// every voxel. The occupied and stored counts of the cloud's earlier bricks
-// come from a look-back. Every output is written once, the work is
+// many entries), a scatter that carries each point's coordinates and index. Then two
+// passes over the bricks, a wave per brick (a workgroup for the largest):
+// one counts each brick's points per voxel in LDS, which gives its occupancy
+// words and its occupied and stored totals; the other sums the totals of the
+// cloud's earlier bricks, ranks its occupied voxels by popcount, and places
+// the n_v lowest point indices of every voxel. Every output is written once, the work is
 // proportional to the points and the occupied voxels, and no global atomic
 // is taken per point.
 constexpr int kSortT = 1024;                    // threads per sort tile
 constexpr int kSortIPT = kSortTile / kSortT;    // points per thread
 constexpr int kHGroup = 64;                     // bricks per block of the column scan
-constexpr int kBrickIPT = kBrickCap / kBrickT;  // points per thread, kept in registers
-constexpr int kBrickWaves = kBrickT / kWave;
-static_assert(2 * kBrickCap + 1 >= kBrickV, "a heavy part counts every voxel of its brick in LDS");
-static_assert(kBrickCap <= kBrickV, "a brick of one part has at most kBrickCap occupied voxels");
+constexpr int kBrickIPT = kBrickCap / kBrickT;  // points per thread of a part
+constexpr int kLoadIPT = 8;                     // of them, loaded together
+constexpr int kWaveIPT = kWavePts / kWave;      // points per lane of a wave's brick
+constexpr int kBrickWaves = kBrickT / kWave;    // bricks per block
 static_assert(kBrickW <= kWave, "a brick's occupancy words are scanned by one wave");
+static_assert(kBrickIPT % kLoadIPT == 0 && kBrickCap < 65536, "a part is loaded in whole steps");
+static_assert(kSortTile <= kBrickCap, "a tile's points of one brick fit in one part");
+static_assert(kWavePts < kBrickCap && kBrickV % kBrickT == 0, "brick sizes");
 
 // Linear voxel id of a point; `bad` is set for a non-finite coordinate (its
 // axis index is then 0).
@@ -344,7 +348,7 @@ __device__ __forceinline__ uint32_t voxel_lin(float x, float y, float z, const G
 // words [clr, clr + n16) (status, tickets, descriptors) that the later
 // kernels use.
 __global__ __launch_bounds__(kSortT) void k_bhist(const float* __restrict__ P, int32_t N, int32_t BN, GridArgs g,
-                                                  int32_t Q, int32_t BQ, int32_t T, bool own,
+                                                  int32_t Q, int32_t BQ, int32_t vshift, int32_t T, bool own,
                                                   uint32_t* __restrict__ hist, uint4* __restrict__ clr, int64_t n16) {
     __shared__ uint32_t s_h[kMaxBricks];
     const int tid = threadIdx.x;
@@ -370,27 +374,87 @@ __global__ __launch_bounds__(kSortT) void k_bhist(const float* __restrict__ P, i
         if (gid >= BN) break;
         bool bad = false;
         const uint32_t lin = voxel_lin(c[k][0], c[k][1], c[k][2], g, bad);
-        atomicAdd(&s_h[(gid / N) * Q + (int32_t)(lin / kBrickV)], 1u);
+        atomicAdd(&s_h[(gid / N) * Q + (int32_t)(lin >> vshift)], 1u);
     }
     lds_barrier();
     uint32_t* row = hist + (size_t)t * BQ;
     for (int32_t i = e0 + tid; i < e1; i += kSortT) row[i] = s_h[i];
 }
 
+// The work items of the brick passes: a part of a brick of more than
+// kWavePts points, for one block.
+struct BrickItem {
+    uint32_t g;   // the brick
+    uint32_t p0;  // the part's first sorted position
+    uint32_t n;   // (part << 12) | (its points - 1)
+    int32_t hb;   // the heavy brick it is a part of, -1: the whole brick is one part
+};
+
+struct BrickLists {
+    BrickItem* item;
+    uint32_t* hfirst;  // per heavy brick: the count row of its first part
+    uint32_t* hparts;  //                  its parts
+    int* status;
+};
+
+// Lists a brick of more than kWavePts points (brick g at sorted position
+// `start`, `tot` points, those of tile t being hist[t * BQ + g], tiles
+// [tf, tl]): one item for at most kBrickCap points, otherwise (heavy) parts of
+// whole tiles, as many as fit in kBrickCap points. Tiles follow the points'
+// order, so every point of an earlier part has a lower index than those of a
+// later one, and a point's rank among its voxel's is the voxel's points in
+// the earlier parts plus its rank within its own. Every lane of the wave
+// calls it; one atomic per wave lists its bricks of one part.
+__device__ __forceinline__ void list_big(const BrickLists& o, bool valid, uint32_t g, uint32_t start, uint32_t tot,
+                                         const uint32_t* __restrict__ hist, int32_t BQ, int32_t tf, int32_t tl) {
+    const bool one = valid && tot > (uint32_t)kWavePts && tot <= (uint32_t)kBrickCap;
+    const uint64_t m = __ballot(one);
+    if (m) {
+        const int first = __ffsll((unsigned long long)m) - 1;
+        uint32_t base = 0;
+        if (lane_id() == first) base = (uint32_t)atomicAdd(&o.status[kStItems], __popcll(m));
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, first);
+        if (one) o.item[base + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1))] = BrickItem{g, start, tot - 1, -1};
+    }
+    if (!valid || tot <= (uint32_t)kBrickCap) return;
+    // calls f(part, first position, points) for each part
+    auto walk = [&](auto f) {
+        constexpr int kU = 32;  // column entries in flight
+        uint32_t part = 0, p0 = start, acc = 0;
+        for (int32_t t0 = tf; t0 <= tl; t0 += kU) {
+            uint32_t x[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) x[u] = hist[(size_t)(t0 + u <= tl ? t0 + u : tl) * BQ + g];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const uint32_t v = t0 + u <= tl ? x[u] : 0u;
+                if (acc + v > (uint32_t)kBrickCap) {
+                    f(part++, p0, acc);
+                    p0 += acc;
+                    acc = 0;
+                }
+                acc += v;
+            }
+        }
+        f(part++, p0, acc);
+        return part;
+    };
+    const uint32_t parts = walk([](uint32_t, uint32_t, uint32_t) {});
+    const int32_t hb = atomicAdd(&o.status[kStHeavy], 1);
+    const uint32_t e = (uint32_t)atomicAdd(&o.status[kStItems], (int)parts);
+    o.hfirst[hb] = (uint32_t)atomicAdd(&o.status[kStRows], (int)parts);
+    o.hparts[hb] = parts;
+    walk([&](uint32_t part, uint32_t p0, uint32_t n) { o.item[e + part] = BrickItem{g, p0, (part << 12) | (n - 1), hb}; });
+}
+
 // Sorted positions and work items: bstart[g] = points of the bricks before g
 // (bricks in cloud-major order), and entry (t, g) of the histogram becomes
-// the first position of tile t's points in brick g. Work item g < B * Q is
-// brick g (its first kBrickCap points); a brick of more than kBrickCap points
-// (heavy) has one more item per further kBrickCap points, listed in
-// item_extra as (part << 32 | g), and heavy bricks are numbered in hlist. A
-// block takes kHGroup bricks (one per lane) and splits the tiles over its
-// waves; the blocks' totals are chained by a look-back.
-__global__ __launch_bounds__(kScanThreads) void k_hscan(uint32_t* __restrict__ hist, int32_t BQ, int32_t T,
-                                                        uint32_t* __restrict__ bstart, int32_t* __restrict__ brick_hb,
-                                                        uint64_t* __restrict__ item_extra,
-                                                        uint32_t* __restrict__ hlist, uint32_t* __restrict__ hebase,
-                                                        uint64_t* __restrict__ desc,
-                                                        int* __restrict__ status) {
+// the first position of tile t's points in brick g. A block takes kHGroup
+// bricks (one per lane) and splits the tiles over its waves; the blocks'
+// totals are chained by a look-back.
+__global__ __launch_bounds__(kScanThreads) void k_hscan(uint32_t* hist, int32_t N, int32_t Q, int32_t BQ,
+                                                        int32_t T, uint32_t* __restrict__ bstart, BrickLists lists,
+                                                        uint64_t* __restrict__ desc, int* __restrict__ status) {
     constexpr int kW = kScanThreads / kWave;
     __shared__ uint32_t s_ticket;
     __shared__ uint32_t s_part[kW][kHGroup];
@@ -425,32 +489,23 @@ __global__ __launch_bounds__(kScanThreads) void k_hscan(uint32_t* __restrict__ h
         pre += w < wv ? x : 0u;
         tot += x;
     }
-    // (extra parts << 32 | points), scanned over the bricks
-    const uint32_t parts = !valid ? 0u : (tot > (uint32_t)kBrickCap ? (tot + kBrickCap - 1) / kBrickCap : 1u);
-    uint64_t gtot = 0, ex = 0;
+    uint64_t gtot = 0;
     if (wv == 0) {
-        const uint64_t x = ((uint64_t)(parts ? parts - 1 : 0u) << 32) | tot;
-        const uint64_t incl = wave_incl_scan<uint64_t>(x);
-        ex = incl - x;
-        s_bex[lane] = (uint32_t)ex;
-        gtot = shfl64(incl, kWave - 1);
+        const uint32_t x = valid ? tot : 0u;
+        const uint32_t incl = wave_incl_scan<uint32_t>(x);
+        s_bex[lane] = incl - x;
+        gtot = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
     }
     const uint64_t P0 = tile_lookback(desc, grp, gtot, &s_prefix);
-    if (!valid) return;
     const uint32_t base = (uint32_t)P0 + s_bex[lane];
     if (wv == 0) {
-        const uint32_t ebase = (uint32_t)((P0 + ex) >> 32);
-        bstart[g] = base;
-        for (uint32_t k = 1; k < parts; ++k) item_extra[ebase + k - 1] = ((uint64_t)k << 32) | (uint32_t)g;
-        int32_t hb = -1;
-        if (parts > 1) {
-            hb = (int32_t)atomicAdd((unsigned*)&status[kStHeavy], 1u);
-            hlist[hb] = (uint32_t)g;
-            hebase[hb] = ebase;
-        }
-        brick_hb[g] = hb;
-        if (g == BQ - 1) status[kStItems] = (int)(ebase + parts - 1);
+        if (valid) bstart[g] = base;
+        const int64_t b = valid ? g / Q : 0;
+        list_big(lists, valid, (uint32_t)g, base, tot, hist, BQ, (int32_t)(b * N / kSortTile),
+                 (int32_t)(((b + 1) * N - 1) / kSortTile));
     }
+    __syncthreads();  // the columns are read above and rewritten below
+    if (!valid) return;
     uint32_t run = base + pre;
 #pragma unroll
     for (int j = 0; j < kHKeep; ++j) {
@@ -490,14 +545,10 @@ __device__ __forceinline__ uint32_t sort_excl_scan(uint32_t v, uint32_t* s_wave,
 // t and the brick's total, and an exclusive scan of the totals over the
 // cloud's bricks (clouds hold N sorted positions each) gives the brick's
 // first position. The cloud's first tile also writes those (bstart) and
-// lists the bricks of more than kBrickCap points (heavy): one more work item
-// per further kBrickCap points in item_extra as (part << 32 | brick),
-// numbered in hlist and counted in the status words.
+// lists the bricks of more than kWavePts points.
 __device__ __forceinline__ void tile_columns(int32_t t, int32_t N, int32_t BN, int32_t Q, int32_t BQ,
                                              const uint32_t* __restrict__ hist, uint32_t* s_o, uint32_t* s_wave,
-                                             uint32_t* __restrict__ bstart, int32_t* __restrict__ brick_hb,
-                                             uint64_t* __restrict__ item_extra, uint32_t* __restrict__ hlist,
-                                             uint32_t* __restrict__ hebase, int* __restrict__ status) {
+                                             uint32_t* __restrict__ bstart, const BrickLists& lists) {
     constexpr int kU = 32;  // column loads in flight per thread (a cloud of up to 126976 points: all of them)
     const int tid = threadIdx.x;
     const int32_t p0 = t * kSortTile, p1 = p0 + kSortTile < BN ? p0 + kSortTile : BN;
@@ -524,36 +575,24 @@ __device__ __forceinline__ void tile_columns(int32_t t, int32_t N, int32_t BN, i
             uint32_t sum;
             const uint32_t start = carry + sort_excl_scan(tot, s_wave, &sum);
             carry += sum;
-            if (q >= Q) continue;
             const int32_t gg = b * Q + q;
-            s_o[gg] = start + pre;
-            if (t != tf) continue;
-            bstart[gg] = start;
-            int32_t hb = -1;
-            if (tot > (uint32_t)kBrickCap) {
-                const uint32_t parts = (tot + kBrickCap - 1) / kBrickCap;
-                hb = atomicAdd(&status[kStHeavy], 1);
-                const uint32_t eb = (uint32_t)atomicAdd(&status[kStItems], (int)(parts - 1));
-                hlist[hb] = (uint32_t)gg;
-                hebase[hb] = eb;
-                for (uint32_t k = 1; k < parts; ++k) item_extra[eb + k - 1] = ((uint64_t)k << 32) | (uint32_t)gg;
-            }
-            brick_hb[gg] = hb;
+            if (q < Q) s_o[gg] = start + pre;
+            if (t != tf) continue;  // the same for the whole block
+            if (q < Q) bstart[gg] = start;
+            list_big(lists, q < Q, (uint32_t)gg, start, tot, hist, BQ, tf, tl);
         }
     }
 }
 
-// One lane per point: (x, y, z, index) at the next free position of its
-// brick within the tile's range. With SCAN the tile finds its ranges from
+// One lane per point: (x, y, z, index), and its voxel within the brick, at the
+// next free position of its brick within the tile's range. With SCAN the tile finds its ranges from
 // the histogram columns itself (tile_columns); otherwise k_hscan has
 // rewritten row t of the histogram into them.
 template <bool SCAN>
 __global__ __launch_bounds__(kSortT) void k_bscatter(const float* __restrict__ P, int32_t N, int32_t BN, GridArgs g,
-                                                     int32_t Q, int32_t BQ, const uint32_t* __restrict__ hist,
-                                                     float4* __restrict__ sorted, uint32_t* __restrict__ bstart,
-                                                     int32_t* __restrict__ brick_hb, uint64_t* __restrict__ item_extra,
-                                                     uint32_t* __restrict__ hlist, uint32_t* __restrict__ hebase,
-                                                     int* __restrict__ status) {
+                                                     int32_t Q, int32_t BQ, int32_t vshift, const uint32_t* __restrict__ hist,
+                                                     float4* __restrict__ sorted, uint16_t* __restrict__ svox,
+                                                     uint32_t* __restrict__ bstart, BrickLists lists, int* __restrict__ status) {
     __shared__ uint32_t s_o[kMaxBricks];
     __shared__ uint32_t s_wave[kSortT / kWave];
     const int tid = threadIdx.x;
@@ -568,7 +607,7 @@ __global__ __launch_bounds__(kSortT) void k_bscatter(const float* __restrict__ P
         for (int a = 0; a < 3; ++a) c[k][a] = p[a];
     }
     if constexpr (SCAN) {
-        tile_columns(t, N, BN, Q, BQ, hist, s_o, s_wave, bstart, brick_hb, item_extra, hlist, hebase, status);
+        tile_columns(t, N, BN, Q, BQ, hist, s_o, s_wave, bstart, lists);
     } else {
         const uint32_t* row = hist + (size_t)t * BQ;
         for (int32_t i = tid; i < BQ; i += kSortT) s_o[i] = row[i];
@@ -582,8 +621,9 @@ __global__ __launch_bounds__(kSortT) void k_bscatter(const float* __restrict__ P
         const float x = c[k][0], y = c[k][1], z = c[k][2];
         const uint32_t lin = voxel_lin(x, y, z, g, bad);
         const int32_t b = gid / N;
-        const uint32_t pos = atomicAdd(&s_o[b * Q + (int32_t)(lin / kBrickV)], 1u);
+        const uint32_t pos = atomicAdd(&s_o[b * Q + (int32_t)(lin >> vshift)], 1u);
         sorted[pos] = make_float4(x, y, z, __uint_as_float((uint32_t)(gid - b * N)));
+        svox[pos] = (uint16_t)(lin & ((1u << vshift) - 1));
     }
     if (bad) raise_error(status, CAGQ_ERR_NONFINITE_INPUT);
 }
@@ -591,14 +631,17 @@ __global__ __launch_bounds__(kSortT) void k_bscatter(const float* __restrict__ P
 struct BrickArgs {
     const float* P;
     int32_t N, BN, Q, BQ;
+    int32_t wshift;      // log2 of the occupancy words per brick
+    int32_t groups;      // blocks that take kBrickWaves bricks each
+    int32_t items_max;   // the blocks before them take an item each
     int64_t W;
     uint32_t n_v;
-    GridArgs g;
     const uint32_t* bstart;
-    const int32_t* brick_hb;
-    const uint64_t* item_extra;
-    const uint32_t* hlist;
+    const BrickItem* item;
+    const uint32_t* hfirst;
+    const uint32_t* hparts;
     const float4* sorted;
+    const uint16_t* svox;
     uint64_t* bitmap;
     uint32_t* word_rank;
     uint32_t* vox_lin;
@@ -608,50 +651,51 @@ struct BrickArgs {
     uint32_t* pt_list;
     float4* pt4;
     uint64_t* agg;      // per brick: occupied voxels << 31 | stored points
-    uint32_t* bucket;   // point indices of heavy bricks, grouped by voxel
-    const uint32_t* hebase; // per heavy brick: its first item in item_extra
-    uint32_t* pcnt;     // per further part of a heavy brick and voxel: the brick's points in the parts before it
-    uint32_t* hfo;      // per heavy brick and voxel: exclusive prefix of the points (kBrickV + 1)
+    uint32_t* pcnt;     // count rows: per part of a heavy brick and voxel, the part's points, then
+                        // the brick's points in the parts before it
+    uint32_t* htot;     // per heavy brick and voxel: the points
     uint32_t* hso;      // per heavy brick and voxel: exclusive prefix of min(points, n_v)
-    uint64_t* hpre;     // per heavy brick: the aggregate of the cloud's bricks before it
-    uint32_t* hdone;    // per heavy brick: its parts that have grouped their points
-    int* status;
+    uint32_t* hdone;    // per heavy brick: its parts that have counted their points
+    const int* status;
+
+    __device__ __forceinline__ int32_t words() const { return 1 << wshift; }
+    __device__ __forceinline__ uint32_t voxels() const { return 64u << wshift; }
 };
 
 // Occupancy words of a brick and their exclusive ranks.
 struct WordLds {
     uint64_t word[kBrickW];
     uint32_t wocc[kBrickW];
-    uint32_t nocc;
 };
 
 __device__ __forceinline__ uint32_t brick_rank(const WordLds& s, uint32_t v) {
     return s.wocc[v >> 6] + (uint32_t)__popcll(s.word[v >> 6] & ((1ull << (v & 63)) - 1));
 }
 
-// Exclusive ranks of the occupancy words (one wave): sets s.wocc and s.nocc.
-__device__ __forceinline__ void brick_word_scan(WordLds& s) {
-    const int tid = threadIdx.x;
-    if (tid < kWave) {
-        const uint32_t o = tid < kBrickW ? (uint32_t)__popcll(s.word[tid]) : 0u;
-        const uint32_t oi = wave_incl_scan<uint32_t>(o);
-        if (tid < kBrickW) s.wocc[tid] = oi - o;
-        if (tid == kWave - 1) s.nocc = oi;
+// Puts a brick's occupancy words (lane l holds word l, 0 from the brick's
+// word count on) and their exclusive ranks into LDS; called by one wave. The
+// words' lane also gets its rank.
+__device__ __forceinline__ uint32_t brick_put_words(WordLds& s, uint64_t word) {
+    const int lane = lane_id();
+    const uint32_t o = (uint32_t)__popcll(word);
+    const uint32_t ex = wave_incl_scan<uint32_t>(o) - o;
+    if (lane < kBrickW) {
+        s.word[lane] = word;
+        s.wocc[lane] = ex;
     }
+    return ex;
 }
 
-// Sum and exclusive scan of one value per thread over a brick block; the
-// waves meet at an LDS-only barrier (their global stores are not waited for).
-__device__ __forceinline__ uint64_t block_sum64(uint64_t v, uint64_t* s_wave) {
-    v = wave_sum<uint64_t>(v);
-    if (lane_id() == 0) s_wave[threadIdx.x / kWave] = v;
-    lds_barrier();
-    uint64_t t = 0;
-#pragma unroll
-    for (int i = 0; i < kBrickWaves; ++i) t += s_wave[i];
-    return t;
+// The waves of a brick group's lists exchange data through LDS among the
+// lanes of one wave only.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Exclusive scan of one value per thread over a brick block; the waves meet
+// at an LDS-only barrier (their global stores are not waited for).
 __device__ __forceinline__ uint64_t brick_excl_scan(uint64_t v, uint64_t* s_wave, uint64_t* total) {
     const uint64_t incl = wave_incl_scan<uint64_t>(v);
     const int wv = threadIdx.x / kWave;
@@ -668,373 +712,369 @@ __device__ __forceinline__ uint64_t brick_excl_scan(uint64_t v, uint64_t* s_wave
     return off + incl - v;
 }
 
-// The work item of a block: brick g = blockIdx.x (its first kBrickCap
-// points), or a further part of a heavy brick.
-struct BrickItem {
+// One brick: its cloud, its place in the cloud, its sorted range.
+struct Brick {
     int32_t g, b, q;
-    uint32_t start, cnt;  // the brick's sorted range
-    uint32_t p0, n;       // the part's sorted range
-    uint32_t part, parts;
-    bool heavy;
+    uint32_t start, cnt;
 };
 
-__device__ __forceinline__ bool brick_id(const BrickArgs& a, BrickItem& it) {
-    const uint32_t u = blockIdx.x;
-    it.part = 0;
-    if (u < (uint32_t)a.BQ) {
-        it.g = (int32_t)u;
-    } else {
-        if (u - (uint32_t)a.BQ >= (uint32_t)a.status[kStItems]) return false;
-        const uint64_t x = a.item_extra[u - a.BQ];
-        it.g = (int32_t)(uint32_t)x;
-        it.part = (uint32_t)(x >> 32);
-    }
-    it.b = it.g / a.Q;
-    it.q = it.g - it.b * a.Q;
-    return true;
+__device__ __forceinline__ Brick brick_at(const BrickArgs& a, int32_t g) {
+    Brick k;
+    k.g = g;
+    k.b = g / a.Q;
+    k.q = g - k.b * a.Q;
+    k.start = a.bstart[g];
+    k.cnt = (g + 1 < a.BQ ? a.bstart[g + 1] : (uint32_t)a.BN) - k.start;
+    return k;
 }
 
-__device__ __forceinline__ void brick_range(const BrickArgs& a, BrickItem& it) {
-    it.start = a.bstart[it.g];
-    const uint32_t end = it.g + 1 < a.BQ ? a.bstart[it.g + 1] : (uint32_t)a.BN;
-    it.cnt = end - it.start;
-    it.heavy = it.cnt > (uint32_t)kBrickCap;
-    it.parts = it.heavy ? (it.cnt + kBrickCap - 1) / kBrickCap : 1u;
-    it.p0 = it.start + it.part * (uint32_t)kBrickCap;
-    it.n = end - it.p0 < (uint32_t)kBrickCap ? end - it.p0 : (uint32_t)kBrickCap;
-}
-
-__device__ __forceinline__ bool brick_item(const BrickArgs& a, BrickItem& it) {
-    if (!brick_id(a, it)) return false;
-    brick_range(a, it);
-    return true;
-}
-
-// Voxel (within the brick) of each of the part's points; with MARK, also its
-// occupancy bit in s.word (zeroed and published by the caller's barrier).
-template <bool MARK>
-__device__ __forceinline__ void brick_voxels(const BrickArgs& a, WordLds& s, const BrickItem& it,
-                                             uint32_t (&v)[kBrickIPT], uint32_t (&idx)[kBrickIPT]) {
-    const uint32_t vbase = (uint32_t)it.q * kBrickV;
-    // every point's load first, so that they are in flight together (a load
-    // used under its bounds test would be waited for before the next)
-    float4 ee[kBrickIPT];
+// Voxels (within their brick) of IPT points of the sorted range [p0, p0 + n),
+// `stride` apart from `first` on: every point's load first, so that they are
+// in flight together (a load used under its bounds test would be waited for
+// before the next). n is at least 1: a lane past the end loads the first one.
+template <int IPT>
+__device__ __forceinline__ void brick_voxels(const BrickArgs& a, uint32_t p0, uint32_t n, uint32_t first,
+                                             uint32_t stride, uint32_t (&v)[IPT]) {
 #pragma unroll
-    for (int k = 0; k < kBrickIPT; ++k) {
-        const uint32_t i = threadIdx.x + k * kBrickT;
-        if (i < it.n) ee[k] = a.sorted[it.p0 + i];
+    for (int j = 0; j < IPT; ++j) {
+        const uint32_t i = first + j * stride;
+        v[j] = a.svox[p0 + (i < n ? i : 0u)];
     }
+}
+
+// The points themselves, in the same way.
+template <int IPT>
+__device__ __forceinline__ void brick_points(const BrickArgs& a, uint32_t p0, uint32_t n, uint32_t first,
+                                             uint32_t stride, float (&x)[IPT], float (&y)[IPT], float (&z)[IPT],
+                                             uint32_t (&idx)[IPT]) {
 #pragma unroll
-    for (int k = 0; k < kBrickIPT; ++k) {
-        const uint32_t i = threadIdx.x + k * kBrickT;
-        v[k] = 0u;
-        idx[k] = 0u;
-        if (i < it.n) {
-            const float4 e = ee[k];
-            bool bad = false;
-            v[k] = voxel_lin(e.x, e.y, e.z, a.g, bad) - vbase;
-            idx[k] = __float_as_uint(e.w);
-            if (MARK) atomicOr(reinterpret_cast<unsigned long long*>(&s.word[v[k] >> 6]), 1ull << (v[k] & 63));
-        }
+    for (int j = 0; j < IPT; ++j) {
+        const uint32_t i = first + j * stride;
+        const float4 e = a.sorted[p0 + (i < n ? i : 0u)];
+        x[j] = e.x;
+        y[j] = e.y;
+        z[j] = e.z;
+        idx[j] = __float_as_uint(e.w);
     }
+}
+
+// A block's item, decoded.
+struct BrickPart {
+    Brick k;
+    uint32_t p0, n, part;
+    int32_t hb;
+};
+
+// The item of this block, or false past the last one.
+__device__ __forceinline__ bool brick_part_at(const BrickArgs& a, BrickPart& p) {
+    if (blockIdx.x >= (uint32_t)a.status[kStItems]) return false;
+    const BrickItem it = a.item[blockIdx.x];
+    p.k = brick_at(a, (int32_t)it.g);
+    p.p0 = it.p0;
+    p.n = (it.n & 0xFFFu) + 1;
+    p.part = it.n >> 12;
+    p.hb = it.hb;
+    return true;
 }
 
 struct CountLds {
-    WordLds w;
-    uint32_t cnt[kBrickV];  // per occupied voxel (by rank), or per voxel for a heavy brick
-    uint64_t wave[kScanThreads / kWave];
-};
-
-// Pass 1 over the bricks: per brick its occupancy words (final) and its
-// aggregate (occupied voxels, stored points). A heavy brick is counted by the
-// block of its first part, which streams the parts in turn and writes, per
-// part and voxel, the brick's points in the parts before it (the second pass
-// places each part's points after them), then the per-voxel prefixes and the
-// voxels of more than kBigVoxel points. The blocks of further parts have
-// nothing to do here.
-__global__ __launch_bounds__(kBrickT) void k_brick_count(BrickArgs a) {
-    __shared__ CountLds s;
-    BrickItem it;
-    if (!brick_item(a, it) || it.part != 0) return;
-    const int tid = threadIdx.x;
-    const size_t wbase = (size_t)it.b * a.W + (size_t)it.q * kBrickW;
-    const int64_t wlim = a.W - (int64_t)it.q * kBrickW;  // words of this brick inside the grid
-    if (it.cnt == 0) {
-        if (tid < kBrickW && tid < wlim) a.bitmap[wbase + tid] = 0ull;
-        if (tid == 0) a.agg[it.g] = 0ull;
-        return;
-    }
-    if (tid < kBrickW) s.w.word[tid] = 0ull;
-    if (it.heavy)
-        for (int j = tid; j < kBrickV; j += kBrickT) s.cnt[j] = 0u;
-    lds_barrier();
-    uint32_t v[kBrickIPT], idx[kBrickIPT];
-    if (!it.heavy) {
-        brick_voxels<true>(a, s.w, it, v, idx);
-        lds_barrier();
-        brick_word_scan(s.w);
-        lds_barrier();
-        const uint32_t n_occ = s.w.nocc;
-        for (uint32_t j = tid; j < n_occ; j += kBrickT) s.cnt[j] = 0u;
-        lds_barrier();
-#pragma unroll
-        for (int k = 0; k < kBrickIPT; ++k)
-            if (threadIdx.x + k * kBrickT < it.n) atomicAdd(&s.cnt[brick_rank(s.w, v[k])], 1u);
-        lds_barrier();
-        uint64_t st = 0;
-        for (uint32_t j = tid; j < n_occ; j += kBrickT) st += s.cnt[j] < a.n_v ? s.cnt[j] : a.n_v;
-        st = block_sum64(st, s.wave);
-        if (tid < kBrickW && tid < wlim) a.bitmap[wbase + tid] = s.w.word[tid];
-        if (tid == 0) a.agg[it.g] = ((uint64_t)n_occ << 31) | st;
-        return;
-    }
-    // a heavy brick: its parts in turn; before each, the counts so far are that part's row
-    const int32_t hb = a.brick_hb[it.g];
-    const uint32_t eb = a.hebase[hb];
-    for (uint32_t p = 0; p < it.parts; ++p) {
-        BrickItem pt = it;
-        pt.part = p;
-        pt.p0 = it.start + p * (uint32_t)kBrickCap;
-        pt.n = it.start + it.cnt - pt.p0 < (uint32_t)kBrickCap ? it.start + it.cnt - pt.p0 : (uint32_t)kBrickCap;
-        brick_voxels<true>(a, s.w, pt, v, idx);
-        if (p != 0) {
-            uint32_t* row = a.pcnt + (size_t)(eb + p - 1) * kBrickV;
-            for (int j = tid; j < kBrickV; j += kBrickT) row[j] = s.cnt[j];
-        }
-        lds_barrier();
-#pragma unroll
-        for (int k = 0; k < kBrickIPT; ++k)
-            if (threadIdx.x + k * kBrickT < pt.n) atomicAdd(&s.cnt[v[k]], 1u);
-        lds_barrier();
-    }
-    brick_word_scan(s.w);
-    if (tid < kBrickW && tid < wlim) a.bitmap[wbase + tid] = s.w.word[tid];
-    constexpr int kPer = kBrickV / kBrickT;
-    uint32_t c[kPer];
-    uint64_t sum = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        c[j] = s.cnt[tid * kPer + j];
-        sum += ((uint64_t)c[j] << 32) | (c[j] < a.n_v ? c[j] : a.n_v);
-    }
-    uint64_t total;
-    uint64_t pos = brick_excl_scan(sum, s.wave, &total);
-    uint32_t* fo = a.hfo + (size_t)hb * (kBrickV + 1);
-    uint32_t* so = a.hso + (size_t)hb * kBrickV;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const uint32_t vv = tid * kPer + j;
-        fo[vv] = (uint32_t)(pos >> 32);
-        so[vv] = (uint32_t)pos;
-        pos += ((uint64_t)c[j] << 32) | (c[j] < a.n_v ? c[j] : a.n_v);
-    }
-    if (tid == 0) {
-        fo[kBrickV] = it.cnt;
-        a.agg[it.g] = ((uint64_t)s.w.nocc << 31) | (uint32_t)total;
-    }
-}
-
-// The n_v smallest of the cnt indices at p (in memory), sorted ascending over
-// the wave's lanes: 64-key chunks, four loaded at a time, each sorted by a
-// bitonic network and merged into the best so far; a chunk without an index
-// below the n_v-th best is skipped.
-__device__ __forceinline__ uint64_t wave_select_lowest(const uint32_t* p, uint32_t cnt, uint32_t n_v) {
-    const int lane = lane_id();
-    uint64_t best = ~0ull, kth = ~0ull;
-    for (uint32_t c0 = 0; c0 < cnt; c0 += 4 * kWave) {
-        uint64_t key[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t i = c0 + j * kWave + lane;
-            key[j] = i < cnt ? (uint64_t)p[i] : ~0ull;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (c0 + j * kWave >= cnt) break;
-            uint64_t k = key[j] < kth ? key[j] : ~0ull;
-            const bool first = c0 == 0 && j == 0;
-            if (!first && !__ballot(k != ~0ull)) continue;
-            k = wave_sort64(k);
-            best = first ? k : wave_merge_low64(best, k);
-            kth = shfl64(best, (int)n_v - 1);
-        }
-    }
-    return best;
-}
-
-struct BuildLds {
-    WordLds w;
-    uint64_t bigm[kBrickW];         // bit r: occupied voxel r holds more than kBigVoxel points
     union {
-        struct {
-            uint32_t va[kBrickCap + 1]; // per occupied voxel: count, then (stored prefix << 16 | point prefix)
-            uint32_t idx[kBrickCap];    // point indices grouped by voxel (arrival order)
-        } one;                          // a brick of one part
-        uint32_t arr[kBrickV];          // a part of a heavy brick: its arrivals per voxel
-    } u;
-    uint64_t wave[kScanThreads / kWave];
+        uint32_t cnt2[kBrickWaves][kBrickV / 2];  // points per voxel of a wave's brick, two 16-bit counts a
+                                                  // word (a block's part uses the first row)
+        uint32_t tot[kBrickV];                    // a heavy brick's points per voxel
+    };
+    uint64_t wave[kBrickWaves];
     uint32_t ticket;
 };
 
-// Pass 2 over the bricks: slots, offsets and stored lists. The aggregates of
-// the cloud's earlier bricks are summed directly (every one is final). A
-// brick of one part does everything in LDS; a part of a heavy brick groups
-// its points by voxel in `bucket`, and the last of its parts to finish then
-// selects the brick's lists from there.
-__global__ __launch_bounds__(kBrickT) void k_brick(BrickArgs a) {
-    __shared__ BuildLds s;
-    BrickItem it;
-    if (!brick_id(a, it)) return;
-    const int tid = threadIdx.x;
+// Counts a point of voxel v.
+__device__ __forceinline__ void count_voxel(uint32_t* cnt2, uint32_t v) {
+    atomicAdd(&cnt2[v >> 1], (v & 1u) ? 0x10000u : 1u);
+}
+
+// Pass 1 over the bricks: per brick its occupancy words (final) and its
+// aggregate (occupied voxels, stored points), from the points counted per
+// voxel in LDS: one ballot over 64 counts is an occupancy word. The blocks
+// after the first items_max take kBrickWaves bricks, `groups` apart
+// (neighbouring bricks, alike in size, go to different blocks), and count
+// those of at most kWavePts points by one wave each, without a barrier: most
+// bricks of an indoor scene hold under 100 points, and a wave's chain of loads
+// and LDS steps is no longer than a block's, so that every brick's wave is
+// resident at once. The blocks before them take a larger brick, or a part of
+// a heavy one, each; the last part of a heavy brick to finish turns the
+// parts' count rows into the counts before each part and sums them.
+__global__ __launch_bounds__(kBrickT) void k_brick_count(BrickArgs a) {
+    __shared__ CountLds s;
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const int32_t nw = a.words();
+    // from the brick's counts, cnt(v): its occupancy words and its stored
+    // points; called by one wave
+    auto finish = [&](auto cnt, const Brick& k) {
+        uint64_t mine = 0;
+        uint32_t st = 0, occ = 0;
+        for (int32_t j = 0; j < nw; ++j) {
+            const uint32_t c = cnt(j * kWave + lane);
+            const uint64_t bal = __ballot(c != 0);
+            mine = lane == j ? bal : mine;
+            occ += (uint32_t)__popcll(bal);
+            st += c < a.n_v ? c : a.n_v;
+        }
+        st = wave_sum_u32(st);
+        if (lane < nw && (int64_t)k.q * nw + lane < a.W) a.bitmap[(size_t)k.b * a.W + (size_t)k.q * nw + lane] = mine;
+        if (lane == 0) a.agg[k.g] = ((uint64_t)occ << 31) | st;
+    };
+    if (blockIdx.x >= (uint32_t)a.items_max) {
+        const int32_t g = (int32_t)blockIdx.x - a.items_max + wv * a.groups;
+        if (g >= a.BQ) return;
+        const Brick k = brick_at(a, g);
+        if (k.cnt > (uint32_t)kWavePts) return;
+        uint32_t* cnt2 = s.cnt2[wv];
+        uint4* c4 = reinterpret_cast<uint4*>(cnt2);
+        for (int32_t j = lane; j < nw * 8; j += kWave) c4[j] = make_uint4(0u, 0u, 0u, 0u);
+        wave_lds_order();
+        if (k.cnt) {
+            uint32_t v[kWaveIPT];
+            brick_voxels<kWaveIPT>(a, k.start, k.cnt, (uint32_t)lane, kWave, v);
+#pragma unroll
+            for (int j = 0; j < kWaveIPT; ++j)
+                if ((uint32_t)(lane + j * kWave) < k.cnt) count_voxel(cnt2, v[j]);
+        }
+        wave_lds_order();
+        finish([&](int32_t x) { return (uint32_t)reinterpret_cast<const uint16_t*>(cnt2)[x]; }, k);
+        return;
+    }
+    BrickPart p;
+    if (!brick_part_at(a, p)) return;
+    uint32_t* cnt2 = s.cnt2[0];
+    const uint16_t* cnt = reinterpret_cast<const uint16_t*>(cnt2);
+    const uint32_t nvx = a.voxels();
+    for (uint32_t j = tid; j < nvx / 2; j += kBrickT) cnt2[j] = 0u;
+    lds_barrier();
+#pragma unroll
+    for (int h = 0; h < kBrickIPT; h += kLoadIPT) {
+        if ((uint32_t)(h * kBrickT) < p.n) {
+            uint32_t v[kLoadIPT];
+            brick_voxels<kLoadIPT>(a, p.p0, p.n, (uint32_t)(tid + h * kBrickT), kBrickT, v);
+#pragma unroll
+            for (int j = 0; j < kLoadIPT; ++j)
+                if ((uint32_t)(tid + (h + j) * kBrickT) < p.n) count_voxel(cnt2, v[j]);
+        }
+    }
+    lds_barrier();
+    if (p.hb < 0) {
+        if (wv == 0) finish([&](int32_t x) { return (uint32_t)cnt[x]; }, p.k);
+        return;
+    }
+    const uint32_t parts = a.hparts[p.hb];
+    uint32_t* row = a.pcnt + (size_t)a.hfirst[p.hb] * nvx;
+    for (uint32_t j = tid; j < nvx; j += kBrickT) row[(size_t)p.part * nvx + j] = cnt[j];
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) s.ticket = atomicAdd(&a.hdone[p.hb], 1u);
+    __syncthreads();
+    if (s.ticket != parts - 1) return;
+    __threadfence();
+    for (uint32_t j = tid; j < nvx; j += kBrickT) {
+        uint32_t run = 0;
+        for (uint32_t i = 0; i < parts; ++i) {
+            const uint32_t x = row[(size_t)i * nvx + j];
+            row[(size_t)i * nvx + j] = run;
+            run += x;
+        }
+        s.tot[j] = run;
+        a.htot[(size_t)p.hb * nvx + j] = run;
+    }
+    lds_barrier();
+    if (wv == 0) finish([&](int32_t x) { return s.tot[x]; }, p.k);
+    const uint32_t per = (nvx + kBrickT - 1) / kBrickT, x0 = (uint32_t)tid * per;  // nvx is a power of two
+    uint64_t sum = 0;
+    for (uint32_t x = x0; x < x0 + per && x < nvx; ++x) sum += s.tot[x] < a.n_v ? s.tot[x] : a.n_v;
+    uint64_t total;
+    uint32_t pos = (uint32_t)brick_excl_scan(sum, s.wave, &total);
+    for (uint32_t x = x0; x < x0 + per && x < nvx; ++x) {
+        a.hso[(size_t)p.hb * nvx + x] = pos;
+        pos += s.tot[x] < a.n_v ? s.tot[x] : a.n_v;
+    }
+}
+
+// The lists of one wave's brick, and of a block's.
+struct WaveLists {
+    WordLds w;
+    uint32_t va[kWavePts + 1];  // per occupied voxel: count, then (stored prefix << 16 | point prefix)
+    uint32_t idx[kWavePts];     // point indices grouped by voxel (arrival order)
+    uint16_t vox[kWavePts];     // the occupied voxels
+};
+
+struct BlockLists {
+    WordLds w;
+    uint64_t bigm[kBrickW];     // bit r: occupied voxel r holds more than kBigVoxel points
+    uint32_t va[kBrickV + 1];
+    uint32_t idx[kBrickCap];
+    uint16_t vox[kBrickV];
+    uint64_t wave[kBrickWaves];
+};
+
+union BuildLds {
+    WaveLists wl[kBrickWaves];
+    BlockLists bl;
+};
+
+// A voxel of c > kBigVoxel points at p (LDS): one wave writes its `keep`
+// lowest indices and their points to the stored positions from dst on.
+__device__ __forceinline__ void wave_big_voxel(const BrickArgs& a, const uint32_t* p, uint32_t c, uint32_t keep,
+                                               size_t pb, size_t dst) {
     const int lane = lane_id();
-    const int wv = tid / kWave;
-    // the cloud's bricks before this one (loads issued with the range's,
-    // four per thread at a time)
-    uint64_t pre = 0;
-    const uint64_t* ag = a.agg + (size_t)it.b * a.Q;
-    for (int32_t j0 = 0; j0 < it.q; j0 += 4 * kBrickT) {
-        uint64_t x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int32_t j = j0 + u * kBrickT + tid;
-            x[u] = j < it.q ? ag[j] : 0ull;
-        }
-        pre += (x[0] + x[1]) + (x[2] + x[3]);
+    uint64_t best = ~0ull, kth = ~0ull;
+    for (uint32_t c0 = 0; c0 < c; c0 += kWave) {
+        uint64_t key = (c0 + lane < c) ? (uint64_t)p[c0 + lane] : ~0ull;
+        // an index above the keep-th lowest so far is never kept
+        key = key < kth ? key : ~0ull;
+        if (c0 != 0 && !__ballot(key != ~0ull)) continue;
+        key = wave_sort64(key);
+        best = c0 == 0 ? key : wave_merge_low64(best, key);
+        kth = shfl64(best, (int)keep - 1);
     }
-    const uint64_t my = ag[it.q];
-    brick_range(a, it);
-    const uint32_t vbase = (uint32_t)it.q * kBrickV;
-    const size_t pb = (size_t)it.b * a.N;
-    const size_t wbase = (size_t)it.b * a.W + (size_t)it.q * kBrickW;
-    const int64_t wlim = a.W - (int64_t)it.q * kBrickW;
-    uint32_t* vo = a.vox_off + (size_t)it.b * (a.N + 1);
-    if (tid < kBrickW) {
-        s.w.word[tid] = it.heavy ? (tid < wlim ? a.bitmap[wbase + tid] : 0ull) : 0ull;
-        s.bigm[tid] = 0ull;
+    if ((uint32_t)lane < keep) {
+        const uint32_t i = (uint32_t)best;
+        const float* q = a.P + (pb + i) * 3;
+        a.pt_list[dst + lane] = i;
+        a.pt4[dst + lane] = make_float4(q[0], q[1], q[2], __uint_as_float(i));
     }
-    pre = block_sum64(pre, s.wave);  // its barrier also publishes the words
+}
+
+// A brick of at most kWavePts points: slots, offsets and stored lists by one
+// wave, in LDS, without a barrier. `word`: lane l's occupancy word.
+__device__ __forceinline__ void brick_by_wave(const BrickArgs& a, WaveLists& s, const Brick& k, uint64_t pre,
+                                              uint32_t n_occ, uint64_t word) {
+    const int lane = lane_id();
     const uint32_t p_occ = (uint32_t)(pre >> 31), p_st = (uint32_t)(pre & 0x7FFFFFFFu);
-    if (it.cnt == 0) {
-        if (tid < kBrickW && tid < wlim) a.word_rank[wbase + tid] = p_occ;
-        if (it.q == a.Q - 1 && tid == 0) {
-            a.nvox[it.b] = (int32_t)p_occ;
-            vo[p_occ] = p_st;
-        }
-        return;
+    const int32_t nw = a.words();
+    const uint32_t vbase = (uint32_t)k.q * a.voxels();
+    const size_t pb = (size_t)k.b * a.N;
+    // the points' loads go out first
+    uint32_t v[kWaveIPT], idx[kWaveIPT];
+    float x[kWaveIPT], y[kWaveIPT], z[kWaveIPT];
+    if (k.cnt) {
+        brick_voxels<kWaveIPT>(a, k.start, k.cnt, (uint32_t)lane, kWave, v);
+        brick_points<kWaveIPT>(a, k.start, k.cnt, (uint32_t)lane, kWave, x, y, z, idx);
     }
+    const uint32_t wr = brick_put_words(s.w, word);
+    if (lane < nw && (int64_t)k.q * nw + lane < a.W)
+        a.word_rank[(size_t)k.b * a.W + (size_t)k.q * nw + lane] = p_occ + wr;
+    if (k.cnt == 0) return;
+    for (uint32_t j = lane; j <= n_occ; j += kWave) s.va[j] = 0u;
+    wave_lds_order();
+    // voxel rank and arrival position of every point; the first arrival
+    // names the voxel
+#pragma unroll
+    for (int j = 0; j < kWaveIPT; ++j) {
+        if ((uint32_t)(lane + j * kWave) < k.cnt) {
+            const uint32_t r = brick_rank(s.w, v[j]);
+            const uint32_t pos = atomicAdd(&s.va[r], 1u);
+            if (pos == 0) s.vox[r] = (uint16_t)v[j];
+            v[j] = (r << 16) | pos;
+        }
+    }
+    wave_lds_order();
+    // exclusive prefixes of (count, stored), packed as stored << 16 | count,
+    // and the slots' own outputs, 64 occupied voxels at a time
+    uint32_t run = 0;
+    uint64_t big[kWaveIPT];  // voxels of more than kBigVoxel points
+#pragma unroll
+    for (int j = 0; j < kWaveIPT; ++j) {
+        big[j] = 0;
+        if ((uint32_t)(j * kWave) >= n_occ) continue;
+        const uint32_t r = (uint32_t)(j * kWave + lane);
+        const uint32_t c = r < n_occ ? s.va[r] : 0u;
+        const uint32_t both = ((c < a.n_v ? c : a.n_v) << 16) | c;
+        const uint32_t incl = wave_incl_sum_u32(both);
+        const uint32_t ex = run + incl - both;
+        run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+        big[j] = __ballot(c > kBigVoxel);
+        if (r < n_occ) {
+            s.va[r] = ex;
+            const size_t slot = pb + p_occ + r;
+            a.vox_lin[slot] = vbase + s.vox[r];
+            a.vox_count[slot] = c;
+            a.vox_off[slot + k.b] = p_st + (ex >> 16);
+        }
+    }
+    if (lane == 0) s.va[n_occ] = run;
+    wave_lds_order();
+#pragma unroll
+    for (int j = 0; j < kWaveIPT; ++j)
+        if ((uint32_t)(lane + j * kWave) < k.cnt) s.idx[(s.va[v[j] >> 16] & 0xFFFFu) + (v[j] & 0xFFFFu)] = idx[j];
+    wave_lds_order();
+    // stored lists: a point of a voxel of at most kBigVoxel points by its rank
+#pragma unroll
+    for (int j = 0; j < kWaveIPT; ++j) {
+        uint32_t c = 0, f0 = 0, rank = 0, o = 0;
+        if ((uint32_t)(lane + j * kWave) < k.cnt) {
+            const uint32_t r = v[j] >> 16;
+            o = s.va[r];
+            f0 = o & 0xFFFFu;
+            c = (s.va[r + 1] & 0xFFFFu) - f0;
+        }
+        if (c <= kBigVoxel) {
+            for (uint32_t i = 0; i < c; ++i) rank += s.idx[f0 + i] < idx[j] ? 1u : 0u;
+            if (c && rank < a.n_v) {
+                const size_t dst = pb + p_st + (o >> 16) + rank;
+                a.pt_list[dst] = idx[j];
+                a.pt4[dst] = make_float4(x[j], y[j], z[j], __uint_as_float(idx[j]));
+            }
+        }
+    }
+    // larger voxels: the n_v smallest indices by bitonic selection
+#pragma unroll
+    for (int j = 0; j < kWaveIPT; ++j) {
+        for (uint64_t m = big[j]; m; m &= m - 1) {
+            const uint32_t r = (uint32_t)(j * kWave + __ffsll((unsigned long long)m) - 1);
+            const uint32_t o = s.va[r], f0 = o & 0xFFFFu, c = (s.va[r + 1] & 0xFFFFu) - f0;
+            wave_big_voxel(a, s.idx + f0, c, a.n_v, pb, pb + p_st + (o >> 16));
+        }
+    }
+}
+
+// A larger brick, or a part of a heavy one: the same by a block. A heavy
+// brick's slots come from its totals, written by its first part, and its
+// points rank after those of their voxel in the parts before.
+__device__ __forceinline__ void brick_by_block(const BrickArgs& a, BlockLists& s, const BrickPart& p, uint64_t pre,
+                                               uint32_t n_occ, uint64_t word) {
+    const Brick& k = p.k;
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const uint32_t p_occ = (uint32_t)(pre >> 31), p_st = (uint32_t)(pre & 0x7FFFFFFFu);
+    const int32_t nw = a.words();
+    const uint32_t nvx = a.voxels(), vbase = (uint32_t)k.q * nvx;
+    const size_t pb = (size_t)k.b * a.N;
+    const bool heavy = p.hb >= 0;
+    const uint32_t* before = heavy ? a.pcnt + (size_t)(a.hfirst[p.hb] + p.part) * nvx : nullptr;
+    const uint32_t* so = heavy ? a.hso + (size_t)p.hb * nvx : nullptr;
+    uint32_t* va = s.va;  // n_occ + 1 entries
+    // the points' loads go out first
     uint32_t v[kBrickIPT], idx[kBrickIPT];
-    if (it.heavy) brick_voxels<false>(a, s.w, it, v, idx);
-    else brick_voxels<true>(a, s.w, it, v, idx);
-    lds_barrier();
-    brick_word_scan(s.w);
-    lds_barrier();
-    const uint32_t n_occ = (uint32_t)(my >> 31);
-    if (it.part == 0) {
-        if (tid < kBrickW && tid < wlim) a.word_rank[wbase + tid] = p_occ + s.w.wocc[tid];
-        if (it.q == a.Q - 1 && tid == 0) {
-            a.nvox[it.b] = (int32_t)(p_occ + n_occ);
-            vo[p_occ + n_occ] = p_st + (uint32_t)(my & 0x7FFFFFFFu);
-        }
-        if (it.heavy && tid == 0) a.hpre[a.brick_hb[it.g]] = pre;
+    float x[kBrickIPT], y[kBrickIPT], z[kBrickIPT];
+    brick_voxels<kBrickIPT>(a, p.p0, p.n, (uint32_t)tid, kBrickT, v);
+    brick_points<kBrickIPT>(a, p.p0, p.n, (uint32_t)tid, kBrickT, x, y, z, idx);
+    if (wv == 0) {
+        const uint32_t wr = brick_put_words(s.w, word);
+        if (p.part == 0 && lane < nw && (int64_t)k.q * nw + lane < a.W)
+            a.word_rank[(size_t)k.b * a.W + (size_t)k.q * nw + lane] = p_occ + wr;
     }
-    if (it.heavy) {
-        // a point's position within its voxel: the voxel's points in the
-        // parts before this one, then its arrival in this part
-        const int32_t hb = a.brick_hb[it.g];
-        const uint32_t* before = it.part == 0 ? nullptr : a.pcnt + (size_t)(a.hebase[hb] + it.part - 1) * kBrickV;
-        const uint32_t* fo = a.hfo + (size_t)hb * (kBrickV + 1);
-        const uint32_t* so = a.hso + (size_t)hb * kBrickV;
-        for (int j = tid; j < kBrickV; j += kBrickT) s.u.arr[j] = 0u;
-        lds_barrier();
-        // every point's loads first, then the stores
-        uint32_t bf[kBrickIPT], f0s[kBrickIPT], f1s[kBrickIPT], sos[kBrickIPT];
-#pragma unroll
-        for (int k = 0; k < kBrickIPT; ++k) {
-            const bool in = threadIdx.x + k * kBrickT < it.n;
-            bf[k] = in && before ? before[v[k]] : 0u;
-            f0s[k] = in ? fo[v[k]] : 0u;
-            f1s[k] = in ? fo[v[k] + 1] : 0u;
-            sos[k] = in ? so[v[k]] : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < kBrickIPT; ++k) {
-            if (threadIdx.x + k * kBrickT >= it.n) break;
-            const uint32_t ps = bf[k] + atomicAdd(&s.u.arr[v[k]], 1u);
-            const uint32_t f0 = f0s[k];
-            a.bucket[it.start + f0 + ps] = idx[k];
-            if (ps == 0) {
-                const uint32_t slot = p_occ + brick_rank(s.w, v[k]);
-                a.vox_lin[pb + slot] = vbase + v[k];
-                a.vox_count[pb + slot] = f1s[k] - f0;
-                vo[slot] = p_st + sos[k];
-            }
-        }
-        // the last part to finish selects the brick's stored lists: a point
-        // of a voxel of at most kBigVoxel points by its rank (one lane per
-        // point), a larger voxel by one wave's bitonic selection
-        __threadfence();
-        __syncthreads();
-        if (tid == 0) s.ticket = atomicAdd(&a.hdone[hb], 1u);
-        __syncthreads();
-        if (s.ticket != it.parts - 1) return;
-        __threadfence();
-        const uint32_t* bk = a.bucket + it.start;
-        for (uint32_t i = tid; i < it.cnt; i += kBrickT) {
-            const float4 e = a.sorted[it.start + i];
-            bool bad = false;
-            const uint32_t vv = voxel_lin(e.x, e.y, e.z, a.g, bad) - vbase;
-            const uint32_t f0 = fo[vv], c = fo[vv + 1] - f0;
-            if (c > kBigVoxel) continue;
-            const uint32_t id = __float_as_uint(e.w);
-            uint32_t rank = 0;
-            for (uint32_t j = 0; j < c; ++j) rank += bk[f0 + j] < id ? 1u : 0u;
-            if (rank < a.n_v) {
-                const size_t dst = pb + p_st + so[vv] + rank;
-                a.pt_list[dst] = id;
-                a.pt4[dst] = e;
-            }
-        }
-        for (uint32_t ch = tid / kWave; ch < (uint32_t)kBrickV / kWave; ch += kBrickWaves) {
-            const uint32_t f0v = fo[ch * kWave + lane], cv = fo[ch * kWave + lane + 1] - f0v;
-            const uint32_t sov = so[ch * kWave + lane];
-            for (uint64_t m = __ballot(cv > kBigVoxel); m; m &= m - 1) {
-                const int l = __ffsll((unsigned long long)m) - 1;
-                const uint32_t f0 = (uint32_t)__shfl((int)f0v, l, kWave);
-                const uint32_t cnt = (uint32_t)__shfl((int)cv, l, kWave);
-                const uint32_t sl = (uint32_t)__shfl((int)sov, l, kWave);
-                const uint64_t best = wave_select_lowest(bk + f0, cnt, a.n_v);
-                if ((uint32_t)lane < a.n_v) {
-                    const uint32_t i = (uint32_t)best;
-                    const size_t dst = pb + p_st + sl + lane;
-                    const float* p = a.P + (pb + i) * 3;
-                    a.pt_list[dst] = i;
-                    a.pt4[dst] = make_float4(p[0], p[1], p[2], __uint_as_float(i));
-                }
-            }
-        }
-        return;
-    }
-    // a brick of one part: counts per occupied voxel, arrival positions
-    uint32_t* va = s.u.one.va;  // n_occ + 1 entries
+    if (tid < kBrickW) s.bigm[tid] = 0ull;
     for (uint32_t j = tid; j <= n_occ; j += kBrickT) va[j] = 0u;
     lds_barrier();
-    uint32_t r[kBrickIPT], pos[kBrickIPT];
+    // voxel rank and arrival position of every point; the first arrival names
+    // the voxel
 #pragma unroll
-    for (int k = 0; k < kBrickIPT; ++k) {
-        r[k] = 0u;
-        pos[k] = 0u;
-        if (threadIdx.x + k * kBrickT < it.n) {
-            r[k] = brick_rank(s.w, v[k]);
-            pos[k] = atomicAdd(&va[r[k]], 1u);
+    for (int j = 0; j < kBrickIPT; ++j) {
+        if ((uint32_t)(tid + j * kBrickT) < p.n) {
+            const uint32_t r = brick_rank(s.w, v[j]);
+            const uint32_t pos = atomicAdd(&va[r], 1u);
+            if (pos == 0) s.vox[r] = (uint16_t)v[j];
+            v[j] = (r << 16) | pos;
         }
     }
     lds_barrier();
-    // the points' coordinates, loaded again for the stored lists (issued here
-    // so that the scan and grouping below hide their latency)
-    float4 e[kBrickIPT];
-#pragma unroll
-    for (int k = 0; k < kBrickIPT; ++k)
-        if (threadIdx.x + k * kBrickT < it.n) e[k] = a.sorted[it.p0 + threadIdx.x + k * kBrickT];
     // exclusive prefixes of (count, stored) over the occupied voxels, packed
     // as stored << 16 | count (both at most kBrickCap)
     const uint32_t per = (n_occ + kBrickT - 1) / kBrickT;
@@ -1055,60 +1095,126 @@ __global__ __launch_bounds__(kBrickT) void k_brick(BrickArgs a) {
         if (c > kBigVoxel) atomicOr(reinterpret_cast<unsigned long long*>(&s.bigm[rr >> 6]), 1ull << (rr & 63));
         run += ((c < a.n_v ? c : a.n_v) << 16) | c;
     }
-    if (tid == 0) va[n_occ] = it.cnt;
+    if (tid == 0) va[n_occ] = p.n;
     lds_barrier();
-    // the points grouped by voxel; the first arrival in a voxel writes its slot
+    // the points grouped by voxel, and the slots' own outputs
 #pragma unroll
-    for (int k = 0; k < kBrickIPT; ++k) {
-        if (threadIdx.x + k * kBrickT >= it.n) break;
-        const uint32_t o = va[r[k]], f0 = o & 0xFFFFu;
-        s.u.one.idx[f0 + pos[k]] = idx[k];
-        if (pos[k] == 0) {
-            const uint32_t slot = p_occ + r[k];
-            a.vox_lin[pb + slot] = vbase + v[k];
-            a.vox_count[pb + slot] = (va[r[k] + 1] & 0xFFFFu) - f0;
-            vo[slot] = p_st + (o >> 16);
+    for (int j = 0; j < kBrickIPT; ++j)
+        if ((uint32_t)(tid + j * kBrickT) < p.n) s.idx[(va[v[j] >> 16] & 0xFFFFu) + (v[j] & 0xFFFFu)] = idx[j];
+    if (!heavy) {
+        for (uint32_t r = tid; r < n_occ; r += kBrickT) {
+            const uint32_t o = va[r];
+            const size_t slot = pb + p_occ + r;
+            a.vox_lin[slot] = vbase + s.vox[r];
+            a.vox_count[slot] = (va[r + 1] & 0xFFFFu) - (o & 0xFFFFu);
+            a.vox_off[slot + k.b] = p_st + (o >> 16);
+        }
+    } else if (p.part == 0) {
+        for (uint32_t u = tid; u < nvx; u += kBrickT) {
+            const uint32_t c = a.htot[(size_t)p.hb * nvx + u];
+            if (!c) continue;
+            const size_t slot = pb + p_occ + brick_rank(s.w, u);
+            a.vox_lin[slot] = vbase + u;
+            a.vox_count[slot] = c;
+            a.vox_off[slot + k.b] = p_st + so[u];
         }
     }
     lds_barrier();
-    // stored lists: a point of a voxel of at most kBigVoxel points by its rank
+    // stored lists: a point of a voxel of at most kBigVoxel points (of this
+    // part) by its rank
 #pragma unroll
-    for (int k = 0; k < kBrickIPT; ++k) {
-        if (threadIdx.x + k * kBrickT >= it.n) break;
-        const uint32_t o = va[r[k]], f0 = o & 0xFFFFu, c = (va[r[k] + 1] & 0xFFFFu) - f0;
-        if (c > kBigVoxel) continue;
-        uint32_t rank = 0;
-        for (uint32_t j = 0; j < c; ++j) rank += s.u.one.idx[f0 + j] < idx[k] ? 1u : 0u;
-        if (rank < a.n_v) {
-            const size_t dst = pb + p_st + (o >> 16) + rank;
-            a.pt_list[dst] = idx[k];
-            a.pt4[dst] = e[k];
+    for (int j = 0; j < kBrickIPT; ++j) {
+        uint32_t r = 0, c = 0, f0 = 0, rank = 0, at0 = 0;
+        if ((uint32_t)(tid + j * kBrickT) < p.n) {
+            r = v[j] >> 16;
+            at0 = va[r];
+            f0 = at0 & 0xFFFFu;
+            c = (va[r + 1] & 0xFFFFu) - f0;
+            at0 >>= 16;
+        }
+        if (c <= kBigVoxel) {
+            for (uint32_t i = 0; i < c; ++i) rank += s.idx[f0 + i] < idx[j] ? 1u : 0u;
+            if (heavy && c) {
+                rank += before[s.vox[r]];
+                at0 = so[s.vox[r]];
+            }
+            if (c && rank < a.n_v) {
+                const size_t dst = pb + p_st + at0 + rank;
+                a.pt_list[dst] = idx[j];
+                a.pt4[dst] = make_float4(x[j], y[j], z[j], __uint_as_float(idx[j]));
+            }
         }
     }
-    // larger voxels: one wave each, the n_v smallest indices by bitonic selection
+    // larger voxels: one wave each
     for (int j = wv; j < kBrickW; j += kBrickWaves) {
         for (uint64_t m = s.bigm[j]; m; m &= m - 1) {
-            const uint32_t rr = (uint32_t)j * kWave + (uint32_t)(__ffsll((unsigned long long)m) - 1);
-            const uint32_t o = va[rr], f0 = o & 0xFFFFu, c = (va[rr + 1] & 0xFFFFu) - f0;
-            uint64_t best = ~0ull, kth = ~0ull;
-            for (uint32_t c0 = 0; c0 < c; c0 += kWave) {
-                uint64_t key = (c0 + lane < c) ? (uint64_t)s.u.one.idx[f0 + c0 + lane] : ~0ull;
-                // an index above the n_v-th lowest so far is never kept
-                key = key < kth ? key : ~0ull;
-                if (c0 != 0 && !__ballot(key != ~0ull)) continue;
-                key = wave_sort64(key);
-                best = c0 == 0 ? key : wave_merge_low64(best, key);
-                kth = shfl64(best, (int)a.n_v - 1);
-            }
-            if ((uint32_t)lane < a.n_v) {
-                const uint32_t i = (uint32_t)best;
-                const size_t dst = pb + p_st + (o >> 16) + lane;
-                const float* p = a.P + (pb + i) * 3;
-                a.pt_list[dst] = i;
-                a.pt4[dst] = make_float4(p[0], p[1], p[2], __uint_as_float(i));
-            }
+            const uint32_t r = (uint32_t)j * kWave + (uint32_t)(__ffsll((unsigned long long)m) - 1);
+            const uint32_t o = va[r], f0 = o & 0xFFFFu, c = (va[r + 1] & 0xFFFFu) - f0;
+            const uint32_t bf = heavy ? before[s.vox[r]] : 0u, at0 = heavy ? so[s.vox[r]] : o >> 16;
+            if (bf < a.n_v) wave_big_voxel(a, s.idx + f0, c, a.n_v - bf, pb, pb + p_st + at0 + bf);
         }
     }
+}
+
+// The aggregate of the cloud's bricks before brick q (every one is final),
+// in every lane of the wave; the loads go out together, 16 per lane.
+__device__ __forceinline__ uint64_t brick_prefix(const uint64_t* ag, int32_t q) {
+    const int lane = lane_id();
+    uint64_t pre = 0;
+    for (int32_t j0 = 0; j0 < q; j0 += 16 * kWave) {
+        uint64_t x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int32_t j = j0 + u * kWave + lane;
+            x[u] = j < q ? ag[j] : 0ull;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) pre += x[u];
+    }
+    return wave_sum<uint64_t>(pre);
+}
+
+// Pass 2 over the bricks: slots, offsets and stored lists, split over the
+// blocks as in pass 1: a wave per brick of at most kWavePts points (no barrier
+// at all), a block per item. Bound by the chain of loads and LDS steps of its
+// largest bricks, not by bandwidth. Measured, first layer of four indoor
+// scenes (81920 points each, 0.05 voxels): 46 -> 15 us against a block per
+// brick of up to 2048 points, whose heavy bricks were finished by the last of
+// their parts alone (and 13 -> 8 us for pass 1); one such scene on 0.1 voxels,
+// ten heavy bricks: 153 -> 10 us. Waves that took up to 512 points, with the
+// larger bricks after them in the same blocks, measured 54 us.
+__global__ __launch_bounds__(kBrickT) void k_brick(BrickArgs a) {
+    __shared__ BuildLds s;
+    const int lane = lane_id(), wv = threadIdx.x / kWave;
+    const int32_t nw = a.words();
+    auto load_word = [&](int32_t b, int32_t q) {
+        const bool in = lane < nw && (int64_t)q * nw + lane < a.W;
+        return in ? a.bitmap[(size_t)b * a.W + (size_t)q * nw + lane] : 0ull;
+    };
+    if (blockIdx.x < (uint32_t)a.items_max) {
+        BrickPart p;
+        if (!brick_part_at(a, p)) return;
+        const uint64_t* ag = a.agg + (size_t)p.k.b * a.Q;
+        const uint64_t word = load_word(p.k.b, p.k.q);
+        const uint32_t n_occ = (uint32_t)(ag[p.k.q] >> 31);
+        brick_by_block(a, s.bl, p, brick_prefix(ag, p.k.q), n_occ, word);
+        return;
+    }
+    const int32_t g = (int32_t)blockIdx.x - a.items_max + wv * a.groups;
+    if (g >= a.BQ) return;
+    const Brick k = brick_at(a, g);
+    const bool last = k.q == a.Q - 1;
+    if (k.cnt > (uint32_t)kWavePts && !last) return;
+    const uint64_t* ag = a.agg + (size_t)k.b * a.Q;
+    const uint64_t word = load_word(k.b, k.q);
+    const uint64_t my = ag[k.q];
+    const uint64_t pre = brick_prefix(ag, k.q);
+    if (last && lane == 0) {
+        const uint64_t all = pre + my;
+        a.nvox[k.b] = (int32_t)(all >> 31);
+        a.vox_off[(size_t)k.b * (a.N + 1) + (all >> 31)] = (uint32_t)(all & 0x7FFFFFFFu);
+    }
+    if (k.cnt <= (uint32_t)kWavePts) brick_by_wave(a, s.wl[wv], k, pre, (uint32_t)(my >> 31), word);
 }
 
 // ---- small clouds: the whole build in one workgroup per cloud.
@@ -1382,30 +1488,33 @@ hipError_t launch_build(const float* points, const Layout& L, const cagq_grid_de
         const int32_t BQ = B * L.Q;
         uint32_t* hist = at<uint32_t>(ws, L.hist);
         int* status_w = at<int>(ws, L.status);
-        k_bhist<<<(unsigned)L.T, kSortT, 0, s>>>(points, N, BN, g, L.Q, BQ, L.T, L.tile_scan, hist,
+        const BrickLists lists{at<BrickItem>(ws, L.item), at<uint32_t>(ws, L.hfirst), at<uint32_t>(ws, L.hparts),
+                               status_w};
+        k_bhist<<<(unsigned)L.T, kSortT, 0, s>>>(points, N, BN, g, L.Q, BQ, L.wshift + 6, L.T, L.tile_scan, hist,
                                                  at<uint4>(ws, L.status), (int64_t)(L.clear_brick - L.status) / 16);
         if (!L.tile_scan)
             k_hscan<<<(unsigned)((BQ + kHGroup - 1) / kHGroup), kScanThreads, 0, s>>>(
-                hist, BQ, L.T, at<uint32_t>(ws, L.bstart), at<int32_t>(ws, L.brick_hb), at<uint64_t>(ws, L.item_extra),
-                at<uint32_t>(ws, L.hlist), at<uint32_t>(ws, L.hebase), at<uint64_t>(ws, L.desc_h), status_w);
+                hist, N, L.Q, BQ, L.T, at<uint32_t>(ws, L.bstart), lists, at<uint64_t>(ws, L.desc_h), status_w);
         (L.tile_scan ? k_bscatter<true> : k_bscatter<false>)<<<(unsigned)L.T, kSortT, 0, s>>>(
-            points, N, BN, g, L.Q, BQ, hist, at<float4>(ws, L.sorted), at<uint32_t>(ws, L.bstart),
-            at<int32_t>(ws, L.brick_hb), at<uint64_t>(ws, L.item_extra), at<uint32_t>(ws, L.hlist),
-            at<uint32_t>(ws, L.hebase), status_w);
+            points, N, BN, g, L.Q, BQ, L.wshift + 6, hist, at<float4>(ws, L.sorted), at<uint16_t>(ws, L.svox), at<uint32_t>(ws, L.bstart),
+            lists, status_w);
         BrickArgs a;
         a.P = points;
         a.N = N;
         a.BN = BN;
         a.Q = L.Q;
         a.BQ = BQ;
+        a.wshift = L.wshift;
+        a.groups = (BQ + kBrickWaves - 1) / kBrickWaves;
         a.W = L.W;
         a.n_v = (uint32_t)d.n_v;
-        a.g = g;
         a.bstart = at<uint32_t>(ws, L.bstart);
-        a.brick_hb = at<int32_t>(ws, L.brick_hb);
-        a.item_extra = at<uint64_t>(ws, L.item_extra);
-        a.hlist = at<uint32_t>(ws, L.hlist);
+        a.items_max = (int32_t)L.items_max;
+        a.item = lists.item;
+        a.hfirst = lists.hfirst;
+        a.hparts = lists.hparts;
         a.sorted = at<float4>(ws, L.sorted);
+        a.svox = at<uint16_t>(ws, L.svox);
         a.bitmap = at<uint64_t>(ws, L.bitmap);
         a.word_rank = at<uint32_t>(ws, L.word_rank);
         a.vox_lin = at<uint32_t>(ws, L.vox_lin);
@@ -1415,16 +1524,13 @@ hipError_t launch_build(const float* points, const Layout& L, const cagq_grid_de
         a.pt_list = at<uint32_t>(ws, L.pt_list);
         a.pt4 = at<float4>(ws, L.pt4);
         a.agg = at<uint64_t>(ws, L.agg);
-        a.bucket = at<uint32_t>(ws, L.bucket);
-        a.hebase = at<uint32_t>(ws, L.hebase);
         a.pcnt = at<uint32_t>(ws, L.pcnt);
         a.hdone = at<uint32_t>(ws, L.hdone);
-        a.hfo = at<uint32_t>(ws, L.hfo);
+        a.htot = at<uint32_t>(ws, L.htot);
         a.hso = at<uint32_t>(ws, L.hso);
-        a.hpre = at<uint64_t>(ws, L.hpre);
         a.status = status_w;
-        k_brick_count<<<(unsigned)L.items_max, kBrickT, 0, s>>>(a);
-        k_brick<<<(unsigned)L.items_max, kBrickT, 0, s>>>(a);
+        k_brick_count<<<(unsigned)(a.items_max + a.groups), kBrickT, 0, s>>>(a);
+        k_brick<<<(unsigned)(a.items_max + a.groups), kBrickT, 0, s>>>(a);
         return hipGetLastError();
     }
     size_t n16 = (L.clear_end - L.status) / 16;

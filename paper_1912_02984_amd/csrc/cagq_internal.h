@@ -22,12 +22,14 @@ constexpr int kRankTile = kScanThreads * kRankItems;
 constexpr uint32_t kBigVoxel = 64;      // voxels holding more points use the wave selector
 constexpr int kSelBins = 2048;          // bins of the 11-bit digits of the many-block select
 constexpr int kSelChunk = 4096;         // slots per chunk of the many-block select
-constexpr int kBrickW = 32;             // occupancy words per brick of the brick build
-constexpr int kBrickV = kBrickW * 64;   // voxels per brick (a run of consecutive linear ids)
+constexpr int kBrickW = 32;             // most occupancy words per brick of the brick build
+constexpr int kBrickV = kBrickW * 64;   // most voxels per brick (a run of consecutive linear ids)
+constexpr int kMinBrickW = 4;           // fewest words per brick
 constexpr int32_t kMaxBricks = 8192;    // bricks over the batch the brick build's histograms hold
 constexpr int kSortTile = 4096;         // points per tile of the brick histogram and scatter
-constexpr int kBrickT = 256;            // threads per brick work item
-constexpr int kBrickCap = 2048;         // points per brick work item (heavier bricks are split)
+constexpr int kBrickT = 512;            // threads of a block of the brick passes
+constexpr int kWavePts = 256;           // points of a brick that one wave builds
+constexpr int kBrickCap = 4096;         // points of a brick, or of a part of a larger one, that one block builds
 constexpr int64_t kTileScanCap = 1 << 16;  // histogram entries a scatter tile may sum (tiles of a cloud x Q)
 
 // Status word slots (int32 each) at the start of the workspace's control block.
@@ -39,8 +41,9 @@ enum StatusSlot {
     kStTicketSel = 4,  // tile tickets of the center compaction scan
     kStTicketCtx = 5,  // tile tickets of the context-offsets scan
     kStTicketHist = 6, // tile tickets of the brick-histogram scan
-    kStItems = 7,      // brick build: work items (bricks and parts of heavy bricks)
-    kStHeavy = 8,      // brick build: bricks of more than kBrickCap points
+    kStItems = 7,      // brick build: work items (bricks of more than kWavePts points, or their parts)
+    kStHeavy = 8,      // brick build: bricks of more than kBrickCap points (heavy)
+    kStRows = 9,       // brick build: parts of heavy bricks
     kStSlots = 16
 };
 
@@ -53,13 +56,15 @@ struct Layout {
     int64_t tiles_w;      // rank-scan tiles (kRankTile words) over the words of one cloud
     int64_t tiles_s;      // scan tiles over the slots of one cloud
     int64_t big_cap;      // capacity of the big-voxel list
-    int32_t Q;            // bricks per cloud (kBrickW words each)
+    int32_t wshift;       // log2 of the occupancy words per brick (brick_wshift)
+    int32_t Q;            // bricks per cloud
     int32_t T;            // point tiles (kSortTile points) over the batch
     bool bricks;          // the brick build's arrays are present (B * Q <= kMaxBricks)
     bool tile_scan;       // brick build: each scatter tile sums its clouds' histogram columns itself
                           // (at most kTileScanCap entries per tile); otherwise a scan launch does
-    int64_t items_max;    // brick build: bound on the work items, B * Q + ceil(B * N / kBrickCap)
-                          // (the bricks, then the further parts of heavy bricks)
+    int64_t items_max;    // brick build: bound on the work items, B * N / (kWavePts + 1) (every part of a
+                          // heavy brick stands for more points: two in a row hold over kBrickCap)
+    int64_t rows_max;     // brick build: bound on the parts of heavy bricks, 2 n / kBrickCap + 1 for n points
     int64_t heavy_max;    // brick build: bound on the heavy bricks, B * N / (kBrickCap + 1)
     size_t total;
     // exposed
@@ -76,24 +81,22 @@ struct Layout {
     size_t bitmap;        // u64 [B][W] occupancy bits, bit (lin & 63) of word lin >> 6
     size_t word_rank;     // u32 [B][W] occupied voxels before word w (the slot of its first bit)
     size_t pt_slot;       // u32 [B][N] per point: linear id, then slot
-    size_t pt_pos;        // u32 [B][N] per point: arrival position inside its voxel
+    size_t pt_pos;        // u32 [B][N] per point: arrival position inside its voxel (not with bricks)
     size_t hist;          // u32 [T][B*Q] points of tile t in brick g, then the first sorted position of them
     size_t bstart;        // u32 [B*Q] first sorted position of each brick
-    size_t brick_hb;      // i32 [B*Q] index of a heavy brick in hlist, else -1
-    size_t item_extra;    // u64 [items_max - B*Q] further parts of heavy bricks: part << 32 | brick
+    size_t item;          // BrickItem [items_max] the work items
     size_t agg;           // u64 [B*Q] occupied voxels << 31 | stored points of each brick
-    size_t hlist;         // u32 [heavy_max] the heavy bricks
-    size_t hebase;        // u32 [heavy_max] first item_extra entry of each heavy brick
-    size_t pcnt;          // u32 [items_max - B*Q][kBrickV] per further part of a heavy brick and voxel:
+    size_t hfirst;        // u32 [heavy_max] count row of each heavy brick's first part
+    size_t hparts;        // u32 [heavy_max] parts of each heavy brick
+    size_t pcnt;          // u32 [rows_max][voxels per brick] count rows: per part of a heavy brick and voxel,
                           // the brick's points in the parts before it
-    size_t hdone;         // u32 [heavy_max] parts of each heavy brick that have grouped their points
-    size_t hfo;           // u32 [heavy_max][kBrickV + 1] their exclusive prefix
-    size_t hso;           // u32 [heavy_max][kBrickV] exclusive prefix of min(points, n_v)
-    size_t hpre;          // u64 [heavy_max] aggregate of the bricks before each heavy brick
+    size_t hdone;         // u32 [heavy_max] parts of each heavy brick that have counted their points
+    size_t htot;          // u32 [heavy_max][voxels per brick] their points per voxel
+    size_t hso;           // u32 [heavy_max][voxels per brick] exclusive prefix of min(points, n_v)
     size_t sorted;        // float4 [B*N] x, y, z, bits(index) grouped by brick
+    size_t svox;          // u16 [B*N] their voxels within the brick
     size_t full_off;      // u32 [B][N+1] exclusive prefix of the full counts
-    size_t bucket;        // u32 [B][N] every point index grouped by slot (arrival order); in the
-                          // brick build, those of bricks too large for LDS, at their sorted position
+    size_t bucket;        // u32 [B][N] every point index grouped by slot (arrival order; not with bricks)
     size_t pt4;           // float4 [B][N] stored points grouped by slot: x, y, z, bits(index)
     size_t big;           // u32 [big_cap] global slot ids (b*N + s) of big voxels
     size_t cas_cover;     // u32 [B][N] CAS: centers whose neighbourhood holds the voxel
