@@ -8,9 +8,11 @@
 //                           keys' top halves, then compacts in index order;
 //   Farthest Point Sampling from point 0, each next center the point with the
 //                           largest d^2 to its nearest chosen center (ties to
-//                           the lowest index): one 1024-thread workgroup per
-//                           cloud keeps every point's distance in registers
-//                           and reduces (d^2, -index) to the next center;
+//                           the lowest index): one workgroup per cloud keeps
+//                           every point's distance in registers and reduces
+//                           (d^2, -index) to the next center; up to 16384
+//                           points it holds the points too, in spatial runs
+//                           that a far-off center skips;
 //   Ball Query              the first K points in index order with
 //                           d^2 < R^2 among all N: one wave per center scans
 //                           64 points at a time and stops at K;
@@ -105,6 +107,278 @@ __global__ __launch_bounds__(kSelThreads) void k_rps(int32_t N, int32_t M, uint6
 
 // ------------------------------------------------------------------ FPS
 
+// Lane i reads lane i - N of its row, or the row broadcasts of DPP control C;
+// lanes without a source keep their own value.
+template <int C, int RM>
+__device__ __forceinline__ float dpp_own(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), C, RM, 0xF, false));
+}
+
+// Minimum over the wave, in every lane.
+__device__ __forceinline__ float wave_fmin(float v) {
+    v = fminf(v, dpp_own<0x111, 0xF>(v));  // row_shr:1, 2, 4, 8
+    v = fminf(v, dpp_own<0x112, 0xF>(v));
+    v = fminf(v, dpp_own<0x114, 0xF>(v));
+    v = fminf(v, dpp_own<0x118, 0xF>(v));
+    v = fminf(v, dpp_own<0x142, 0xA>(v));  // row_bcast:15 into rows 1 and 3
+    v = fminf(v, dpp_own<0x143, 0xC>(v));  // row_bcast:31 into rows 2 and 3
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
+}
+
+// Farthest Point Sampling of clouds of at most 1024 * PER points: one
+// workgroup per cloud, every point's coordinates and distance in registers.
+// The picks are a serial chain; what a pick costs is what its slowest wave
+// does between two barriers. So that a pick touches few points, the
+// workgroup first sorts its points by the Morton code of a 16^3 grid over
+// their bounding box (a counting sort in LDS): register k of a wave then
+// holds 64 neighbouring points (a run), whose bounding box and largest
+// distance sit in the wave's lane k. A new center changes no distance of a
+// run when its distance to the box is at least the run's largest distance.
+// That holds exactly in fp32: the distance to the box is computed with the
+// same operations in the same order as a point's, from per-axis gaps no
+// larger than any point's, and every rounding is monotonic. Points that are
+// not finite are left out of the boxes: their distance to any center is
+// infinite or not a number, so they keep the infinity they start with, as
+// does every point against a center that is not finite.
+// Measured: 4 clouds of 8192 points, 1024 picks: 1.99 -> 1.08 ms (a pick re-reading
+// and updating every point: 1.95 us, now 1.05).
+template <int PER>
+__global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restrict__ points, int32_t N, int32_t M,
+                                                          int32_t* __restrict__ center_idx) {
+    constexpr int kW = kSelThreads / kWave;  // most waves of the workgroup
+    constexpr int kCells = 4096;
+    static_assert(PER <= 16 && kW == 16, "a wave's runs, and the waves, fit in 16 lanes");
+    __shared__ uint32_t s_cell[kCells];
+    __shared__ uint16_t s_perm[kSelThreads * PER];
+    __shared__ float s_box[6][kW];
+    __shared__ uint32_t s_wave[kW];
+    __shared__ uint64_t s_key[2][kW];
+    __shared__ float4 s_xyz[2][kW];
+    const int32_t b = blockIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const int nt = blockDim.x, nw = nt / kWave;
+    const float* P = points + (size_t)b * N * 3;
+    int32_t* out = center_idx + (size_t)b * M;
+    const float inf = __builtin_inff();
+
+    // bounding box of the finite points
+    float lo[3] = {inf, inf, inf}, hi[3] = {-inf, -inf, -inf};
+    for (int32_t i = tid; i < N; i += nt) {
+        const float c[3] = {P[(size_t)i * 3], P[(size_t)i * 3 + 1], P[(size_t)i * 3 + 2]};
+        if (isfinite(c[0]) && isfinite(c[1]) && isfinite(c[2])) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                lo[a] = fminf(lo[a], c[a]);
+                hi[a] = fmaxf(hi[a], c[a]);
+            }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = wave_fmin(lo[a]);
+        hi[a] = -wave_fmin(-hi[a]);
+        if (lane == 0) {
+            s_box[a][wv] = lo[a];
+            s_box[3 + a][wv] = hi[a];
+        }
+    }
+    for (int i = tid; i < kCells; i += nt) s_cell[i] = 0u;
+    __syncthreads();
+    float scale[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        for (int w = 0; w < nw; ++w) {
+            lo[a] = fminf(lo[a], s_box[a][w]);
+            hi[a] = fmaxf(hi[a], s_box[3 + a][w]);
+        }
+        scale[a] = 16.0f / (hi[a] - lo[a]);  // a flat or empty box: not finite, cell 0
+    }
+    // the cell of a point (any cell will do for one that is not finite: the
+    // order decides only how well the runs' boxes fit)
+    auto cell_of = [&](int32_t i) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float t = (P[(size_t)i * 3 + a] - lo[a]) * scale[a];
+            uint32_t q = t >= 0.0f && t < 16.0f ? (uint32_t)t : (t >= 16.0f ? 15u : 0u);
+            q = (q | (q << 4)) & 0xC3u;
+            q = (q | (q << 2)) & 0x249u;
+            m |= q << a;
+        }
+        return m;
+    };
+    uint32_t cell[PER], pos[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int32_t i = tid + k * nt;
+        cell[k] = pos[k] = 0;
+        if (i < N) {
+            cell[k] = cell_of(i);
+            pos[k] = atomicAdd(&s_cell[cell[k]], 1u);
+        }
+    }
+    __syncthreads();
+    {   // exclusive scan of the cells, kCells / nt of them per thread
+        const int per = kCells / nt;
+        uint32_t sum = 0;
+        for (int j = 0; j < per; ++j) sum += s_cell[tid * per + j];
+        const uint32_t incl = wave_incl_scan<uint32_t>(sum);
+        if (lane == kWave - 1) s_wave[wv] = incl;
+        __syncthreads();
+        uint32_t run = incl - sum;
+        for (int w = 0; w < wv; ++w) run += s_wave[w];
+        for (int j = 0; j < per; ++j) {
+            const uint32_t c = s_cell[tid * per + j];
+            s_cell[tid * per + j] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        if (tid + k * nt < N) s_perm[s_cell[cell[k]] + pos[k]] = (uint16_t)(tid + k * nt);
+    __syncthreads();
+
+    // this wave's points, PER runs of 64; a place past the end holds no
+    // number, distance 0 and the index that loses every tie
+    float x[PER], y[PER], z[PER], dm[PER];
+    uint32_t id[PER];
+    float bl[3] = {inf, inf, inf}, bh[3] = {-inf, -inf, -inf};  // lane k: the box of run k
+    uint32_t rmax = 0;                                          // lane k: bits of run k's largest distance
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int32_t at = (wv * PER + k) * kWave + lane;
+        const bool in = at < N;
+        id[k] = in ? (uint32_t)s_perm[at] : 0xFFFFFFFFu;
+        const float* p = P + (size_t)(in ? id[k] : 0u) * 3;
+        x[k] = in ? p[0] : __builtin_nanf("");
+        y[k] = p[1];
+        z[k] = p[2];
+        dm[k] = in ? inf : 0.0f;
+        const bool fin = in && isfinite(x[k]) && isfinite(y[k]) && isfinite(z[k]);
+        const float c3[3] = {x[k], y[k], z[k]};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float l = wave_fmin(fin ? c3[a] : inf), h = -wave_fmin(fin ? -c3[a] : inf);
+            bl[a] = lane == k ? l : bl[a];
+            bh[a] = lane == k ? h : bh[a];
+        }
+        const bool any = __ballot(in) != 0;
+        rmax = lane == k && any ? __float_as_uint(inf) : rmax;
+    }
+
+    // the wave's farthest point: key (bits(d^2) << 32) | ~index, coordinates
+    uint64_t wkey = 0;
+    float wx = 0.f, wy = 0.f, wz = 0.f;
+    auto find_best = [&]() {
+        uint32_t m = lane < PER ? rmax : 0u;
+        m = max(m, dpp_row_shr<1>(m));
+        m = max(m, dpp_row_shr<2>(m));
+        m = max(m, dpp_row_shr<4>(m));
+        m = max(m, dpp_row_shr<8>(m));
+        const uint32_t wm = (uint32_t)__builtin_amdgcn_readlane((int)m, 15);
+        const uint64_t runs = __ballot(lane < PER && rmax == wm);
+        uint32_t ci = 0xFFFFFFFFu;
+        float px = 0.f, py = 0.f, pz = 0.f;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if ((runs >> k) & 1ull) {
+                const bool better = __float_as_uint(dm[k]) == wm && id[k] < ci;
+                ci = better ? id[k] : ci;
+                px = better ? x[k] : px;
+                py = better ? y[k] : py;
+                pz = better ? z[k] : pz;
+            }
+        }
+        uint64_t who = __ballot(ci != 0xFFFFFFFFu);
+        if (who & (who - 1)) {  // a tie between lanes: the lowest index
+            uint32_t mn = ci;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) mn = min(mn, (uint32_t)__shfl_xor((int)mn, d, kWave));
+            who = __ballot(ci == mn);
+        }
+        if (!who) return;  // a wave without points keeps key 0
+        const int l = __ffsll((unsigned long long)who) - 1;
+        wkey = ((uint64_t)wm << 32) | (uint32_t)~(uint32_t)__builtin_amdgcn_readlane((int)ci, l);
+        wx = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(px), l));
+        wy = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(py), l));
+        wz = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(pz), l));
+    };
+    find_best();
+
+    uint32_t cur = 0;
+    float cx = P[0], cy = P[1], cz = P[2];
+    for (int32_t j = 0;; ++j) {
+        if (tid == 0) out[j] = (int32_t)cur;
+        if (j + 1 >= M) break;
+        // the runs the center may change: a lane per run
+        const float gx = fmaxf(fmaxf(bl[0] - cx, cx - bh[0]), 0.0f);
+        const float gy = fmaxf(fmaxf(bl[1] - cy, cy - bh[1]), 0.0f);
+        const float gz = fmaxf(fmaxf(bl[2] - cz, cz - bh[2]), 0.0f);
+        const float gxx = gx * gx, gyy = gy * gy, gzz = gz * gz;
+        const float gxy = gxx + gyy;
+        const float gap = gxy + gzz;
+        const uint64_t need = __ballot(lane < PER && gap < __uint_as_float(rmax));
+        if (need) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                if ((need >> k) & 1ull) {
+                    const float dx = x[k] - cx, dy = y[k] - cy, dz = z[k] - cz;
+                    const float xx = dx * dx, yy = dy * dy, zz = dz * dz;
+                    const float sxy = xx + yy;
+                    const float d = sxy + zz;
+                    dm[k] = d < dm[k] ? d : dm[k];
+                    uint32_t m = __float_as_uint(dm[k]);  // distances order as their bits
+                    m = max(m, dpp_row_shr<1>(m));
+                    m = max(m, dpp_row_shr<2>(m));
+                    m = max(m, dpp_row_shr<4>(m));
+                    m = max(m, dpp_row_shr<8>(m));
+                    m = max(max((uint32_t)__builtin_amdgcn_readlane((int)m, 15),
+                                (uint32_t)__builtin_amdgcn_readlane((int)m, 31)),
+                            max((uint32_t)__builtin_amdgcn_readlane((int)m, 47),
+                                (uint32_t)__builtin_amdgcn_readlane((int)m, 63)));
+                    rmax = lane == k ? m : rmax;
+                }
+            }
+            find_best();
+        }
+        // the farthest of the waves' points; two buffers, so that one barrier
+        // a pick is enough
+        const int par = j & 1;
+        if (lane == 0) {
+            s_key[par][wv] = wkey;
+            s_xyz[par][wv] = make_float4(wx, wy, wz, 0.f);
+        }
+        lds_barrier();
+        const uint64_t key = lane < nw ? s_key[par][lane] : 0ull;
+        const float4 c = s_xyz[par][lane < nw ? lane : 0];
+        uint32_t m = (uint32_t)(key >> 32);
+        m = max(m, dpp_row_shr<1>(m));
+        m = max(m, dpp_row_shr<2>(m));
+        m = max(m, dpp_row_shr<4>(m));
+        m = max(m, dpp_row_shr<8>(m));
+        const uint32_t top = (uint32_t)__builtin_amdgcn_readlane((int)m, 15);
+        uint64_t who = __ballot(lane < nw && (uint32_t)(key >> 32) == top);
+        if (who & (who - 1)) {
+            uint32_t low = ((who >> lane) & 1ull) ? (uint32_t)key : 0u;
+            uint32_t mx = low;
+            mx = max(mx, dpp_row_shr<1>(mx));
+            mx = max(mx, dpp_row_shr<2>(mx));
+            mx = max(mx, dpp_row_shr<4>(mx));
+            mx = max(mx, dpp_row_shr<8>(mx));
+            mx = (uint32_t)__builtin_amdgcn_readlane((int)mx, 15);
+            who = __ballot(((who >> lane) & 1ull) && (uint32_t)key == mx);
+        }
+        const int w = __ffsll((unsigned long long)who) - 1;
+        cur = ~(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, w);
+        cx = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c.x), w));
+        cy = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c.y), w));
+        cz = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c.z), w));
+    }
+}
+
+// Larger clouds: every thread keeps PER distances in registers, and every
+// pick reads the cloud again.
 template <int PER>
 __global__ __launch_bounds__(kSelThreads) void k_fps(const float* __restrict__ points, int32_t N, int32_t M,
                                                      int32_t* __restrict__ center_idx) {
@@ -270,10 +544,17 @@ hipError_t launch_sample_points(const float* points, int32_t B, int32_t N, int32
         k_rps<<<B, kSelThreads, 0, s>>>(N, M, seed, center_idx);
     } else {
         const int32_t per = (N + kSelThreads - 1) / kSelThreads;
+        // points in registers, sorted into runs, up to 16384 of them (the
+        // most a workgroup's registers hold); the fewest waves (a power of
+        // two, which divides the sort's cells) for up to 4096
+        int waves = 1;
+        while (waves < kSelThreads / kWave && waves * 4 * kWave < N) waves *= 2;
         if (per <= 4)
-            k_fps<4><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
+            k_fps_runs<4><<<B, waves * kWave, 0, s>>>(points, N, M, center_idx);
+        else if (per <= 8)
+            k_fps_runs<8><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
         else if (per <= 16)
-            k_fps<16><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
+            k_fps_runs<16><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
         else if (per <= 40)
             k_fps<40><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
         else

@@ -2,7 +2,10 @@
 or dispatch rules change over, bit-exact (see tests/test_gpu_parity.py)."""
 import numpy as np
 import pytest
+import torch
 
+import oracle
+from paper_1912_02984_amd import cagq
 from paper_1912_02984_amd import workloads as W
 from tests.test_gpu_parity import run_both
 
@@ -38,3 +41,22 @@ def test_brick_sizes(words, depth, order):
     for n_v in (1, 64):
         spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, n_v, 1)
         run_both(P, spec, 500, 32, "rvs", "knn", 3, where=f"words={words} n_v={n_v} {order}")
+
+
+@pytest.mark.parametrize("N,M", [(1, 1), (64, 64), (255, 40), (256, 256), (257, 60), (1025, 300), (4096, 200),
+                                 (4097, 200), (8192, 300), (8193, 100), (16384, 100), (16385, 20)])
+def test_fps_sizes(N, M):
+    """Farthest Point Sampling where its workgroup and its points per lane
+    change: a spread cloud, one of many equal points (ties go to the lowest
+    index, at last with every distance 0), a flat one, and one with points
+    that are not finite, which stay infinitely far."""
+    rng = np.random.default_rng(N)
+    spread = rng.normal(size=(N, 3)).astype(np.float32)
+    equal = rng.integers(0, 3, (N, 3)).astype(np.float32)
+    flat = spread * np.float32([1, 1, 0])
+    odd = spread.copy()
+    odd[N // 2:: max(1, N // 7), 1] = np.float32(np.inf)
+    odd[N // 3:: max(1, N // 5), 0] = np.float32(np.nan)
+    for P in (np.stack([spread, equal, flat]), odd[None]):
+        c = cagq.sample_points(torch.from_numpy(P).to("cuda:0"), M, "fps")
+        assert np.array_equal(c.cpu().numpy(), oracle.sample_points(P, M, "fps")), (N, M)
