@@ -10,8 +10,11 @@
 // challenge again. The final incumbents are emitted in ascending linear id.
 //
 // The procedure is sequential, but most challenges leave the state alone
-// (about one in eight is accepted on the indoor scenes), so one wave per
-// cloud decides 64 challenges at a time, one per lane, speculatively:
+// (about one in eight is accepted on the indoor scenes), so they are decided
+// ahead and again only when a swap before them may have changed them.
+// With r = 1 a workgroup per cloud does so (k_cas_swap_wg, below). With r >= 2,
+// and for clouds whose state leaves no room for that kernel's batches in LDS,
+// one wave per cloud decides 64 challenges at a time, one per lane (k_cas_swap):
 // * every lane loads the grid rows of pi(C) and pi(I) for its challenge once
 //   and evaluates both heuristics against the current coverage counts;
 // * a sweep walks the accepted lanes in challenge order; an accepted lane
@@ -126,7 +129,7 @@ __device__ __forceinline__ void cover(uint32_t* cov_w, const Occ& o, const Hood<
 
 __device__ __forceinline__ bool near(int32_t ax, int32_t ay, int32_t az, int32_t bx, int32_t by, int32_t bz,
                                      int32_t d) {
-    return abs(ax - bx) <= d && abs(ay - by) <= d && abs(az - bz) <= d;
+    return (abs(ax - bx) <= d) & (abs(ay - by) <= d) & (abs(az - bz) <= d);
 }
 
 template <int RAD, typename CT>
@@ -294,6 +297,351 @@ __global__ __launch_bounds__(kWave) void k_cas_swap(int32_t N, int64_t W, GridDi
     }
 }
 
+// ---- r = 1: a workgroup per cloud, one wave of it deciding.
+// What a challenge costs is a chain: its voxels' coverage counts, the two
+// heuristics, and, when it is accepted, the counts' update and the challenges
+// it may change. For r = 1 the two windows hold 2 * 27 positions, one per lane
+// of a wave, so a wave decides one challenge with one read of each lane's
+// count and two ballots, and applies one with one LDS add per lane. The other
+// work (the next challengers, their incumbents, and the slots of their
+// windows' positions, loads from memory all) is done ahead, into LDS, by the
+// workgroup's other waves while the first decides. Per batch of 64 challenges:
+//   1. every wave decides four of them against the counts as they are;
+//   2. wave 0, with a lane per challenge, walks those that are accepted or
+//      stale in challenge order: a stale one is decided again; an accepted one
+//      updates the counts and marks as stale the later ones it may touch (the
+//      same incumbent slot, or any pair of C/I voxels within distance 2); the
+//      other waves prepare the next batch.
+// Measured, two rooms of 30011 points with M = 3001: 4.9 -> 1.3 ms against one wave
+// per cloud that decides 64 challenges a lane each and sweeps again from the
+// first stale one.
+constexpr int kSwapT = 1024;
+constexpr int kSwapWaves = kSwapT / kWave;
+constexpr int kSwapHelpers = kSwapWaves - 1;
+constexpr int kSwapQ = (kWave + kSwapHelpers - 1) / kSwapHelpers;  // challenges a helper prepares per batch
+constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
+
+// A batch of challenges in LDS: per challenge the slots of the positions of
+// pi(C) (entries 0..26) and pi(I) (32..58), kNoSlot where there is no voxel.
+struct SwapBatch {
+    uint32_t slot[kWave][kWave];
+    uint32_t clin[kWave];
+    uint32_t ilin[kWave];  // the incumbent whose window the slots are
+    uint32_t j[kWave];     // its slot among the incumbents
+};
+
+struct SwapLds {
+    SwapBatch batch[2];
+    uint32_t acc[kWave];
+    int32_t nb[2];
+    uint32_t part[kSwapWaves];
+};
+
+// The grid, with its divisions by multiply and shift.
+struct SwapGrid {
+    GridDims g;
+    Magic d0, d01;
+
+    __device__ __forceinline__ void decode(uint32_t lin, int32_t& x, int32_t& y, int32_t& z) const {
+        const uint32_t zq = udiv(lin, d01);
+        const uint32_t rem = lin - zq * (uint32_t)g.D[0] * (uint32_t)g.D[1];
+        const uint32_t yq = udiv(rem, d0);
+        x = (int32_t)(rem - yq * (uint32_t)g.D[0]), y = (int32_t)yq, z = (int32_t)zq;
+    }
+};
+
+// A lane's window position: its offset, none from 27 on.
+struct WindowPos {
+    int32_t dx, dy, dz;
+    bool is;
+};
+
+// The voxel at a window position around voxel `lin`, if it is in the grid.
+__device__ __forceinline__ bool window_voxel(const SwapGrid& sg, uint32_t lin, const WindowPos& at, uint32_t& nl) {
+    int32_t x, y, z;
+    sg.decode(lin, x, y, z);
+    x += at.dx;
+    y += at.dy;
+    z += at.dz;
+    const bool in = at.is && x >= 0 && y >= 0 && z >= 0 && x < sg.g.D[0] && y < sg.g.D[1] && z < sg.g.D[2];
+    nl = in ? (uint32_t)x + (uint32_t)sg.g.D[0] * ((uint32_t)y + (uint32_t)sg.g.D[1] * (uint32_t)z) : 0u;
+    return in;
+}
+
+// Whether two voxels lie within Chebyshev distance 2, their coordinates packed
+// into 10-bit fields: each field of p + 2 - q and of q + 2 - p, offset by 512,
+// keeps its bit 9 when the difference is not negative. Coordinates are below
+// kPackDim, so that no field borrows or carries.
+constexpr int32_t kPackDim = 510;
+__device__ __forceinline__ bool near_packed(uint32_t p, uint32_t q) {
+    constexpr uint32_t kOnes = 1u | 1u << 10 | 1u << 20, kBias = 514u * kOnes, kSign = 512u * kOnes;
+    return ((p + (kBias - q)) & ((q + kBias) - p) & kSign) == kSign;
+}
+
+// Orders a wave's LDS accesses before those after it.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(kSwapT) void k_cas_swap_wg(int32_t N, int64_t W, SwapGrid sg, int32_t M, uint64_t seed,
+                                                        uint32_t beta_q16, const int32_t* __restrict__ nvox,
+                                                        const uint32_t* __restrict__ vox_lin,
+                                                        const uint64_t* __restrict__ bitmap,
+                                                        const uint32_t* __restrict__ word_rank,
+                                                        int32_t* __restrict__ center_lin,
+                                                        const int32_t* __restrict__ m_valid) {
+    constexpr int64_t lam = 27;
+    extern __shared__ __align__(16) unsigned char lds[];
+    SwapLds& s = *reinterpret_cast<SwapLds*>(lds);
+    const int32_t b = blockIdx.x;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int32_t nv = nvox[b];
+    const int32_t m = m_valid[b];
+    if (m <= 0) return;
+    uint32_t* inc = reinterpret_cast<uint32_t*>(lds + sizeof(SwapLds));  // incumbent slot j -> linear id
+    uint32_t* bits = inc + M;                                            // initial set, one bit per slot
+    uint8_t* cov = reinterpret_cast<uint8_t*>(bits + (N + 31) / 32);     // incumbents covering the voxel
+    uint32_t* cov_w = reinterpret_cast<uint32_t*>(cov);
+    const uint64_t* bm = bitmap + (size_t)b * W;
+    const uint32_t* wr = word_rank + (size_t)b * W;
+    const Occ o{bm, wr, sg.g};
+    const uint32_t* vl = vox_lin + (size_t)b * N;
+    int32_t* out = center_lin + (size_t)b * M;
+
+    for (int32_t w = tid; w < (nv + 31) / 32; w += kSwapT) bits[w] = 0u;
+    for (int32_t w = tid; w < (nv + 3) / 4; w += kSwapT) cov_w[w] = 0u;
+    __syncthreads();
+    // the RVS incumbents: their linear ids, their bits, their coverage
+    for (int32_t j = tid; j < m; j += kSwapT) {
+        const uint32_t lin = (uint32_t)out[j];
+        const int32_t sl = slot_of(bm, wr, lin);
+        inc[j] = lin;
+        atomicOr(&bits[sl >> 5], 1u << (sl & 31));
+        int32_t x, y, z;
+        sg.decode(lin, x, y, z);
+        Hood<1> h;
+        h.load(o, x, y, z, true);
+        cover<1, uint8_t>(cov_w, o, h, true);
+    }
+    __syncthreads();
+
+    const int wp = lane & 31;
+    const WindowPos at{wp % 3 - 1, wp / 3 % 3 - 1, wp / 9 - 1, wp < 27};
+    const uint64_t hb = sm64(sm64(seed ^ 3ull) ^ (uint64_t)b);
+    const auto count_add = [&](uint32_t sl, bool add) {
+        const uint32_t unit = 1u << (8 * (sl & 3u));
+        if (add)
+            atomicAdd(&cov_w[sl >> 2], unit);
+        else
+            atomicSub(&cov_w[sl >> 2], unit);
+    };
+    // the challenge whose positions' slots the lanes hold: accepted or not
+    const auto decide = [&](uint32_t sl) {
+        const bool on = sl != kNoSlot;
+        const uint32_t c = cov[on ? sl : 0u];
+        const uint64_t zero = __ballot(on && c == 0), one = __ballot(on && c == 1);
+        const int32_t n0 = __popc((uint32_t)zero), r1 = __popc((uint32_t)(one >> 32));
+        if (!beta_q16) return n0 > r1;
+        const int64_t sum = (int64_t)wave_sum_u32(on && lane < 32 ? c : 0u);
+        return 65536LL * lam * (n0 - r1) > (int64_t)beta_q16 * sum;
+    };
+    // a challenge's incumbent window again, around voxel `lin`; returns the
+    // lane's slot
+    const auto rewindow = [&](SwapBatch& t, int q, uint32_t lin) {
+        uint32_t sl = t.slot[q][lane];
+        if (lane >= 32) {
+            uint32_t nl;
+            const bool in = window_voxel(sg, lin, at, nl);
+            const uint64_t w = bm[nl >> 6];
+            const uint32_t rk = wr[nl >> 6];
+            sl = in && ((w >> (nl & 63)) & 1ull) ? rk + (uint32_t)__popcll(w & ((1ull << (nl & 63)) - 1)) : kNoSlot;
+            t.slot[q][lane] = sl;
+        }
+        return sl;
+    };
+    // a voxel's coordinates as near_packed takes them, on grids it can pack
+    const bool packed = sg.g.D[0] <= kPackDim && sg.g.D[1] <= kPackDim && sg.g.D[2] <= kPackDim;
+    const auto pack = [&](uint32_t lin) {
+        if (!packed) return lin;
+        int32_t x, y, z;
+        sg.decode(lin, x, y, z);
+        return (uint32_t)x | (uint32_t)y << 10 | (uint32_t)z << 20;
+    };
+    int32_t t0 = 0, sc = 0;  // challenges prepared, slot cursor (the same in every helper wave)
+    // prepares the next batch: every helper finds the batch's challengers and
+    // prepares its own of them
+    const auto prepare = [&](SwapBatch& t, int32_t* nb_out) {
+        uint32_t csl[kSwapQ];
+#pragma unroll
+        for (int i = 0; i < kSwapQ; ++i) csl[i] = 0;
+        int32_t filled = 0;
+        while (filled < kWave && sc < nv) {
+            const int32_t sv = sc + lane;
+            const bool ch = sv < nv && !((bits[sv >> 5] >> (sv & 31)) & 1u);
+            const uint64_t bal = __ballot(ch);
+            const int32_t rank = filled + (int32_t)__popcll(bal & ((1ull << lane) - 1));
+#pragma unroll
+            for (int i = 0; i < kSwapQ; ++i) {
+                const int32_t q = wv - 1 + i * kSwapHelpers;
+                const uint64_t hit = __ballot(ch && rank == q);
+                if (hit) csl[i] = (uint32_t)(sc + __ffsll((unsigned long long)hit) - 1);
+            }
+            const int32_t cnt = (int32_t)__popcll(bal), need = kWave - filled;
+            if (cnt <= need) {
+                sc = sc + kWave < nv ? sc + kWave : nv;
+                filled += cnt;
+            } else {
+                sc += __ffsll((unsigned long long)__ballot(ch && rank == kWave - 1));
+                filled = kWave;
+            }
+        }
+        if (wv == 1 && lane == 0) *nb_out = filled;
+        // incumbent slots, a lane per challenge
+        const uint32_t jj = (uint32_t)(sm64(hb ^ (uint64_t)(uint32_t)(t0 + lane)) >> 32) % (uint32_t)m;
+        uint32_t cl[kSwapQ];
+#pragma unroll
+        for (int i = 0; i < kSwapQ; ++i) cl[i] = vl[csl[i]];
+        uint32_t nl[kSwapQ], rk[kSwapQ];
+        uint64_t w[kSwapQ];
+        bool in[kSwapQ];
+#pragma unroll
+        for (int i = 0; i < kSwapQ; ++i) {
+            const int32_t q = wv - 1 + i * kSwapHelpers;
+            in[i] = false;
+            nl[i] = 0;
+            if (q < filled) {  // the same for the whole wave
+                const uint32_t j = (uint32_t)__builtin_amdgcn_readlane((int)jj, q);
+                const uint32_t il = (uint32_t)__builtin_amdgcn_readfirstlane((int)inc[j]);
+                in[i] = window_voxel(sg, lane < 32 ? cl[i] : il, at, nl[i]);
+                if (lane == 0) {
+                    t.clin[q] = cl[i];
+                    t.ilin[q] = il;
+                    t.j[q] = j;
+                }
+            }
+            w[i] = bm[nl[i] >> 6];
+            rk[i] = wr[nl[i] >> 6];
+        }
+#pragma unroll
+        for (int i = 0; i < kSwapQ; ++i) {
+            const int32_t q = wv - 1 + i * kSwapHelpers;
+            const uint32_t bit = nl[i] & 63u;
+            const bool occ = in[i] && ((w[i] >> bit) & 1ull);
+            if (q < filled) t.slot[q][lane] = occ ? rk[i] + (uint32_t)__popcll(w[i] & ((1ull << bit) - 1)) : kNoSlot;
+        }
+        t0 += filled;
+    };
+
+    if (wv != 0) prepare(s.batch[0], &s.nb[0]);
+    __syncthreads();
+    for (int p = 0;; p ^= 1) {
+        SwapBatch& t = s.batch[p];
+        const int32_t nb = s.nb[p];
+        if (nb == 0) break;
+        // 1. the batch against the counts as they are; a window prepared for
+        // an incumbent that has been replaced since is made again
+        for (int q = wv; q < nb; q += kSwapWaves) {
+            const uint32_t il = inc[t.j[q]];
+            uint32_t sl = t.slot[q][lane];
+            if (il != t.ilin[q]) {
+                sl = rewindow(t, q, il);
+                if (lane == 0) t.ilin[q] = il;
+            }
+            const bool a = decide(sl);
+            if (lane == 0) s.acc[q] = a ? 1u : 0u;
+        }
+        lds_barrier();
+        if (wv != 0) {
+            prepare(s.batch[p ^ 1], &s.nb[p ^ 1]);
+        } else {
+            // 2. a lane per challenge; the other waves of its SIMD give way
+            __builtin_amdgcn_s_setprio(3);
+            const bool live = lane < nb;
+            const uint32_t clin = live ? t.clin[lane] : 0u, j = live ? t.j[lane] : 0u;
+            const uint32_t ilin = live ? t.ilin[lane] : 0u;
+            const uint32_t cp = pack(clin);
+            uint32_t ip = pack(ilin);
+            bool acc = live && s.acc[lane] != 0, stale = false, reload = false;
+            uint64_t todo = __ballot(acc);
+            while (todo) {
+                const int a = __ffsll((unsigned long long)todo) - 1;
+                uint32_t sl = t.slot[a][lane];
+                const uint32_t ja = (uint32_t)__builtin_amdgcn_readlane((int)j, a);
+                if ((__ballot(stale) >> a) & 1ull) {
+                    if ((__ballot(reload) >> a) & 1ull) {
+                        const uint32_t il = (uint32_t)__builtin_amdgcn_readfirstlane((int)inc[ja]);
+                        sl = rewindow(t, a, il);
+                        ip = lane == a ? pack(il) : ip;
+                    }
+                    if (!decide(sl)) {
+                        todo &= todo - 1;
+                        continue;
+                    }
+                }
+                // accepted: the counts, the incumbent, the challenges it may touch
+                if (sl != kNoSlot) count_add(sl, lane < 32);
+                const uint32_t ca = (uint32_t)__builtin_amdgcn_readlane((int)clin, a);
+                if (lane == 0) inc[ja] = ca;
+                wave_lds_fence();
+                const uint32_t ac = (uint32_t)__builtin_amdgcn_readlane((int)cp, a),
+                               ai = (uint32_t)__builtin_amdgcn_readlane((int)ip, a);
+                const bool after = live && lane > a;
+                const bool same = after && j == ja;
+                bool touch;
+                if (packed) {
+                    touch = near_packed(cp, ac) | near_packed(cp, ai) | near_packed(ip, ac) | near_packed(ip, ai);
+                } else {  // here cp and ip are the linear ids
+                    int32_t x[4], y[4], z[4];
+                    sg.decode(cp, x[0], y[0], z[0]);
+                    sg.decode(ip, x[1], y[1], z[1]);
+                    sg.decode(ac, x[2], y[2], z[2]);
+                    sg.decode(ai, x[3], y[3], z[3]);
+                    touch = near(x[0], y[0], z[0], x[2], y[2], z[2], 2) | near(x[0], y[0], z[0], x[3], y[3], z[3], 2) |
+                            near(x[1], y[1], z[1], x[2], y[2], z[2], 2) | near(x[1], y[1], z[1], x[3], y[3], z[3], 2);
+                }
+                reload = reload || same;
+                stale = stale || same || (after && touch);
+                todo = __ballot(after && (acc || stale));
+            }
+            __builtin_amdgcn_s_setprio(0);
+        }
+        lds_barrier();
+    }
+
+    // the final incumbents in ascending linear id: their bits, then an
+    // ordered pass over the slots, a range of whole words per wave; position
+    // p < m also fills p + m, ...
+    for (int32_t w = tid; w < (nv + 31) / 32; w += kSwapT) bits[w] = 0u;
+    __syncthreads();
+    for (int32_t j = tid; j < m; j += kSwapT) {
+        const int32_t sl = slot_of(bm, wr, inc[j]);
+        atomicOr(&bits[sl >> 5], 1u << (sl & 31));
+    }
+    __syncthreads();
+    const int32_t span = ((nv + kSwapT - 1) / kSwapT) * kWave;  // slots per wave
+    const int32_t s0 = wv * span, s1 = s0 + span < nv ? s0 + span : nv;
+    uint32_t cnt = 0;
+    for (int32_t w = s0 / 32 + lane; w * 32 < s1; w += kWave) cnt += (uint32_t)__popc(bits[w]);
+    cnt = wave_sum_u32(cnt);
+    if (lane == 0) s.part[wv] = cnt;
+    __syncthreads();
+    uint32_t base = 0;
+    for (int w = 0; w < wv; ++w) base += s.part[w];
+    for (int32_t c0 = s0; c0 < s1; c0 += kWave) {
+        const int32_t sv = c0 + lane;
+        const bool chosen = sv < s1 && ((bits[sv >> 5] >> (sv & 31)) & 1u);
+        const uint64_t bal = __ballot(chosen);
+        if (chosen) {
+            const uint32_t pos = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1));
+            for (int32_t k = (int32_t)pos; k < M; k += m) out[k] = (int32_t)vl[sv];
+        }
+        base += (uint32_t)__popcll(bal);
+    }
+}
+
 size_t swap_lds_bytes(int32_t N, int32_t M, int rad) {
     const size_t cbytes = rad <= 2 ? 1 : 2;
     return 4 * (size_t)M + 4 * (size_t)((N + 31) / 32) + cbytes * (size_t)N + 16;
@@ -313,6 +661,16 @@ hipError_t launch_cas_swap(const Layout& L, const cagq_grid_desc& d, void* ws, i
     GridDims g;
     for (int a = 0; a < 3; ++a) g.D[a] = d.dims[a];
     const size_t bytes = swap_lds_bytes(L.N, M, d.radius);
+    const size_t wg = sizeof(SwapLds) + bytes;
+    if (d.radius == 1 && wg + kSwapLdsStatic <= kSwapLdsLimit) {
+        e = hipFuncSetAttribute((const void*)k_cas_swap_wg, hipFuncAttributeMaxDynamicSharedMemorySize, (int)wg);
+        if (e != hipSuccess) return e;
+        const SwapGrid sg{g, make_magic((uint32_t)g.D[0]), make_magic((uint32_t)g.D[0] * (uint32_t)g.D[1])};
+        k_cas_swap_wg<<<L.B, kSwapT, wg, s>>>(L.N, L.W, sg, M, seed, beta_q16, at<int32_t>(ws, L.nvox),
+                                              at<uint32_t>(ws, L.vox_lin), at<uint64_t>(ws, L.bitmap),
+                                              at<uint32_t>(ws, L.word_rank), center_lin, m_valid);
+        return hipGetLastError();
+    }
     auto go = [&](auto kern) {
         hipError_t r = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         if (r != hipSuccess) return r;

@@ -455,6 +455,25 @@ struct GridDims {
     int32_t D[3];
 };
 
+// Division by a divisor d that is the same for the whole launch, for
+// dividends below 2^31: floor(n / d) = (n * m) >> (31 + l) with
+// l = ceil(log2 d) and m = ceil(2^(31+l) / d) < 2^32 (Granlund and
+// Montgomery, "Division by invariant integers using multiplication", 1994).
+struct Magic {
+    uint32_t m, sh;
+};
+
+inline Magic make_magic(uint32_t d) {
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;
+    const uint64_t p = 1ull << (31 + l);
+    return Magic{(uint32_t)((p + d - 1) / d), 31 + l};
+}
+
+__device__ __forceinline__ uint32_t udiv(uint32_t n, const Magic& g) {
+    return (uint32_t)(((uint64_t)n * g.m) >> g.sh);
+}
+
 // One grid-row segment of a cloud's occupancy: the slot of the first occupied
 // voxel at or after the segment's start, and bit j set when voxel x - h + j
 // of the segment is occupied (clear outside the grid).

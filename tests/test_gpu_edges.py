@@ -60,3 +60,26 @@ def test_fps_sizes(N, M):
     for P in (np.stack([spread, equal, flat]), odd[None]):
         c = cagq.sample_points(torch.from_numpy(P).to("cuda:0"), M, "fps")
         assert np.array_equal(c.cpu().numpy(), oracle.sample_points(P, M, "fps")), (N, M)
+
+
+@pytest.mark.parametrize("case", ["one incumbent", "three incumbents", "last batch of one", "every voxel",
+                                  "wide axis", "more state than the workgroup kernel holds"])
+def test_cas_swap_edges(case):
+    """The challenger / incumbent procedure where its workgroup kernel changes
+    course: every challenge meeting the same slot, slots replaced again and
+    again within a batch, a batch of a single challenge, no challenge at all,
+    coordinates that do not fit the packed test, and a state that leaves the
+    cloud to the one-wave kernel; with and without beta."""
+    rng = np.random.default_rng(7)
+    dims, nvox, extra = (40, 30, 20), 3001, 900
+    M = {"one incumbent": 1, "three incumbents": 3, "last batch of one": nvox - 129, "every voxel": nvox}.get(case, 200)
+    if case == "wide axis":
+        dims = (700, 12, 6)
+    if case == "more state than the workgroup kernel holds":
+        dims, nvox, extra, M = (64, 64, 16), 20000, 61920, 8700
+    lin = np.stack([rng.choice(dims[0] * dims[1] * dims[2], nvox, replace=False) for _ in range(2)])
+    lin = np.concatenate([lin, lin[:, rng.integers(0, nvox, extra)]], 1)
+    P = _points_in(lin, dims, rng)
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 8, 1)
+    for beta in (0, 20000):
+        run_both(P, spec, M, 8, "cas_swap", "cube", 11, beta_q16=beta, where=f"{case} beta={beta}")
