@@ -203,7 +203,9 @@ __device__ __forceinline__ void cas_u_bound(const uint32_t* __restrict__ uhist, 
     __syncthreads();
     // the first wave: lane l holds U = kCasUBins - 1 - l (from the top), an
     // inclusive scan of the counts, and the first lane whose running count
-    // reaches m gives U* and the ties taken there (no picks at all: 0, 0)
+    // reaches m gives U* and the ties taken there; no lane, and U* = 0: what
+    // the picks leave missing comes from the voxels with U = 0, which the
+    // rounds do not pick
     static_assert(kCasUBins <= kWave, "one bin per lane");
     if (tid < kWave) {
         const int u = kCasUBins - 1 - tid;
@@ -211,7 +213,7 @@ __device__ __forceinline__ void cas_u_bound(const uint32_t* __restrict__ uhist, 
         const uint32_t incl = wave_incl_sum_u32(hu);
         const uint64_t hit = __ballot(m > 0 && tid < kCasUBins && incl >= m);
         if (!hit) {
-            if (tid == 0) *out = sel_pack(0, 0);
+            if (tid == kWave - 1) *out = m > 0 ? sel_pack(0xFFFFFFFFull - 2147483648ull, m - incl) : sel_pack(0, 0);
         } else if (tid == __ffsll((unsigned long long)hit) - 1) {
             const uint64_t bound = 0xFFFFFFFFull - (uint64_t)(unit * u + 2147483648ll);
             *out = sel_pack(bound, m - (incl - hu));
@@ -278,7 +280,9 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         const int32_t s = s0 + i;
-        const uint64_t k = s < nv ? (key_mode == 0 ? select_key(0, hb, s, nullptr) : ~pk[i]) : ~0ull;
+        // with the picks' U histogram, an unpicked voxel stands for one with U = 0
+        const uint64_t pick = uhist && pk[i] == 0 ? cas_key(0, ln[i]) : pk[i];
+        const uint64_t k = s < nv ? (key_mode == 0 ? select_key(0, hb, s, nullptr) : ~pick) : ~0ull;
         const uint64_t top = k >> 32;
         const bool counted = s < nv && (key_mode == 0 || k != ~0ull);
         lt[i] = counted && top < bound;
@@ -1059,7 +1063,11 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
     const uint32_t prev = R == 0 ? 0u
                           : one_cloud ? wave_sum_u32(cp0 + cp1)
                                       : parts_sum(ctl.cpart + (size_t)((R - 1) % kCasBufs) * part, b);
-    if (active && prev >= (uint32_t)(M < nv ? M : nv)) {
+    const uint64_t G = R == 0 ? ~0ull
+                       : one_cloud ? wave_max_u64(gp0 > gp1 ? gp0 : gp1)
+                                   : parts_max(ctl.gpart + (size_t)((R - 1) % kCasBufs) * part, b);
+    // done: enough picks above the bound, or no voxel left that can be picked
+    if (active && (prev >= (uint32_t)(M < nv ? M : nv) || G == 0)) {
         if (s == 0) {
             ctl.done[b] = 1;
             // the last cloud to finish tells the host, without a copy on the stream
@@ -1074,9 +1082,6 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
             ctl.gpart[o] = 0;
             ctl.cpart[o] = 0;
         }
-    const uint64_t G = R == 0 ? ~0ull
-                       : one_cloud ? wave_max_u64(gp0 > gp1 ? gp0 : gp1)
-                                   : parts_max(ctl.gpart + (size_t)((R - 1) % kCasBufs) * part, b);
     const uint32_t cur = (uint32_t)R + 1;
     uint64_t k = 0;
     uint32_t above = 0;
@@ -1100,7 +1105,10 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
     if (active && s < nv) {
         if (rnd0 != 0) {
             above = pk0 > G ? 1u : 0u;
-        } else {
+        } else if (beta_q16 != 0 || (uint32_t)(my0 >> 32) > 0x80000000u) {
+            // (with beta = 0 a voxel whose neighbourhood is covered, score 0,
+            // stays out: picking it changes nothing, and the greedy comes to it
+            // after every other; the selection takes such voxels by slot)
             k = my0;
             bool beaten = false;
             if (bl0 >= 0) beaten = kb_ > my0 && (rb_ == 0 || rb_ == cur);

@@ -83,3 +83,21 @@ def test_cas_swap_edges(case):
     spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 8, 1)
     for beta in (0, 20000):
         run_both(P, spec, M, 8, "cas_swap", "cube", 11, beta_q16=beta, where=f"{case} beta={beta}")
+
+
+@pytest.mark.parametrize("N,radius", [(1500, 1), (1500, 2), (6000, 1), (20000, 1)])
+def test_cas_past_full_coverage(N, radius):
+    """Greedy CAS whose picks run out of uncovered voxels: the last centers
+    come from the covered ones by linear id. Single-workgroup rounds (r = 1 and
+    2) and many-kernel rounds, M from just past full coverage to every voxel."""
+    rng = np.random.default_rng(N)
+    dims = (36, 36, 36)
+    V = dims[0] * dims[1] * dims[2]
+    solid = np.flatnonzero((np.arange(V) // dims[0] % dims[1] < 9) & (np.arange(V) % dims[0] < 30))
+    lin = np.stack([np.concatenate([rng.choice(solid, 3 * N // 4), rng.integers(0, V, N - 3 * N // 4)])
+                    for _ in range(2)])
+    P = _points_in(lin, dims, rng)
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 4, radius)
+    nv = min(len(np.unique(x)) for x in lin)
+    for M in (nv // 3, nv - 1, nv + 70):
+        run_both(P, spec, M, 16, "cas", "knn", 5, where=f"N={N} r={radius} M={M}")
