@@ -113,6 +113,8 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->berr = take(4 * (size_t)B);
     L->sel_ghist = take(4 * (size_t)B * kSelBins);
     L->sel_cnt = take(4 * (size_t)B);
+    L->ctx_tiles = ((int64_t)BN + kScanThreads - 1) / kScanThreads;
+    L->ctx_desc = take(8 * (size_t)L->ctx_tiles);
     L->clear_small = off;
     L->desc_h = take(8 * ((BQ + 63) / 64));
     L->hdone = take(4 * H);
@@ -160,7 +162,7 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->sel_bins = take(4 * (size_t)B * sel_chunks * kSelBins);
     L->sel_base = take(4 * (size_t)B * sel_chunks);
     L->sel_take = take(4 * (size_t)B * sel_chunks);
-    L->cov_mark = take((BN + 15) / 16 * 16);
+    L->cov_mark = L->bricks ? take((BN + 15) / 16 * 16) : L->pt_pos;
     L->total = off;
     return true;
 }

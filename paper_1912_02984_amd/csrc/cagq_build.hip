@@ -1259,7 +1259,8 @@ __global__ __launch_bounds__(kSmallT) void k_build_small(
     const float* __restrict__ P, int32_t N, GridArgs g, int64_t W, uint32_t n_v, uint32_t* __restrict__ pt_slot,
     uint64_t* __restrict__ bitmap, uint32_t* __restrict__ word_rank, uint32_t* __restrict__ vox_lin,
     uint32_t* __restrict__ vox_count, int32_t* __restrict__ nvox, uint32_t* __restrict__ vox_off,
-    uint32_t* __restrict__ pt_list, float4* __restrict__ pt4, int* __restrict__ status, int* __restrict__ berr) {
+    uint32_t* __restrict__ pt_list, float4* __restrict__ pt4, int* __restrict__ status, int* __restrict__ berr,
+    uint64_t* __restrict__ ctx_desc, int32_t ctx_tiles) {
     extern __shared__ __align__(16) unsigned char lds[];
     uint64_t* s_bm = reinterpret_cast<uint64_t*>(lds);   // [W] occupancy words
     uint32_t* s_wr = reinterpret_cast<uint32_t*>(s_bm + W);  // [W] ranks
@@ -1273,8 +1274,10 @@ __global__ __launch_bounds__(kSmallT) void k_build_small(
     const size_t pb = (size_t)b * N;
 
     // the status words start at zero for the kernels after this one (this
-    // kernel writes none: its errors go to the cloud's own word)
+    // kernel writes none: its errors go to the cloud's own word), and so do
+    // the descriptors of the context offsets
     if (b == 0 && tid < kStSlots) status[tid] = 0;
+    for (int32_t i = b * kSmallT + tid; i < ctx_tiles; i += (int32_t)gridDim.x * kSmallT) ctx_desc[i] = 0ull;
     for (int64_t w = tid; w < W; w += kSmallT) s_bm[w] = 0ull;
     for (int32_t i = tid; i <= N; i += kSmallT) s_off[i] = 0u;
     if (tid == 0) {
@@ -1481,7 +1484,8 @@ hipError_t launch_build(const float* points, const Layout& L, const cagq_grid_de
                                                 at<uint32_t>(ws, L.vox_lin), at<uint32_t>(ws, L.vox_count),
                                                 at<int32_t>(ws, L.nvox), at<uint32_t>(ws, L.vox_off),
                                                 at<uint32_t>(ws, L.pt_list), at<float4>(ws, L.pt4), status,
-                                                at<int>(ws, L.berr));
+                                                at<int>(ws, L.berr), at<uint64_t>(ws, L.ctx_desc),
+                                                (int32_t)L.ctx_tiles);
         return hipGetLastError();
     }
     if (L.bricks) {

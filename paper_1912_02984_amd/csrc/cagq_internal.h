@@ -39,11 +39,12 @@ enum StatusSlot {
     kStTicketOff = 2,  // tile tickets of the offsets scan
     kStBigCount = 3,   // number of voxels with more than kBigVoxel points
     kStTicketSel = 4,  // tile tickets of the center compaction scan
-    kStTicketCtx = 5,  // tile tickets of the context-offsets scan
+    kStTicketCtx = 5,  // tile tickets of the context-offsets scan (zero between calls)
     kStTicketHist = 6, // tile tickets of the brick-histogram scan
     kStItems = 7,      // brick build: work items (bricks of more than kWavePts points, or their parts)
     kStHeavy = 8,      // brick build: bricks of more than kBrickCap points (heavy)
     kStRows = 9,       // brick build: parts of heavy bricks
+    kStCtxDone = 10,   // tiles of the context-offsets scan that have finished (zero between calls)
     kStSlots = 16
 };
 
@@ -55,6 +56,7 @@ struct Layout {
     int64_t W;            // 64-bit occupancy words per cloud
     int64_t tiles_w;      // rank-scan tiles (kRankTile words) over the words of one cloud
     int64_t tiles_s;      // scan tiles over the slots of one cloud
+    int64_t ctx_tiles;    // capacity of the context-offsets scan, ceil(B * N / kScanThreads)
     int64_t big_cap;      // capacity of the big-voxel list
     int32_t wshift;       // log2 of the occupancy words per brick (brick_wshift)
     int32_t Q;            // bricks per cloud
@@ -111,13 +113,15 @@ struct Layout {
     bool has_nbr16, has_nbr32;
     size_t sel_thr;       // u64 [B] selection threshold, see sel_pack
     size_t sel_ghist;     // u32 [B][kSelBins] top-11-bit histogram of the many-block select (zero between selections)
+    size_t ctx_desc;      // u64 [ctx_tiles] scan descriptors of the context offsets (zero between calls)
     size_t sel_cnt;       // u32 [B] block tickets of the many-block select (zero between selections)
     size_t sel_keys;      // u32 [B][chunks][4096] top halves of the select keys, each chunk sorted by its top 11 bits
     size_t sel_bins;      // u32 [B][chunks][kSelBins] end of each 11-bit bin in its sorted chunk
     size_t sel_base;      // u32 [B][chunks] first output position of each chunk's chosen slots
     size_t sel_take;      // u32 [B][chunks] ties at the bound each chunk takes
     size_t clear_small;   // [status, clear_small) is zeroed by every build
-    size_t cov_mark;      // u8  [B][N] coverage metric: 1 when the slot holds a node point
+    size_t cov_mark;      // u8  [B][N] coverage metric: 1 when the slot holds a node point (in pt_pos's
+                          // place where the layout has that: the build is done with it)
     size_t clear_end;     // [status, clear_end) is zeroed at the start of every build
 };
 

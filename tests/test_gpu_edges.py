@@ -101,3 +101,29 @@ def test_cas_past_full_coverage(N, radius):
     nv = min(len(np.unique(x)) for x in lin)
     for M in (nv // 3, nv - 1, nv + 70):
         run_both(P, spec, M, 16, "cas", "knn", 5, where=f"N={N} r={radius} M={M}")
+
+
+@pytest.mark.parametrize("N,dims,radius", [(700, (16, 16, 16), 1), (700, (16, 16, 16), 3), (9000, (40, 40, 40), 2),
+                                           (9000, (512, 512, 128), 1)])
+def test_context_offsets_again_and_again(N, dims, radius):
+    """The context lists of several sets of centers of one grid, call after
+    call (each leaves the scan's state ready for the next): one center, tiles
+    just full, one more, and more centers than points (several a thread); on
+    grids of all three builds, some centers empty or repeated."""
+    rng = np.random.default_rng(N + radius)
+    B, V = 2, dims[0] * dims[1] * dims[2]
+    lin = rng.integers(0, min(V, 4 * N), (B, N))
+    P = _points_in(lin, dims, rng)
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 5, radius)
+    ot = oracle.Table(P, oracle.grid_from_spec(spec))
+    g = cagq.build_grid(torch.from_numpy(P).to("cuda:0"), cagq.desc_from_spec(spec))
+    for M in (1, 128, 129, 256, 500, N, N + 1, 3 * N + 5):
+        cl = np.where(rng.random((B, M)) < 0.8, lin[:, rng.integers(0, N, M)], rng.integers(0, V, (B, M)))
+        cl = cl.astype(np.int32)
+        off_o, list_o = ot.context_list(cl)
+        t = torch.from_numpy(cl).to("cuda:0")
+        off = cagq.context_offsets(g, t)
+        assert np.array_equal(off.cpu().numpy(), off_o), (N, radius, M)
+        got = cagq.context_list(g, t, off)
+        assert np.array_equal(got.cpu().numpy()[:len(list_o)], list_o), (N, radius, M)
+    assert cagq.get_device_status(g) == 0
