@@ -704,9 +704,7 @@ __device__ __forceinline__ void clean16(uint64_t& k, uint32_t& p, int lg) {
     for (int j = 8; j > 0; j >>= 1) gcx(k, p, j, (lg & j) == 0);
 }
 
-// Sampled centers with 16 < K <= 32, Cube Query or k-NN: 16 lanes per center
-// (four per wave), two result registers per lane, ranks 0..15 in `b0` and
-// 16..31 in `b1`.
+// K <= 32, Cube Query or k-NN: 16 lanes per center (four per wave).
 //   1. Each group probes the (2r+1)^2 grid rows of its center's block, one
 //      lane per row: a row segment of the block holds consecutive slots,
 //      whose stored points are contiguous in the slot-ordered copy, so the
@@ -716,14 +714,32 @@ __device__ __forceinline__ void clean16(uint64_t& k, uint32_t& p, int lg) {
 //   2. The block's 16 centers are ranked by context size and group g takes
 //      the center of rank g, so each wave works on four centers of similar
 //      size and its chunk loop and sort depth follow them.
-//   3. Chunks of 16 entries are sorted across the group; the first is the
-//      running best, each later one is merged in: the 16 smallest of b1 and
-//      the chunk (elementwise minimum against the chunk reversed, then
-//      half-cleaners), then b0 and that merged the same way into the new b0
-//      (smaller half) and b1 (larger half).
-//   4. Node slot k is b0 lane k or b1 lane k - 16; slots k >= n repeat slot 0.
-//      The center's pairwise sum runs strides 1..8 inside each half, then
+//   3. In a wave whose contexts hold at most 32 points each, every entry's
+//      rank among its context is counted, and the entries below K go to the
+//      slot of their rank. In the others, chunks of 16 entries are sorted
+//      across the group with two result registers per lane, ranks 0..15 in
+//      `b0` and 16..31 in `b1`; the first chunk is the running best, each
+//      later one is merged in: the 16 smallest of b1 and the chunk (elementwise
+//      minimum against the chunk reversed, then half-cleaners), then b0 and
+//      that merged the same way into the new b0 (smaller half) and b1 (larger
+//      half). Either way the nodes end up in LDS by slot.
+//   4. Lane l of the group writes slots l and l + 16; slots k >= n repeat slot
+//      0. The center's pairwise sum runs strides 1..8 inside each half, then
 //      node 16 into node 0 -- the order of the single-register tree.
+// Adds to `r` how many of the row's 16 lanes hold a `k` below `mine`.
+template <int G, int J>
+__device__ __forceinline__ void count_below(uint32_t k, uint32_t mine, uint32_t& r) {
+    if constexpr (J < G) {
+        r += row_lane<J>(k) < mine ? 1u : 0u;
+        count_below<G, J + 1>(k, mine, r);
+    }
+}
+
+template <int N>
+__device__ __forceinline__ uint64_t row_shr64(uint64_t v) {
+    return ((uint64_t)dpp_row_shr<N>((uint32_t)(v >> 32)) << 32) | dpp_row_shr<N>((uint32_t)v);
+}
+
 constexpr int32_t kRankMin = 8192;  // centers of a launch above which k_query_r2 ranks a block's centers
 
 template <int MODE, int RAD, bool UP>
@@ -743,6 +759,8 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
     __shared__ float s_q[GPB][3];
     __shared__ uint32_t s_src[GPB];
     __shared__ uint32_t s_def[GPB];
+    __shared__ float4 s_node[GPB][2 * G];  // the group's nodes by slot: x, y, z, bits(index)
+    __shared__ uint32_t s_wt[GPB][2 * G];  // and their weights
     const int lane = lane_id();
     const int lg = lane & (G - 1);
     const int gb = threadIdx.x / G;
@@ -839,16 +857,11 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
     int src = gb;
     if (total > kRankMin) {
         __syncthreads();
-        if (lg == 0) {
-            const uint32_t mine = s_c[gb];
-            uint32_t r = 0;
-#pragma unroll
-            for (int h = 0; h < GPB; ++h) {
-                const uint32_t o = s_c[h];
-                r += (o < mine || (o == mine && h < gb)) ? 1u : 0u;
-            }
-            s_src[r] = (uint32_t)gb;
-        }
+        // lane lg of a group compares its center with center lg
+        static_assert(G == GPB, "a lane per center of the block");
+        const uint32_t mine = s_c[gb], o = s_c[lg];
+        const uint64_t less = __ballot(o < mine || (o == mine && lg < gb));
+        if (lg == 0) s_src[__popc((uint32_t)(less >> (lane & ~(G - 1))) & 0xFFFFu)] = (uint32_t)gb;
         __syncthreads();
         src = (int)s_src[gb];
     } else {
@@ -878,23 +891,94 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
         cmax = o > cmax ? o : cmax;
     }
     cmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)cmax);
-    const bool one = c <= (uint32_t)G;
+    // position in the copy of context entry e: the last row range starting
+    // at or before it
+    auto locate = [&](uint32_t e) {
+        uint32_t lo = 0;
+#pragma unroll
+        for (uint32_t h = 64; h > 0; h >>= 1) {
+            if (h >= (uint32_t)NR) continue;
+            const uint32_t t = lo + h;
+            if (s_pr[t < (uint32_t)NR ? t : (uint32_t)NR] <= e && t < (uint32_t)NR) lo = t;
+        }
+        return s_sr[lo] + (e - s_pr[lo]);
+    };
+    auto key_of = [&](const float4& v) -> uint64_t {
+        const uint32_t i = __float_as_uint(v.w);
+        if (MODE == CAGQ_QUERY_CUBE) return (sm64(hc ^ (uint64_t)i) & 0xFFFFFFFF00000000ull) | i;
+        const float dx = v.x - qx, dy = v.y - qy, dz = v.z - qz;
+        const float xx = dx * dx, yy = dy * dy, zz = dz * dz;
+        const float sxy = xx + yy;
+        const float d2 = sxy + zz;
+        return ((uint64_t)__float_as_uint(d2) << 32) | i;
+    };
+    float4* s_nd = s_node[gb];
+    uint32_t* s_nw = s_wt[gb];
+    const uint32_t n = c < (uint32_t)K ? c : (uint32_t)K;
+    if (cmax <= 2 * G) {
+        // contexts of at most 32 points: a node's slot is its rank, the
+        // number of smaller keys, counted against each entry in turn (the
+        // top halves, broadcast over the row of 16 lanes: one comparison and
+        // one addition each, about a quarter of a sorting network's work).
+        // The entries go to their slots in LDS.
+        uint32_t hk[2], id[2];
+        float4 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t e = (uint32_t)(h * G + lg);
+            v[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (e < c) v[h] = p4[locate(e)];
+        }
+        uint64_t kk[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            kk[h] = (uint32_t)(h * G + lg) < c ? key_of(v[h]) : ~0ull;
+            hk[h] = (uint32_t)(kk[h] >> 32);
+            id[h] = (uint32_t)kk[h];
+        }
+        uint32_t r0 = 0, r1 = 0;
+        const bool two = cmax > (uint32_t)G;
+        count_below<G, 0>(hk[0], hk[0], r0);
+        if (two) {
+            count_below<G, 0>(hk[1], hk[0], r0);
+            count_below<G, 0>(hk[0], hk[1], r1);
+            count_below<G, 0>(hk[1], hk[1], r1);
+        }
+        // keys with equal top halves (equal distances) share a rank: the
+        // ranks' powers of two then do not add up to 2^c - 1
+        const bool in0 = (uint32_t)lg < c, in1 = (uint32_t)(G + lg) < c;
+        uint64_t bits = (in0 ? 1ull << r0 : 0ull) + (in1 ? 1ull << r1 : 0ull);
+        bits += row_shr64<1>(bits);
+        bits += row_shr64<2>(bits);
+        bits += row_shr64<4>(bits);
+        bits += row_shr64<8>(bits);
+        const bool tie = lg == G - 1 && bits != (1ull << c) - 1;
+        if (__ballot(tie)) {  // by the whole keys
+            r0 = r1 = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                for (int j = 0; j < G; ++j) {
+                    const uint64_t o = gshfl64<G>(kk[h], j);
+                    r0 += o < kk[0] ? 1u : 0u;
+                    r1 += o < kk[1] ? 1u : 0u;
+                }
+            }
+        }
+        if (in0 && r0 < (uint32_t)K) s_nd[r0] = v[0];
+        if (in1 && r1 < (uint32_t)K) s_nd[r1] = v[1];
+        if (Wt) {
+            const uint32_t* wb = Wt + (size_t)b * N;
+            uint32_t w[2] = {1u, 1u};
+            if (in0) w[0] = wb[id[0]];
+            if (in1) w[1] = wb[id[1]];
+            if (in0 && r0 < (uint32_t)K) s_nw[r0] = w[0];
+            if (in1 && r1 < (uint32_t)K) s_nw[r1] = w[1];
+        }
+    } else {
     uint32_t top = 2;
     while (top < cmax && top < (uint32_t)G) top <<= 1;
     uint64_t b0k = ~0ull, b1k = ~0ull;
     uint32_t b0p = 0, b1p = 0;
-    float4 v0 = make_float4(0.f, 0.f, 0.f, 0.f);
-    uint32_t w0 = 1u;
-    // position in the copy of context entry e: the last row range starting
-    // at or before it
-    auto locate = [&](uint32_t e) {
-        uint32_t lo = 0, hi = NR - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi + 1) >> 1;
-            if (s_pr[mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        return s_sr[lo] + (e - s_pr[lo]);
-    };
     // each chunk's points are loaded one chunk ahead, so that a long
     // context's loads overlap the previous chunk's sort and merge
     uint32_t pos_n = 0;
@@ -913,25 +997,10 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
             pos_n = locate(e + G);
             v_n = p4[pos_n];
         }
-        if (e < c) {
-            const uint32_t i = __float_as_uint(v.w);
-            if (one) {
-                v0 = v;
-                if (Wt) w0 = Wt[(size_t)b * N + i];
-                pos = (uint32_t)lg;
-            }
-            if (MODE == CAGQ_QUERY_CUBE) {
-                key = (sm64(hc ^ (uint64_t)i) & 0xFFFFFFFF00000000ull) | i;
-            } else {
-                const float dx = v.x - qx, dy = v.y - qy, dz = v.z - qz;
-                const float xx = dx * dx, yy = dy * dy, zz = dz * dz;
-                const float sxy = xx + yy;
-                const float d2 = sxy + zz;
-                key = ((uint64_t)__float_as_uint(d2) << 32) | i;
-            }
-        } else {
+        if (e < c)
+            key = key_of(v);
+        else
             pos = 0;
-        }
         // a key above the K-th best so far can never be kept (keys are
         // distinct); a chunk left without keys anywhere in the wave changes
         // nothing and is not sorted
@@ -963,12 +1032,25 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
             clean16(b0k, b0p, lg);
             clean16(b1k, b1p, lg);
         }
-        // the K-th best key so far, rank K-1 in b1 (~0 while fewer than K are held)
-        kth = gshfl64<G>(b1k, K - 1 - G);
+        // the K-th best key so far, rank K-1 (~0 while fewer than K are held)
+        kth = K > G ? gshfl64<G>(b1k, K - 1 - G) : gshfl64<G>(b0k, K - 1);
     }
+    // the nodes' points, read again, to their slots
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t k = (uint32_t)(h * G + lg);
+        if (k < n) {
+            const float4 v = p4[h ? b1p : b0p];
+            s_nd[k] = v;
+            if (Wt) s_nw[k] = Wt[(size_t)b * N + __float_as_uint(v.w)];
+        }
+    }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
     // 4. outputs (an empty context gives n = 0)
-    const uint32_t n = c < (uint32_t)K ? c : (uint32_t)K;
     uint32_t nmax = n;
 #pragma unroll
     for (int d = G; d < kWave; d <<= 1) {
@@ -976,32 +1058,18 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
         nmax = o > nmax ? o : nmax;
     }
     nmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)nmax);
-    const uint64_t s0k = ((uint64_t)row0((uint32_t)(b0k >> 32)) << 32) | row0((uint32_t)b0k);
-    const uint32_t s0p = row0(b0p);
     float tx = 0.f, ty = 0.f, tz = 0.f, ux = 0.f, uy = 0.f, uz = 0.f;
     uint32_t wsum = 0;
-    // slot lg (from b0) and slot 16 + lg (from b1, written only when K > 16 + lg)
+    // slot lg and slot 16 + lg (written only when K > 16 + lg); slots k >= n
+    // repeat slot 0
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const uint32_t k = (uint32_t)(h * G + lg);
         const bool own = k < n;
-        const uint64_t mk = own ? (h ? b1k : b0k) : s0k;
-        const uint32_t mp = own ? (h ? b1p : b0p) : s0p;
-        const uint32_t idx = n ? (uint32_t)mk : 0u;
-        const int from = one ? (int)mp : 0;
-        float x = __shfl(v0.x, from, G), y = __shfl(v0.y, from, G), z = __shfl(v0.z, from, G);
-        uint32_t w = (uint32_t)__shfl((int)w0, from, G);
-        if (!one) {
-            const float4 pv = p4[mp];
-            x = pv.x;
-            y = pv.y;
-            z = pv.z;
-            if (!UP) w = Wt ? Wt[(size_t)b * N + idx] : 1u;
-        }
-        if (!n) {
-            x = y = z = 0.0f;
-            w = 1u;
-        }
+        const float4 v = s_nd[own ? k : 0u];
+        const uint32_t idx = n ? __float_as_uint(v.w) : 0u;
+        const float x = n ? v.x : 0.0f, y = n ? v.y : 0.0f, z = n ? v.z : 0.0f;
+        const uint32_t w = !UP && Wt && n ? s_nw[own ? k : 0u] : 1u;
         if (live && k < (uint32_t)K) {
             node_idx[cK + k] = UP ? (n ? (int32_t)idx : -1) : (int32_t)idx;
             if (node_xyz) {
@@ -1137,8 +1205,8 @@ void launch_r2(const Layout& L, const QGrid& g, void* ws, const QueryIO& io, int
 template <int MODE, bool UP>
 void launch_mode(const Layout& L, const QGrid& g, int32_t rad, int32_t n_v, void* ws, const QueryIO& io, int32_t M,
                  int32_t K, uint64_t seed, hipStream_t s) {
-    if (MODE != kRing && K > 16 && K <= 32) {
-        // 16 lanes and two result registers per center
+    if (MODE != kRing && K <= 32) {
+        // 16 lanes per center
         if (rad == 1)
             launch_r2<MODE, 1, UP>(L, g, ws, io, M, K, seed, n_v, s);
         else if (rad == 2)
