@@ -72,9 +72,16 @@ __constant__ Shells kShells = make_shells();
 struct QGrid {
     float o[3];
     float s[3];
+    float r[3];  // voxel_recip(s)
     int32_t D[3];
     Magic d0, d01, mm;  // division by D_x, by D_x * D_y and by M
 };
+
+// Voxel coordinate of a center point on one axis, 0 when it is not finite.
+__device__ __forceinline__ int32_t axis_of(const QGrid& g, int a, float p) {
+    const int32_t i = axis_index_recip(p, g.o[a], g.s[a], g.r[a], g.D[a]);
+    return isfinite(p) ? i : 0;
+}
 
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -265,9 +272,9 @@ __global__ __launch_bounds__(kQueryThreads) void k_query(
         py = center_pts[(size_t)c_id * 3 + 1];
         pz = center_pts[(size_t)c_id * 3 + 2];
         const bool bad = !isfinite(px) || !isfinite(py) || !isfinite(pz);
-        gx = isfinite(px) ? axis_index(px, g.o[0], g.s[0], g.D[0]) : 0;
-        gy = isfinite(py) ? axis_index(py, g.o[1], g.s[1], g.D[1]) : 0;
-        gz = isfinite(pz) ? axis_index(pz, g.o[2], g.s[2], g.D[2]) : 0;
+        gx = axis_of(g, 0, px);
+        gy = axis_of(g, 1, py);
+        gz = axis_of(g, 2, pz);
         lin = (uint32_t)gx + (uint32_t)g.D[0] * ((uint32_t)gy + (uint32_t)g.D[1] * (uint32_t)gz);
         if (live && bad && lg == 0) raise_error(status, CAGQ_ERR_NONFINITE_INPUT);
     } else {
@@ -784,9 +791,9 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
             qy = center_pts[(size_t)c_id * 3 + 1];
             qz = center_pts[(size_t)c_id * 3 + 2];
             const bool bad = !isfinite(qx) || !isfinite(qy) || !isfinite(qz);
-            gx = isfinite(qx) ? axis_index(qx, g.o[0], g.s[0], g.D[0]) : 0;
-            gy = isfinite(qy) ? axis_index(qy, g.o[1], g.s[1], g.D[1]) : 0;
-            gz = isfinite(qz) ? axis_index(qz, g.o[2], g.s[2], g.D[2]) : 0;
+            gx = axis_of(g, 0, qx);
+            gy = axis_of(g, 1, qy);
+            gz = axis_of(g, 2, qz);
             lin = (uint32_t)gx + (uint32_t)g.D[0] * ((uint32_t)gy + (uint32_t)g.D[1] * (uint32_t)gz);
             if (live && bad && lg == 0) raise_error(status, CAGQ_ERR_NONFINITE_INPUT);
         } else {
@@ -1230,6 +1237,7 @@ QGrid make_qgrid(const cagq_grid_desc& d, int32_t M) {
     for (int a = 0; a < 3; ++a) {
         g.o[a] = d.origin[a];
         g.s[a] = d.voxel_size[a];
+        g.r[a] = voxel_recip(d.voxel_size[a]);
         g.D[a] = d.dims[a];
     }
     g.d0 = make_magic((uint32_t)d.dims[0]);

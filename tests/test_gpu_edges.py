@@ -127,3 +127,61 @@ def test_context_offsets_again_and_again(N, dims, radius):
         got = cagq.context_list(g, t, off)
         assert np.array_equal(got.cpu().numpy()[:len(list_o)], list_o), (N, radius, M)
     assert cagq.get_device_status(g) == 0
+
+
+@pytest.mark.parametrize("size", [0.1, 1.0 / 3.0, 7.0, 2.0 ** -130, 1e38])
+def test_upsampling_voxel_of_centers_near_faces(size):
+    """The upsampling query's voxel of center points on voxel faces and a few
+    floats beside them, far outside the grid, at zero and not finite, with
+    voxel sizes whose reciprocal is exact, rounded, subnormal or infinite."""
+    s = np.float32(size)
+    dims = (50, 1, 1)
+    k = np.arange(-3, 53).astype(np.float32)
+    with np.errstate(over="ignore"):  # the largest size's far faces are not finite
+        face = (k * s).astype(np.float32)
+        inside = ((np.arange(50, dtype=np.float32) + np.float32(0.5)) * s).clip(0, np.float32(3e38))
+    x = np.concatenate([face + np.float32(0)] + [v for v in _beside(face)] +
+                       [np.float32([0, -0.0, np.inf, -np.inf, np.nan, 3e38, -3e38]), k + np.float32(0.37)])
+    Q = np.zeros((1, len(x), 3), np.float32)
+    Q[0, :, 0] = x
+    P = np.zeros((1, 50, 3), np.float32)
+    P[0, :, 0] = inside
+    spec = W.GridSpec((0.0,) * 3, (float(s), 1.0, 1.0), dims, 4, 1)
+    ot = oracle.Table(P, oracle.grid_from_spec(spec))
+    g = cagq.build_grid(torch.from_numpy(P).to("cuda:0"), cagq.desc_from_spec(spec))
+    for K, mode in ((8, "knn"), (32, "cube")):
+        a = cagq.query_points(g, torch.from_numpy(Q).to("cuda:0"), K, mode, 3)
+        b = ot.query_points(Q, K, mode, 3, allow_nonfinite=True)
+        for name in ("center_lin", "ctx_count", "n_valid", "node_idx"):
+            assert np.array_equal(a[name].cpu().numpy(), b[name]), (size, mode, name)
+
+
+def _beside(v):
+    """The floats one and two steps above and below each value."""
+    up, down = v, v
+    for _ in range(2):
+        up = np.nextafter(up, np.float32(np.inf))
+        down = np.nextafter(down, np.float32(-np.inf))
+        yield up
+        yield down
+
+
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 31, 32])
+@pytest.mark.parametrize("mode", ["cube", "knn"])
+def test_short_context_ranks(K, mode):
+    """Contexts of 1 to 40 points, on both sides of one and two chunks and of
+    K, with many points at one place (equal distances, ordered by index) and
+    with weights."""
+    rng = np.random.default_rng(K)
+    dims = (64, 4, 4)
+    counts = np.concatenate([np.arange(1, 41), rng.integers(1, 34, 14)])
+    lin = np.concatenate([np.full(c, 4 + 4 * (i % 14) + 64 * (1 + i // 14 % 2) + 256 * (1 + i // 28 % 2))
+                          for i, c in enumerate(counts)])
+    P = _points_in(lin, dims, rng)
+    same = rng.random(len(lin)) < 0.4  # at their voxel's center
+    P[same] = (((np.stack([lin % 64, lin // 64 % 4, lin // 256], -1) + 0.5) * 0.1).astype(np.float32))[same]
+    P = P[rng.permutation(len(P))][None]
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 48, 1)
+    weights = rng.integers(1, 9, P.shape[:2])
+    for w in (None, weights):
+        run_both(P, spec, 60, K, "rvs", mode, 6, weights=w, where=f"K={K} {mode}")
