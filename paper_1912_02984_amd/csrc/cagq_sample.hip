@@ -7,10 +7,10 @@
 // slot, or the linear id for CAS) rises with the slot, so the m smallest
 // keys are those whose top half is below a bound T, plus the first `need`
 // slots whose top half equals T. A radix select over the top halves finds T
-// and `need` (one workgroup per cloud in LDS, or one histogram kernel per
-// digit for large clouds); a look-back compaction over the slots, counting
-// keys below T and keys equal to T, then writes the winners in slot (=
-// ascending linear id) order.
+// and `need`, and a compaction over the slots, counting keys below T and keys
+// equal to T, writes the winners in slot (= ascending linear id) order: RVS in
+// one workgroup per cloud, or over many blocks for large clouds; CAS from its
+// picks.
 //
 // CAS (Eqs. 1-2, greedy reading): the sequential greedy repeatedly picks the
 // unpicked voxel of largest score 2^16*lambda*#{V in pi(v): C_V = 0} -
@@ -82,12 +82,13 @@ __device__ __forceinline__ uint64_t sel_pack(uint64_t bound, uint32_t need) {
     return ((uint64_t)need << 33) | bound;
 }
 
-// One workgroup per cloud: the bound and tie count of the m = min(M, |O_v|)
-// smallest keys by an 8-bit radix select over their top halves. Unpicked CAS
+// CAS pick keys, smaller clouds, one workgroup per cloud: the bound and tie
+// count of the m = min(M, |O_v|) smallest complements by an 8-bit radix select
+// over their top halves. Unpicked
 // voxels (key ~0) are never among the m smallest and are not counted. Also
 // clears the scan state of the compaction that follows.
 __global__ __launch_bounds__(kSelThreads) void k_sel_threshold(
-    int32_t N, int64_t tiles_s, const int32_t* __restrict__ nvox, int32_t M, int key_mode, uint64_t seed,
+    int32_t N, int64_t tiles_s, const int32_t* __restrict__ nvox, int32_t M,
     const uint64_t* __restrict__ cas_pick, uint64_t* __restrict__ thr, int32_t* __restrict__ m_valid,
     uint64_t* __restrict__ desc_s, int* __restrict__ status) {
     __shared__ uint32_t hist[256];
@@ -96,8 +97,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_threshold(
     const int32_t b = blockIdx.x;
     const int32_t nv = nvox[b];
     const int32_t m = M < nv ? M : nv;
-    const uint64_t hb = sm64(sm64(seed ^ 1ull) ^ (uint64_t)b);
-    const uint64_t* pick = cas_pick ? cas_pick + (size_t)b * N : nullptr;
+    const uint64_t* pick = cas_pick + (size_t)b * N;
     const int tid = threadIdx.x;
     const int lane = lane_id();
     for (int64_t t = tid; t < tiles_s; t += kSelThreads) desc_s[(size_t)b * tiles_s + t] = 0;
@@ -114,12 +114,12 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_threshold(
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int32_t s = s0 + u * kSelThreads + tid;
-                k[u] = s < nv ? select_key(key_mode, hb, s, pick) : 0;
+                k[u] = s < nv ? ~pick[s] : 0;
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int32_t s = s0 + u * kSelThreads + tid;
-                const bool act = s < nv && (k[u] & mask) == prefix && (key_mode == 0 || k[u] != ~0ull);
+                const bool act = s < nv && (k[u] & mask) == prefix && k[u] != ~0ull;
                 const uint32_t d = (uint32_t)(k[u] >> shift) & 255u;
                 // one atomic for the wave when all its counted keys share a digit
                 const uint64_t am = __ballot(act);
@@ -221,7 +221,7 @@ __device__ __forceinline__ void cas_u_bound(const uint32_t* __restrict__ uhist, 
     }
 }
 
-// Ordered compaction of the chosen slots: tile of kScanTile slots per block,
+// Ordered compaction of the chosen slots (CAS): tile of kScanTile slots per block,
 // look-back scan over the packed pair (keys below the bound << 31 | keys at
 // the bound). Slot s chosen at position p < m writes its linear id to every
 // j = p, p + m, p + 2m, ... < M (the cyclic padding). The bound comes from
@@ -229,7 +229,7 @@ __device__ __forceinline__ void cas_u_bound(const uint32_t* __restrict__ uhist, 
 // when the first tile of each cloud also writes thr and m_valid.
 __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
     int32_t N, int64_t tiles_s, const int32_t* __restrict__ nvox, const uint32_t* __restrict__ vox_lin,
-    int32_t M, int key_mode, uint64_t seed, const uint64_t* __restrict__ cas_pick,
+    int32_t M, const uint64_t* __restrict__ cas_pick,
     uint64_t* __restrict__ thr, int32_t* __restrict__ center_lin, uint64_t* __restrict__ desc_s,
     int* __restrict__ status, const uint32_t* __restrict__ uhist, int64_t unit, int32_t* __restrict__ m_valid) {
     __shared__ uint32_t s_ticket;
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         const size_t at = (size_t)b * N + (size_t)(s0 + i < N ? s0 + i : N - 1);
-        pk[i] = cas_pick ? cas_pick[at] : 0ull;
+        pk[i] = cas_pick[at];
         ln[i] = vox_lin[at];
     }
     const int32_t nv = nvox[b];
@@ -274,7 +274,6 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
     }
     const uint64_t bound = packed & ((1ull << 33) - 1);
     const uint32_t need = (uint32_t)(packed >> 33);
-    const uint64_t hb = sm64(sm64(seed ^ 1ull) ^ (uint64_t)b);
     bool lt[kScanItems], eq[kScanItems];
     uint64_t cnt = 0;
 #pragma unroll
@@ -282,9 +281,9 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
         const int32_t s = s0 + i;
         // with the picks' U histogram, an unpicked voxel stands for one with U = 0
         const uint64_t pick = uhist && pk[i] == 0 ? cas_key(0, ln[i]) : pk[i];
-        const uint64_t k = s < nv ? (key_mode == 0 ? select_key(0, hb, s, nullptr) : ~pick) : ~0ull;
+        const uint64_t k = s < nv ? ~pick : ~0ull;
         const uint64_t top = k >> 32;
-        const bool counted = s < nv && (key_mode == 0 || k != ~0ull);
+        const bool counted = s < nv && k != ~0ull;
         lt[i] = counted && top < bound;
         eq[i] = counted && top == bound;
         cnt += lt[i] ? (1ull << 31) : (eq[i] ? 1ull : 0ull);
@@ -304,6 +303,155 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
             }
         }
         before += lt[i] ? (1ull << 31) : (eq[i] ? 1ull : 0ull);
+    }
+}
+
+// ---- RVS selection of smaller clouds: one workgroup of T threads per cloud
+// and one launch. Slot u * T + tid's key stays in a register from the
+// histogram to the emit. A pass counts the next digit (10, 11 and 11 bits) of
+// the keys that share the digits before it, and finds the digit where the
+// count reaches what is needed; the keys are uniform hashes, so that after one
+// pass a few share it (nvox / 1024 on average), and as soon as they are at most
+// kOneCand their ranks are counted directly. The emit's positions come from
+// one ballot per 64 slots and one scan over the ballots' counts.
+// Measured against a launch for the bound (four 8-bit passes that recompute
+// the keys) and one for the emit: 1024 points 21 -> 19 us a
+// layer, the 8192-, 2048- and 512-point layers of one scene 137 -> 127 us a
+// network.
+constexpr int kOneBins = 2048;
+constexpr uint32_t kOneCand = 16;
+
+template <int T, int PER>
+__global__ __launch_bounds__(T) void k_sel_one(int32_t N, const int32_t* __restrict__ nvox,
+                                               const uint32_t* __restrict__ vox_lin, int32_t M, uint64_t seed,
+                                               int32_t* __restrict__ center_lin, int32_t* __restrict__ m_valid) {
+    constexpr int kW = T / kWave, kGroups = PER * kW;  // groups of 64 slots, in slot order
+    constexpr int kBinsPer = kOneBins / T, kGroupsPer = (kGroups + kWave - 1) / kWave;
+    __shared__ uint32_t s_hist[kOneBins];
+    __shared__ uint32_t s_wave[kW];
+    __shared__ uint32_t s_find[3];
+    __shared__ uint32_t s_cand[kOneCand];
+    __shared__ uint32_t s_nc;
+    __shared__ uint32_t s_grp[kGroups];
+    const int32_t b = blockIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const uint32_t* vl = vox_lin + (size_t)b * N;
+    // the slots' linear ids, for the emit (the passes cover their latency;
+    // indices clamped into the cloud's row)
+    uint32_t ln[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int32_t sl = u * T + tid;
+        ln[u] = vl[sl < N ? sl : N - 1];
+    }
+    const int32_t nv = nvox[b];
+    const int32_t m = M < nv ? M : nv;
+    const uint64_t hb = sm64(sm64(seed ^ 1ull) ^ (uint64_t)b);
+    uint32_t k[PER];  // the keys' top halves
+#pragma unroll
+    for (int u = 0; u < PER; ++u) k[u] = (uint32_t)(sm64(hb ^ (uint64_t)(uint32_t)(u * T + tid)) >> 32);
+    if (tid == 0) {
+        m_valid[b] = m;
+        s_nc = 0;
+    }
+    if (m <= 0) return;
+    // the keys below `bound` are chosen, and of those equal to it the first `need`
+    uint32_t prefix = 0, mask = 0, need = (uint32_t)m, cnt = 0;
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 22 : pass == 1 ? 11 : 0;
+        const uint32_t dm = pass == 0 ? 1023u : 2047u;
+        for (int i = tid; i < kOneBins; i += T) s_hist[i] = 0u;
+        lds_barrier();
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u * T + tid < nv && (k[u] & mask) == prefix) atomicAdd(&s_hist[(k[u] >> shift) & dm], 1u);
+        lds_barrier();
+        uint32_t h[kBinsPer], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kBinsPer; ++i) {
+            h[i] = s_hist[tid * kBinsPer + i];
+            sum += h[i];
+        }
+        const uint32_t incl = wave_incl_sum_u32(sum);
+        if (lane == kWave - 1) s_wave[wv] = incl;
+        lds_barrier();
+        uint32_t run = incl - sum;
+#pragma unroll
+        for (int w = 0; w < kW; ++w) run += w < wv ? s_wave[w] : 0u;
+#pragma unroll
+        for (int i = 0; i < kBinsPer; ++i) {
+            if (run < need && run + h[i] >= need) {
+                s_find[0] = (uint32_t)(tid * kBinsPer + i);
+                s_find[1] = run;
+                s_find[2] = h[i];
+            }
+            run += h[i];
+        }
+        lds_barrier();
+        prefix |= s_find[0] << shift;
+        mask |= dm << shift;
+        need -= s_find[1];
+        cnt = s_find[2];
+        if (cnt <= kOneCand) break;
+    }
+    uint32_t bound = prefix;
+    if (mask != ~0u) {
+        // the few keys left: their ranks, in every wave alike
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u * T + tid < nv && (k[u] & mask) == prefix) s_cand[atomicAdd(&s_nc, 1u)] = k[u];
+        lds_barrier();
+        const uint32_t mine = lane < (int)cnt ? s_cand[lane] : ~0u;
+        uint32_t lt = 0, le = 0;
+        for (uint32_t j = 0; j < cnt; ++j) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
+            lt += o < mine ? 1u : 0u;
+            le += o <= mine ? 1u : 0u;
+        }
+        const uint64_t hit = __ballot(lane < (int)cnt && lt < need && le >= need);
+        const int l = __ffsll((unsigned long long)hit) - 1;
+        bound = (uint32_t)__builtin_amdgcn_readlane((int)mine, l);
+        need -= (uint32_t)__builtin_amdgcn_readlane((int)lt, l);
+    }
+    // keys below the bound << 16 | keys at it (both below 2^15), per group of
+    // 64 slots, then scanned over the groups
+    static_assert(T * PER < 32768, "two 16-bit counts a word");
+    uint64_t blt[PER], beq[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const bool in = u * T + tid < nv;
+        blt[u] = __ballot(in && k[u] < bound);
+        beq[u] = __ballot(in && k[u] == bound);
+        if (lane == 0) s_grp[u * kW + wv] = ((uint32_t)__popcll(blt[u]) << 16) | (uint32_t)__popcll(beq[u]);
+    }
+    lds_barrier();
+    if (wv == 0) {
+        uint32_t g[kGroupsPer], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kGroupsPer; ++i) {
+            g[i] = lane * kGroupsPer + i < kGroups ? s_grp[lane * kGroupsPer + i] : 0u;
+            sum += g[i];
+        }
+        uint32_t run = wave_incl_sum_u32(sum) - sum;
+#pragma unroll
+        for (int i = 0; i < kGroupsPer; ++i) {
+            if (lane * kGroupsPer + i < kGroups) s_grp[lane * kGroupsPer + i] = run;
+            run += g[i];
+        }
+    }
+    lds_barrier();
+    int32_t* out = center_lin + (size_t)b * M;
+    const uint64_t below = (1ull << lane) - 1;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const uint32_t base = s_grp[u * kW + wv];
+        const uint32_t nlt = (base >> 16) + (uint32_t)__popcll(blt[u] & below);
+        const uint32_t neq = (base & 0xFFFFu) + (uint32_t)__popcll(beq[u] & below);
+        const bool lt = (blt[u] >> lane) & 1ull, eq = (beq[u] >> lane) & 1ull;
+        if (lt || (eq && neq < need)) {
+            const uint32_t pos = nlt + (neq < need ? neq : need);
+            for (int64_t j = (int64_t)pos; j < M; j += m) out[j] = (int32_t)ln[u];
+        }
     }
 }
 
@@ -1281,13 +1429,21 @@ hipError_t launch_select(const Layout& L, void* ws, int32_t M, int key_mode, uin
         k_sel_emit_chunks<<<dim3((unsigned)nchunk, (unsigned)L.B), kPickThreads, 0, s>>>(
             L.N, nvox, at<uint32_t>(ws, L.vox_lin), M, key_mode, seed, pick, thr, base, take, center_lin);
         return hipGetLastError();
-    } else {
-        k_sel_threshold<<<L.B, kSelThreads, 0, s>>>(L.N, L.tiles_s, nvox, M, key_mode, seed, pick, thr, m_valid,
-                                                    desc_s, status);
     }
+    if (key_mode == 0) {
+        const uint32_t* vl = at<uint32_t>(ws, L.vox_lin);
+        auto go = [&](auto kern, int threads) {
+            kern<<<L.B, threads, 0, s>>>(L.N, nvox, vl, M, seed, center_lin, m_valid);
+            return hipGetLastError();
+        };
+        if (L.N <= 1024) return go(k_sel_one<256, 4>, 256);
+        if (L.N <= 4096) return go(k_sel_one<1024, 4>, 1024);
+        if (L.N <= 8192) return go(k_sel_one<1024, 8>, 1024);
+        return go(k_sel_one<1024, 16>, 1024);
+    }
+    k_sel_threshold<<<L.B, kSelThreads, 0, s>>>(L.N, L.tiles_s, nvox, M, pick, thr, m_valid, desc_s, status);
     k_sel_emit<<<(unsigned)(L.B * L.tiles_s), kScanThreads, 0, s>>>(L.N, L.tiles_s, nvox,
-                                                                   at<uint32_t>(ws, L.vox_lin), M, key_mode, seed,
-                                                                   pick, thr, center_lin, desc_s, status, nullptr, 0,
+                                                                   at<uint32_t>(ws, L.vox_lin), M, pick, thr, center_lin, desc_s, status, nullptr, 0,
                                                                    nullptr);
     return hipGetLastError();
 }
@@ -1304,7 +1460,7 @@ hipError_t launch_select_cas(const Layout& L, const cagq_grid_desc& d, void* ws,
     const int32_t* nvox = at<int32_t>(ws, L.nvox);
     // the neighbour-list kernel has cleared the compaction's scan state
     k_sel_emit<<<(unsigned)(L.B * L.tiles_s), kScanThreads, 0, s>>>(L.N, L.tiles_s, nvox,
-                                                                   at<uint32_t>(ws, L.vox_lin), M, 1, 0,
+                                                                   at<uint32_t>(ws, L.vox_lin), M,
                                                                    at<uint64_t>(ws, L.cas_pick), thr, center_lin,
                                                                    desc_s, status, ctl.uhist, 65536 * side * side * side,
                                                                    m_valid);

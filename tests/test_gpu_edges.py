@@ -185,3 +185,23 @@ def test_short_context_ranks(K, mode):
     weights = rng.integers(1, 9, P.shape[:2])
     for w in (None, weights):
         run_both(P, spec, 60, K, "rvs", mode, 6, weights=w, where=f"K={K} {mode}")
+
+
+@pytest.mark.parametrize("N", [1, 63, 1023, 1024, 1025, 4096, 4097, 8192, 8193, 16383, 16384])
+def test_rvs_selection_sizes(N):
+    """Random Voxel Sampling where its kernel and its keys per thread change
+    (at 16383 voxels a second digit is counted for some bounds), for M of one
+    voxel, a few, half, all but one, all, and more than there are."""
+    rng = np.random.default_rng(N)
+    dims = (32, 32, 32)
+    lin = np.stack([rng.choice(dims[0] * dims[1] * dims[2], N, replace=False) for _ in range(2)])
+    P = _points_in(lin, dims, rng)
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 2, 1)
+    ot = oracle.Table(P, oracle.grid_from_spec(spec))
+    g = cagq.build_grid(torch.from_numpy(P).to("cuda:0"), cagq.desc_from_spec(spec))
+    for M in sorted({1, min(5, N), (N + 1) // 2, max(1, N - 1), N, 2 * N + 3}):
+        for seed in (1, 2, 3):
+            cl, mv = cagq.sample_centers(g, M, "rvs", seed)
+            ocl, omv = ot.sample_rvs(M, seed)
+            assert np.array_equal(mv.cpu().numpy(), omv), (N, M, seed)
+            assert np.array_equal(cl.cpu().numpy(), ocl), (N, M, seed)
