@@ -6,9 +6,9 @@
 // with one bit per grid voxel; a voxel's slot is its rank (popcount of the
 // bits before it), which is a minimal, order-preserving hash of the linear
 // voxel id to a compact slot. Points mark a byte per voxel with plain stores
-// (no atomics); a single-pass decoupled look-back scan packs the bytes into
-// bitmap words and ranks them; counts come from one atomic per point,
-// offsets from a second look-back scan over the slots. Per-voxel lists hold
+// (no atomics); two kernels pack the bytes into bitmap words and rank them;
+// counts come from one atomic per point,
+// offsets from a look-back scan over the slots. Per-voxel lists hold
 // the n_v lowest point indices in ascending order, independent of the
 // arrival order the atomics produce: small voxels rank each point against
 // the voxel's bucket, large voxels are reduced by a wavefront bitonic
@@ -83,55 +83,71 @@ __device__ __forceinline__ uint64_t pack_bytes(const uint4* __restrict__ p) {
     return r;
 }
 
-// Occupancy words from the bytes, and their ranks: word_rank[w] = occupied
-// voxels before word w. Also lists every occupied voxel's linear id at its
-// slot and clears its count.
-__global__ __launch_bounds__(kScanThreads) void k_rank(
-    const uint8_t* __restrict__ bytemap, uint64_t* __restrict__ bitmap, int64_t W, int64_t tiles_w, int32_t N,
-    uint32_t* __restrict__ word_rank, uint32_t* __restrict__ vox_lin, uint32_t* __restrict__ vox_count,
-    int32_t* __restrict__ nvox, uint64_t* __restrict__ desc_w, int* __restrict__ status) {
-    __shared__ uint32_t s_ticket;
-    __shared__ uint64_t s_wave[kScanThreads / kWave];
-    __shared__ uint64_t s_prefix;
-    if (threadIdx.x == 0) s_ticket = atomicAdd((unsigned*)&status[kStTicketRank], 1u);
-    __syncthreads();
-    const uint32_t t = s_ticket;
-    const int32_t b = (int32_t)(t / tiles_w);
-    const int64_t tile = (int64_t)(t % tiles_w);
-    const uint4* bytes = reinterpret_cast<const uint4*>(bytemap + (size_t)b * W * 64);
-    uint64_t* bm = bitmap + (size_t)b * W;
-    const int64_t w0 = tile * kRankTile + (int64_t)threadIdx.x * kRankItems;
-    uint64_t words[kRankItems];
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int i = 0; i < kRankItems; ++i) {
-        int64_t w = w0 + i;
-        words[i] = w < W ? pack_bytes(bytes + (size_t)w * 4) : 0ull;
-        if (w < W) bm[w] = words[i];
-        cnt += (uint32_t)__popcll(words[i]);
+// Occupancy words from the bytes, one word per thread, and the occupied voxels
+// of each tile of kRankTile words and (device atomics on zeroed words, one per
+// tile) of each group of kRankGroup tiles. With k_rank this replaces a
+// look-back scan, whose tiles numbered themselves by tickets from one address:
+// at about 20 ns a ticket the 1296 tiles of a 2^20-point sweep (802 x 802 x 33
+// voxels) took 30 us, and 27 us with four words a thread, where a lane then
+// lists four words' voxels in series; the two kernels take half (the sweep's
+// layer: 236 -> 226 us).
+__global__ __launch_bounds__(kScanThreads) void k_pack(const uint8_t* __restrict__ bytemap,
+                                                       uint64_t* __restrict__ bitmap, int64_t W, int64_t tiles_w,
+                                                       uint32_t* __restrict__ tile_cnt,
+                                                       uint32_t* __restrict__ group_cnt) {
+    __shared__ uint32_t s_wave[kScanThreads / kWave];
+    const int32_t b = (int32_t)(blockIdx.x / tiles_w);
+    const int64_t tile = (int64_t)(blockIdx.x % tiles_w);
+    const int64_t w = tile * kRankTile + threadIdx.x;
+    uint64_t word = 0;
+    if (w < W) {
+        word = pack_bytes(reinterpret_cast<const uint4*>(bytemap + (size_t)b * W * 64) + (size_t)w * 4);
+        bitmap[(size_t)b * W + w] = word;
     }
+    const uint32_t n = wave_sum_u32((uint32_t)__popcll(word));
+    if (lane_id() == 0) s_wave[threadIdx.x / kWave] = n;
+    lds_barrier();
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+#pragma unroll
+        for (int i = 0; i < kScanThreads / kWave; ++i) t += s_wave[i];
+        tile_cnt[(size_t)b * tiles_w + tile] = t;
+        if (t) atomicAdd(&group_cnt[(size_t)b * (tiles_w / kRankGroup + 1) + tile / kRankGroup], t);
+    }
+}
+
+// Ranks of the occupancy words: word_rank[w] = occupied voxels before word w,
+// from the groups and the tiles before this one. Also lists every occupied
+// voxel's linear id at its slot and clears its count.
+__global__ __launch_bounds__(kScanThreads) void k_rank(
+    const uint64_t* __restrict__ bitmap, int64_t W, int64_t tiles_w, int32_t N,
+    const uint32_t* __restrict__ tile_cnt, const uint32_t* __restrict__ group_cnt, uint32_t* __restrict__ word_rank,
+    uint32_t* __restrict__ vox_lin, uint32_t* __restrict__ vox_count, int32_t* __restrict__ nvox) {
+    __shared__ uint64_t s_wave[kScanThreads / kWave];
+    const int32_t b = (int32_t)(blockIdx.x / tiles_w);
+    const int64_t tile = (int64_t)(blockIdx.x % tiles_w);
+    const int64_t w = tile * kRankTile + threadIdx.x;
+    uint64_t m = w < W ? bitmap[(size_t)b * W + w] : 0ull;
+    const int64_t g = tile / kRankGroup;
+    const uint32_t* gc = group_cnt + (size_t)b * (tiles_w / kRankGroup + 1);
+    uint32_t before = 0;
+    for (int64_t i = threadIdx.x; i < g; i += kScanThreads) before += gc[i];
+    const int64_t t0 = g * kRankGroup;
+    if (threadIdx.x < tile - t0) before += tile_cnt[(size_t)b * tiles_w + t0 + threadIdx.x];
+    // both sums in one scan: occupied voxels before the tile << 32 | of the tile
     uint64_t total;
-    uint64_t excl = block_excl_scan(cnt, s_wave, &total);
-    uint64_t prefix = tile_lookback(desc_w + (size_t)b * tiles_w, tile, total, &s_prefix);
-    uint32_t r = (uint32_t)(prefix + excl);
-    uint32_t* wr = word_rank + (size_t)b * W;
+    const uint64_t mine = ((uint64_t)before << 32) | (uint32_t)__popcll(m);
+    const uint64_t excl = block_excl_scan(mine, s_wave, &total);
+    uint32_t r = (uint32_t)(total >> 32) + (uint32_t)excl;
+    if (tile == tiles_w - 1 && threadIdx.x == 0) nvox[b] = (int32_t)((uint32_t)(total >> 32) + (uint32_t)total);
+    if (w >= W) return;
+    word_rank[(size_t)b * W + w] = r;
     uint32_t* vl = vox_lin + (size_t)b * N;
     uint32_t* vc = vox_count + (size_t)b * N;
-#pragma unroll
-    for (int i = 0; i < kRankItems; ++i) {
-        int64_t w = w0 + i;
-        if (w >= W) break;
-        wr[w] = r;
-        uint64_t m = words[i];
-        while (m) {
-            int bit = __ffsll((unsigned long long)m) - 1;
-            vl[r] = (uint32_t)(w * 64 + bit);
-            vc[r] = 0u;
-            ++r;
-            m &= m - 1;
-        }
+    for (; m; m &= m - 1, ++r) {
+        vl[r] = (uint32_t)(w * 64 + __ffsll((unsigned long long)m) - 1);
+        vc[r] = 0u;
     }
-    if (tile == tiles_w - 1 && threadIdx.x == 0) nvox[b] = (int32_t)(prefix + total);
 }
 
 // One lane per point: slot (rank of its voxel) and arrival position.
@@ -172,19 +188,16 @@ __global__ __launch_bounds__(256) void k_count(int32_t BN, int32_t N, int64_t W,
 // prefix of count, over the slots [0, nvox[b]) of each cloud; entry nvox[b]
 // holds the totals. Both are scanned at once, packed as (full << 31) | stored.
 __global__ __launch_bounds__(kScanThreads) void k_offsets(
-    int32_t N, int64_t tiles_s, uint32_t n_v, const int32_t* __restrict__ nvox,
+    int32_t B, int32_t N, int64_t tiles_s, uint32_t n_v, const int32_t* __restrict__ nvox,
     const uint32_t* __restrict__ vox_count, uint32_t* __restrict__ vox_off, uint32_t* __restrict__ full_off,
     uint64_t* __restrict__ desc_s, int* __restrict__ status, uint32_t* __restrict__ big, int64_t big_cap) {
     __shared__ uint32_t s_ticket;
     __shared__ uint64_t s_wave[kScanThreads / kWave];
     __shared__ uint64_t s_prefix;
-    if (threadIdx.x == 0) s_ticket = atomicAdd((unsigned*)&status[kStTicketOff], 1u);
-    __syncthreads();
-    const uint32_t t = s_ticket;
-    const int32_t b = (int32_t)(t / tiles_s);
-    const int64_t tile = (int64_t)(t % tiles_s);
+    int32_t b;
+    int64_t tile;
+    if (!slot_tile(B, tiles_s, kScanTile, nvox, (unsigned*)&status[kStTicketOff], &s_ticket, b, tile)) return;
     const int64_t nv = nvox[b];
-    if (tile * kScanTile >= nv) return;  // no slot here; later tiles never wait on this one
     const int64_t s0 = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
     const uint32_t* vc = vox_count + (size_t)b * N;
     uint32_t cnt[kScanItems];
@@ -1544,15 +1557,18 @@ hipError_t launch_build(const float* points, const Layout& L, const cagq_grid_de
     const int pb = (BN + 255) / 256;
     k_mark<<<pb, 256, 0, s>>>(points, N, BN, g, L.W, at<uint32_t>(ws, L.pt_slot), at<uint8_t>(ws, L.bytemap),
                               status);
+    uint32_t* tile_cnt = at<uint32_t>(ws, L.desc_w);
+    uint32_t* group_cnt = tile_cnt + (size_t)B * L.tiles_w;
+    k_pack<<<(unsigned)(B * L.tiles_w), kScanThreads, 0, s>>>(at<uint8_t>(ws, L.bytemap), at<uint64_t>(ws, L.bitmap),
+                                                              L.W, L.tiles_w, tile_cnt, group_cnt);
     k_rank<<<(unsigned)(B * L.tiles_w), kScanThreads, 0, s>>>(
-        at<uint8_t>(ws, L.bytemap), at<uint64_t>(ws, L.bitmap), L.W, L.tiles_w, N, at<uint32_t>(ws, L.word_rank),
-        at<uint32_t>(ws, L.vox_lin), at<uint32_t>(ws, L.vox_count), at<int32_t>(ws, L.nvox),
-        at<uint64_t>(ws, L.desc_w), status);
+        at<uint64_t>(ws, L.bitmap), L.W, L.tiles_w, N, tile_cnt, group_cnt, at<uint32_t>(ws, L.word_rank),
+        at<uint32_t>(ws, L.vox_lin), at<uint32_t>(ws, L.vox_count), at<int32_t>(ws, L.nvox));
     k_count<<<pb, 256, 0, s>>>(BN, N, L.W, at<uint64_t>(ws, L.bitmap), at<uint32_t>(ws, L.word_rank),
                                at<uint32_t>(ws, L.pt_slot), at<uint32_t>(ws, L.pt_pos),
                                at<uint32_t>(ws, L.vox_count));
     k_offsets<<<(unsigned)(B * L.tiles_s), kScanThreads, 0, s>>>(
-        N, L.tiles_s, (uint32_t)d.n_v, at<int32_t>(ws, L.nvox), at<uint32_t>(ws, L.vox_count),
+        B, N, L.tiles_s, (uint32_t)d.n_v, at<int32_t>(ws, L.nvox), at<uint32_t>(ws, L.vox_count),
         at<uint32_t>(ws, L.vox_off), at<uint32_t>(ws, L.full_off), at<uint64_t>(ws, L.desc_s), status,
         at<uint32_t>(ws, L.big), L.big_cap);
     k_scatter<<<pb, 256, 0, s>>>(BN, N, at<uint32_t>(ws, L.pt_slot), at<uint32_t>(ws, L.pt_pos),

@@ -17,8 +17,11 @@ constexpr int kWave = 64;
 constexpr int kScanThreads = 256;       // threads per scan tile
 constexpr int kScanItems = 4;           // items per thread in a scan tile
 constexpr int kScanTile = kScanThreads * kScanItems;
-constexpr int kRankItems = 1;           // occupancy words per thread of the rank scan
-constexpr int kRankTile = kScanThreads * kRankItems;
+constexpr int kEmitItems = 8;           // slots per thread of the CAS selection's compaction
+constexpr int kEmitTile = kScanThreads * kEmitItems;
+static_assert(kEmitTile >= kScanTile, "the compaction uses the offsets scan's descriptors");
+constexpr int kRankTile = kScanThreads; // occupancy words per tile of the rank kernels, one per thread
+constexpr int kRankGroup = 64;          // tiles per group total
 constexpr uint32_t kBigVoxel = 64;      // voxels holding more points use the wave selector
 constexpr int kSelBins = 2048;          // bins of the 11-bit digits of the many-block select
 constexpr int kSelChunk = 4096;         // slots per chunk of the many-block select
@@ -35,7 +38,6 @@ constexpr int64_t kTileScanCap = 1 << 16;  // histogram entries a scatter tile m
 // Status word slots (int32 each) at the start of the workspace's control block.
 enum StatusSlot {
     kStError = 0,      // first device-side error code (0 = none)
-    kStTicketRank = 1, // tile tickets of the occupancy-rank scan
     kStTicketOff = 2,  // tile tickets of the offsets scan
     kStBigCount = 3,   // number of voxels with more than kBigVoxel points
     kStTicketSel = 4,  // tile tickets of the center compaction scan
@@ -54,7 +56,7 @@ struct Layout {
     int32_t B, N;
     int64_t V;            // voxels per grid
     int64_t W;            // 64-bit occupancy words per cloud
-    int64_t tiles_w;      // rank-scan tiles (kRankTile words) over the words of one cloud
+    int64_t tiles_w;      // rank tiles (kRankTile words) over the words of one cloud
     int64_t tiles_s;      // scan tiles over the slots of one cloud
     int64_t ctx_tiles;    // capacity of the context-offsets scan, ceil(B * N / kScanThreads)
     int64_t big_cap;      // capacity of the big-voxel list
@@ -77,7 +79,8 @@ struct Layout {
     size_t desc_h;        // u64 [blocks of the column scan] scan descriptors (brick totals)
     size_t clear_brick;   // [status, clear_brick) is zeroed by the brick build (status, tickets,
                           // descriptors, hdone)
-    size_t desc_w;        // u64 [B][tiles_w] scan descriptors (occupancy ranks)
+    size_t desc_w;        // u32 [B][tiles_w] occupied voxels per tile, u32 [B][tiles_w / kRankGroup + 1] per
+                          // group of tiles
     size_t desc_s;        // u64 [B][tiles_s] scan descriptors (offsets)
     size_t bytemap;       // u8  [B][64 W] one byte per voxel, 1 when a point lies in it
     size_t bitmap;        // u64 [B][W] occupancy bits, bit (lin & 63) of word lin >> 6
@@ -399,6 +402,37 @@ __device__ inline uint64_t tile_lookback_at(F desc, int64_t tile, uint64_t agg, 
 // The same over a contiguous descriptor array.
 __device__ inline uint64_t tile_lookback(uint64_t* desc, int64_t tile, uint64_t agg, uint64_t* s_out) {
     return tile_lookback_at([desc](int64_t t) { return desc + t; }, tile, agg, s_out);
+}
+
+// The tile of a look-back scan over the slots of B clouds, `per` slots a tile:
+// block blockIdx.x stands for tile blockIdx.x % tiles of cloud blockIdx.x /
+// tiles, and returns false when the cloud has no slot there. The others take a
+// ticket, and the tickets number the tiles with slots, so that a predecessor
+// has always started: tickets come from one address at about 20 ns each, and
+// clouds with many points a voxel leave most tiles without a slot. (Over 64
+// clouds every block takes a ticket: finding a ticket's cloud reads their
+// sizes, a wave's worth at a time.) Every thread of the block calls it.
+__device__ __forceinline__ bool slot_tile(int32_t B, int64_t tiles, int32_t per, const int32_t* __restrict__ nvox,
+                                          unsigned* ticket, uint32_t* s_ticket, int32_t& b, int64_t& tile) {
+    const bool few = B <= kWave;
+    if (few) {
+        b = (int32_t)(blockIdx.x / tiles);
+        if ((int64_t)(blockIdx.x % tiles) * per >= nvox[b]) return false;
+    }
+    if (threadIdx.x == 0) *s_ticket = atomicAdd(ticket, 1u);
+    __syncthreads();
+    const uint32_t t = *s_ticket;
+    if (few) {
+        const int lane = lane_id();
+        const uint32_t need = lane < B ? (uint32_t)((nvox[lane < B ? lane : 0] + per - 1) / per) : 0u;
+        const uint32_t incl = wave_incl_sum_u32(need);
+        b = __ffsll((unsigned long long)__ballot(incl > t)) - 1;
+        tile = (int64_t)(t - (uint32_t)__builtin_amdgcn_readlane((int)(incl - need), b));
+        return true;
+    }
+    b = (int32_t)(t / tiles);
+    tile = (int64_t)(t % tiles);
+    return tile * per < nvox[b];
 }
 
 // Exclusive scan of one 64-bit value per thread across a kScanThreads block;

@@ -221,14 +221,14 @@ __device__ __forceinline__ void cas_u_bound(const uint32_t* __restrict__ uhist, 
     }
 }
 
-// Ordered compaction of the chosen slots (CAS): tile of kScanTile slots per block,
+// Ordered compaction of the chosen slots (CAS): tile of kEmitTile slots per block,
 // look-back scan over the packed pair (keys below the bound << 31 | keys at
 // the bound). Slot s chosen at position p < m writes its linear id to every
 // j = p, p + m, p + 2m, ... < M (the cyclic padding). The bound comes from
 // thr, or with `uhist` (CAS on lists, beta = 0) from the picks' U histogram,
 // when the first tile of each cloud also writes thr and m_valid.
 __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
-    int32_t N, int64_t tiles_s, const int32_t* __restrict__ nvox, const uint32_t* __restrict__ vox_lin,
+    int32_t B, int32_t N, int64_t tiles, const int32_t* __restrict__ nvox, const uint32_t* __restrict__ vox_lin,
     int32_t M, const uint64_t* __restrict__ cas_pick,
     uint64_t* __restrict__ thr, int32_t* __restrict__ center_lin, uint64_t* __restrict__ desc_s,
     int* __restrict__ status, const uint32_t* __restrict__ uhist, int64_t unit, int32_t* __restrict__ m_valid) {
@@ -237,29 +237,22 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
     __shared__ uint64_t s_prefix;
     __shared__ uint32_t s_h[kCasUBins];
     __shared__ uint64_t s_thr;
-    if (threadIdx.x == 0) s_ticket = atomicAdd((unsigned*)&status[kStTicketSel], 1u);
-    __syncthreads();
-    const uint32_t t = s_ticket;
-    const int32_t b = (int32_t)(t / tiles_s);
-    const int64_t tile = (int64_t)(t % tiles_s);
-    const int32_t s0 = (int32_t)(tile * kScanTile) + (int32_t)threadIdx.x * kScanItems;
+    int32_t b;
+    int64_t tile;
+    if (!slot_tile(B, tiles, kEmitTile, nvox, (unsigned*)&status[kStTicketSel], &s_ticket, b, tile)) return;
+    const int32_t s0 = (int32_t)(tile * kEmitTile) + (int32_t)threadIdx.x * kEmitItems;
     // the slots' picks and linear ids are loaded at once, beside the bound's
     // inputs (from indices clamped into the cloud's row; used below nv only)
-    uint64_t pk[kScanItems];
-    uint32_t ln[kScanItems];
+    uint64_t pk[kEmitItems];
+    uint32_t ln[kEmitItems];
 #pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
+    for (int i = 0; i < kEmitItems; ++i) {
         const size_t at = (size_t)b * N + (size_t)(s0 + i < N ? s0 + i : N - 1);
         pk[i] = cas_pick[at];
         ln[i] = vox_lin[at];
     }
     const int32_t nv = nvox[b];
     const int32_t m = M < nv ? M : nv;
-    if (uhist && tile == 0 && threadIdx.x == 0 && m <= 0) {
-        thr[b] = sel_pack(0, 0);
-        m_valid[b] = 0;
-    }
-    if (tile * kScanTile >= nv) return;  // later tiles never wait on this one
     uint64_t packed;
     if (uhist) {
         cas_u_bound(uhist, b, (uint32_t)m, unit, s_h, &s_thr);
@@ -274,10 +267,10 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
     }
     const uint64_t bound = packed & ((1ull << 33) - 1);
     const uint32_t need = (uint32_t)(packed >> 33);
-    bool lt[kScanItems], eq[kScanItems];
+    bool lt[kEmitItems], eq[kEmitItems];
     uint64_t cnt = 0;
 #pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
+    for (int i = 0; i < kEmitItems; ++i) {
         const int32_t s = s0 + i;
         // with the picks' U histogram, an unpicked voxel stands for one with U = 0
         const uint64_t pick = uhist && pk[i] == 0 ? cas_key(0, ln[i]) : pk[i];
@@ -290,10 +283,10 @@ __global__ __launch_bounds__(kScanThreads) void k_sel_emit(
     }
     uint64_t total;
     const uint64_t excl = block_excl_scan(cnt, s_wave, &total);
-    uint64_t before = tile_lookback(desc_s + (size_t)b * tiles_s, tile, total, &s_prefix) + excl;
+    uint64_t before = tile_lookback(desc_s + (size_t)b * tiles, tile, total, &s_prefix) + excl;
     int32_t* out = center_lin + (size_t)b * M;
 #pragma unroll
-    for (int i = 0; i < kScanItems; ++i) {
+    for (int i = 0; i < kEmitItems; ++i) {
         const uint32_t nlt = (uint32_t)(before >> 31), neq = (uint32_t)(before & 0x7FFFFFFFull);
         if (lt[i] || (eq[i] && neq < need)) {
             const uint32_t pos = nlt + (neq < need ? neq : need);
@@ -1442,7 +1435,8 @@ hipError_t launch_select(const Layout& L, void* ws, int32_t M, int key_mode, uin
         return go(k_sel_one<1024, 16>, 1024);
     }
     k_sel_threshold<<<L.B, kSelThreads, 0, s>>>(L.N, L.tiles_s, nvox, M, pick, thr, m_valid, desc_s, status);
-    k_sel_emit<<<(unsigned)(L.B * L.tiles_s), kScanThreads, 0, s>>>(L.N, L.tiles_s, nvox,
+    const int64_t tiles = (L.N + kEmitTile - 1) / kEmitTile;
+    k_sel_emit<<<(unsigned)(L.B * tiles), kScanThreads, 0, s>>>(L.B, L.N, tiles, nvox,
                                                                    at<uint32_t>(ws, L.vox_lin), M, pick, thr, center_lin, desc_s, status, nullptr, 0,
                                                                    nullptr);
     return hipGetLastError();
@@ -1459,7 +1453,8 @@ hipError_t launch_select_cas(const Layout& L, const cagq_grid_desc& d, void* ws,
     int* status = at<int>(ws, L.status);
     const int32_t* nvox = at<int32_t>(ws, L.nvox);
     // the neighbour-list kernel has cleared the compaction's scan state
-    k_sel_emit<<<(unsigned)(L.B * L.tiles_s), kScanThreads, 0, s>>>(L.N, L.tiles_s, nvox,
+    const int64_t tiles = (L.N + kEmitTile - 1) / kEmitTile;
+    k_sel_emit<<<(unsigned)(L.B * tiles), kScanThreads, 0, s>>>(L.B, L.N, tiles, nvox,
                                                                    at<uint32_t>(ws, L.vox_lin), M,
                                                                    at<uint64_t>(ws, L.cas_pick), thr, center_lin,
                                                                    desc_s, status, ctl.uhist, 65536 * side * side * side,

@@ -205,3 +205,22 @@ def test_rvs_selection_sizes(N):
             ocl, omv = ot.sample_rvs(M, seed)
             assert np.array_equal(mv.cpu().numpy(), omv), (N, M, seed)
             assert np.array_equal(cl.cpu().numpy(), ocl), (N, M, seed)
+
+
+@pytest.mark.parametrize("B,N,dims,sample", [(3, 3000, (512, 512, 40), "rvs"), (70, 300, (64, 64, 64), "rvs"),
+                                             (3, 9001, (40, 40, 40), "cas"), (66, 4100, (24, 24, 24), "cas")])
+def test_tiles_of_many_clouds(B, N, dims, sample):
+    """The build of grids too large for bricks (its ranks over tiles and groups
+    of tiles, its offsets over the tiles with slots) and the compaction of
+    many-kernel CAS, with a few clouds and with more than a wave of them, their
+    occupied voxels from a handful to all points', on both sides of a tile."""
+    rng = np.random.default_rng(B)
+    V = dims[0] * dims[1] * dims[2]
+    lin = np.empty((B, N), np.int64)
+    for b in range(B):
+        nv = [7, min(1024, N), min(2049, N), N][b % 4]
+        some = rng.choice(V, nv, replace=False)
+        lin[b] = np.concatenate([some, rng.choice(some, N - nv)])[rng.permutation(N)]
+    P = _points_in(lin, dims, rng)
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 3, 1)
+    run_both(P, spec, 40, 16, sample, "knn", 2, where=f"B={B} N={N} {sample}")
