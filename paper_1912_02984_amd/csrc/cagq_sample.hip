@@ -1106,7 +1106,9 @@ __device__ __forceinline__ int window_owner(uint32_t incl, uint32_t n, uint32_t 
 
 // The first of entries 16c..16c+15 of a list of n2 entries (held in q) that
 // is a competitor and whose key beats `my`, or -1. Positions past the list's
-// end read the voxel's own slot `self`, whose key never beats its own.
+// end read the voxel's own slot `self`, whose key never beats its own. In the
+// first round every entry is a competitor, and their pick rounds are not read.
+template <bool FIRST>
 __device__ __forceinline__ int32_t beats(const uint4 (&q)[4], uint32_t c, uint32_t n2, uint32_t self, uint64_t my,
                                          uint32_t cur, const uint64_t* __restrict__ ky,
                                          const uint32_t* __restrict__ rd) {
@@ -1117,7 +1119,7 @@ __device__ __forceinline__ int32_t beats(const uint4 (&q)[4], uint32_t c, uint32
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         kk[j] = ky[sl[j]];
-        rr[j] = rd[sl[j]];
+        rr[j] = FIRST ? 0u : rd[sl[j]];
     }
     // every entry is tested, without short cuts (which the compiler turns
     // into loads issued one at a time), the first from the end to the front
@@ -1157,8 +1159,13 @@ __device__ __forceinline__ int32_t beats(const uint4 (&q)[4], uint32_t c, uint32
 // round's start) bounds every later pick, so round R counts the picks above
 // round R-1's bound and round R+1 retires the cloud: the stopping rule of the
 // two-kernel rounds, one round later.
+// FIRST is the form of round 0, in which nothing is picked or blocked yet: it
+// reads no pick rounds, half of its scattered loads (four scenes' layer 1:
+// 418 -> 409 us; a test of the round at run time costs every round 1.5 us, the
+// pick rounds' loads then waiting for the keys').
 constexpr int kRoundThreads = 64;  // one wave per block: the blocks spread over every CU
 constexpr int kRoundEnt = 28;      // list entries a possible winner keeps in LDS
+template <bool FIRST>
 __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5))) void k_cas_round(int32_t R, int32_t B, int32_t N, int64_t unit, uint32_t beta_q16,
                                                    int32_t M, const int32_t* __restrict__ nvox,
                                                    const uint32_t* __restrict__ nbr, CasState st, CasPtrs ctl) {
@@ -1172,10 +1179,11 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
     // indices for every lane (a load under a test would be waited for
     // alone); then the blocker's key and pick round, together.
     const size_t gc = in_range ? (size_t)gid : 0;
-    const uint32_t rnd0_ = st.round[gc];
-    const uint64_t pk0_ = st.pick[gc], my0_ = st.key[gc];
-    const int32_t bl0_ = st.blocker[gc];
-    const uint32_t done0 = ctl.done[b];
+    // the first round (FIRST): nothing is picked or blocked yet
+    const uint32_t rnd0_ = FIRST ? 0u : st.round[gc];
+    const uint64_t pk0_ = FIRST ? 0ull : st.pick[gc], my0_ = st.key[gc];
+    const int32_t bl0_ = FIRST ? -1 : st.blocker[gc];
+    const uint32_t done0 = FIRST ? 0u : ctl.done[b];
     const int32_t nv = nvox[b];
     const size_t part = (size_t)B * kCasParts;
     const int32_t b0 = __builtin_amdgcn_readlane(b, 0), b1 = __builtin_amdgcn_readlane(b, kWave - 1);
@@ -1183,7 +1191,7 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
     static_assert(kCasParts == 2 * kWave, "two partials per lane");
     uint32_t cp0 = 0, cp1 = 0;
     uint64_t gp0 = 0, gp1 = 0;
-    if (R > 0 && one_cloud) {
+    if (!FIRST && one_cloud) {
         const size_t pp = (size_t)((R - 1) % kCasBufs) * part + (size_t)b0 * kCasParts + lane_id();
         cp0 = ctl.cpart[pp];
         cp1 = ctl.cpart[pp + kWave];
@@ -1192,8 +1200,8 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
     }
     const size_t cb = (size_t)b * N;
     const int32_t blc = bl0_ >= 0 && bl0_ < N ? bl0_ : 0;
-    const uint64_t kb_ = st.key[cb + blc];
-    const uint32_t rb_ = st.round[cb + blc];
+    const uint64_t kb_ = FIRST ? 0ull : st.key[cb + blc];
+    const uint32_t rb_ = FIRST ? 0u : st.round[cb + blc];
     const uint32_t rnd0 = in_range ? rnd0_ : 0u;
     const uint64_t pk0 = in_range ? pk0_ : 0ull;
     const uint64_t my0 = in_range ? my0_ : 0ull;
@@ -1201,10 +1209,10 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
     bool active = in_range && done0 == 0;
     if (ctl.host && blockIdx.x == 0 && threadIdx.x == 0)  // progress for the host's round issue
         __hip_atomic_store(ctl.host + 1, ctl.epoch | (uint32_t)R, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    const uint32_t prev = R == 0 ? 0u
+    const uint32_t prev = FIRST ? 0u
                           : one_cloud ? wave_sum_u32(cp0 + cp1)
                                       : parts_sum(ctl.cpart + (size_t)((R - 1) % kCasBufs) * part, b);
-    const uint64_t G = R == 0 ? ~0ull
+    const uint64_t G = FIRST ? ~0ull
                        : one_cloud ? wave_max_u64(gp0 > gp1 ? gp0 : gp1)
                                    : parts_max(ctl.gpart + (size_t)((R - 1) % kCasBufs) * part, b);
     // done: enough picks above the bound, or no voxel left that can be picked
@@ -1263,7 +1271,7 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
                 for (int j = 0; j < 4; ++j) q[j] = el[1 + j];
                 n2 = h.y;
                 n_r = h.x;
-                found = beats(q, 0, n2, (uint32_t)s, my0, cur, ky, rd);
+                found = beats<FIRST>(q, 0, n2, (uint32_t)s, my0, cur, ky, rd);
                 if (found == -1) {
                     uint4* se = reinterpret_cast<uint4*>(s_ent[threadIdx.x]);
 #pragma unroll
@@ -1301,7 +1309,7 @@ __global__ __launch_bounds__(kRoundThreads) __attribute__((amdgpu_waves_per_eu(5
 #pragma unroll
                     for (int j = 0; j < 3; ++j) se[j] = q[j];
                 }
-                const int32_t f = beats(q, c, o_n2, (uint32_t)((size_t)o_gid - ob), o_my, cur, st.key + ob,
+                const int32_t f = beats<FIRST>(q, c, o_n2, (uint32_t)((size_t)o_gid - ob), o_my, cur, st.key + ob,
                                         st.round + ob);
                 if (f >= 0) s_found[wbase + owner] = f;  // any beating entry will do
             }
@@ -1511,7 +1519,8 @@ hipError_t run_cas(const Layout& L, const cagq_grid_desc& d, void* ws, int32_t M
     auto launch_batch = [&](int rounds) {
         for (int i = 0; i < rounds; ++i, ++R) {
             if (lists) {
-                k_cas_round<<<(BN + kRoundThreads - 1) / kRoundThreads, kRoundThreads, 0, s>>>(
+                (R == 0 ? k_cas_round<true> : k_cas_round<false>)<<<(BN + kRoundThreads - 1) / kRoundThreads,
+                                                                    kRoundThreads, 0, s>>>(
                     (int32_t)R, B, N, 65536 * lam, beta_q16, M, nvox, nbr, st, ctl);
             } else if (rad == 1) {
                 k_cas_score<1><<<pb, 256, 0, s>>>((int32_t)R, B, N, L.W, g, lam, beta_q16, M, nvox,
