@@ -293,18 +293,36 @@ __device__ __forceinline__ T wave_sum(T v) {
 
 __device__ __forceinline__ uint64_t wave_max64(uint64_t v) { return wave_max_u64(v); }
 
-// Ascending bitonic sort of one 64-bit key per lane over the whole wave.
-__device__ __forceinline__ uint64_t wave_sort64(uint64_t v) {
+// Value of lane `lane ^ j` (j a power of two below 64, known at compile time
+// once unrolled): DPP moves within rows of 16 lanes for j <= 8 (quad
+// permutes for 1 and 2, both row shifts for 4, a row rotate for 8), a
+// swizzle for 16 and a permute for 32. None of them touches LDS memory.
+__device__ __forceinline__ uint32_t xlane(uint32_t v, int j) {
+    switch (j) {
+        case 1: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);  // quad_perm 1,0,3,2
+        case 2: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);  // quad_perm 2,3,0,1
+        case 4: {
+            const uint32_t up = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x104, 0xF, 0xF, true);  // row_shl:4
+            const uint32_t dn = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x114, 0xF, 0xF, true);  // row_shr:4
+            return (threadIdx.x & 4) ? dn : up;
+        }
+        case 8: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
+        case 16: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);  // xor 16 within 32 lanes
+        default: return (uint32_t)__shfl_xor((int)v, j, kWave);
+    }
+}
+
+// Ascending bitonic sort of one key per lane over the whole wave, by the lane
+// exchanges above (only the distances 16 and 32 leave the vector registers).
+__device__ __forceinline__ uint32_t wave_sort32(uint32_t v) {
     const int lane = lane_id();
 #pragma unroll
     for (int k = 2; k <= kWave; k <<= 1) {
 #pragma unroll
         for (int j = k >> 1; j > 0; j >>= 1) {
-            uint64_t o = shfl_xor64(v, j);
-            bool asc = (lane & k) == 0;
-            bool low = (lane & j) == 0;
-            uint64_t mn = o < v ? o : v, mx = o < v ? v : o;
-            v = (asc == low) ? mn : mx;
+            const uint32_t o = xlane(v, j);
+            const bool asc = (lane & k) == 0, low = (lane & j) == 0;
+            v = (asc == low) ? (o < v ? o : v) : (o < v ? v : o);
         }
     }
     return v;
@@ -312,16 +330,14 @@ __device__ __forceinline__ uint64_t wave_sort64(uint64_t v) {
 
 // `best` and `add` each sorted ascending over the wave: returns the 64
 // smallest keys of their union, sorted ascending.
-__device__ __forceinline__ uint64_t wave_merge_low64(uint64_t best, uint64_t add) {
+__device__ __forceinline__ uint32_t wave_merge_low32(uint32_t best, uint32_t add) {
     const int lane = lane_id();
-    uint64_t rev = shfl64(add, kWave - 1 - lane);
-    uint64_t v = rev < best ? rev : best;     // bitonic: the 64 smallest of the union
+    const uint32_t rev = (uint32_t)__shfl((int)add, kWave - 1 - lane, kWave);
+    uint32_t v = rev < best ? rev : best;  // bitonic: the 64 smallest of the union
 #pragma unroll
     for (int j = kWave >> 1; j > 0; j >>= 1) {
-        uint64_t o = shfl_xor64(v, j);
-        bool low = (lane & j) == 0;
-        uint64_t mn = o < v ? o : v, mx = o < v ? v : o;
-        v = low ? mn : mx;
+        const uint32_t o = xlane(v, j);
+        v = (lane & j) == 0 ? (o < v ? o : v) : (o < v ? v : o);
     }
     return v;
 }

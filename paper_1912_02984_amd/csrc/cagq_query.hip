@@ -89,25 +89,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Value of lane `lane ^ j` (j a power of two below 64, known at compile time
-// once unrolled): DPP moves within rows of 16 lanes for j <= 8 (quad
-// permutes for 1 and 2, both row shifts for 4, a row rotate for 8), a
-// swizzle for 16 and a permute for 32. None of them touches LDS memory.
-__device__ __forceinline__ uint32_t xlane(uint32_t v, int j) {
-    switch (j) {
-        case 1: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);  // quad_perm 1,0,3,2
-        case 2: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);  // quad_perm 2,3,0,1
-        case 4: {
-            const uint32_t up = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x104, 0xF, 0xF, true);  // row_shl:4
-            const uint32_t dn = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x114, 0xF, 0xF, true);  // row_shr:4
-            return (threadIdx.x & 4) ? dn : up;
-        }
-        case 8: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
-        case 16: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);  // xor 16 within 32 lanes
-        default: return (uint32_t)__shfl_xor((int)v, j, kWave);
-    }
-}
-
 __device__ __forceinline__ float xlanef(float v, int j) { return __uint_as_float(xlane(__float_as_uint(v), j)); }
 
 __device__ __forceinline__ uint64_t xlane64(uint64_t v, int j) {

@@ -224,3 +224,20 @@ def test_tiles_of_many_clouds(B, N, dims, sample):
     P = _points_in(lin, dims, rng)
     spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 3, 1)
     run_both(P, spec, 40, 16, sample, "knn", 2, where=f"B={B} N={N} {sample}")
+
+
+@pytest.mark.parametrize("n_v", [1, 31, 64])
+@pytest.mark.parametrize("build", ["one workgroup", "bricks", "large grid"])
+def test_larger_voxels(build, n_v):
+    """Voxels of 64 points (the last ranked one by one), 65, 128, 129 and 700
+    (selected 64 at a time) in each build, their points scattered through the
+    cloud and in falling order."""
+    rng = np.random.default_rng(n_v)
+    dims = {"one workgroup": (16, 16, 16), "bricks": (40, 40, 40), "large grid": (512, 512, 72)}[build]
+    N = 2000 if build == "one workgroup" else 9000
+    V = dims[0] * dims[1] * dims[2]
+    big = np.repeat([5, 77, 78, 300, V - 1], [64, 65, 128, 129, 700])
+    lin = np.concatenate([big, rng.integers(400, V - 1, N - len(big))])
+    P = np.stack([_points_in(lin, dims, rng)[rng.permutation(N)], _points_in(np.sort(lin)[::-1].copy(), dims, rng)])
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, n_v, 2)
+    run_both(P, spec, 200, 32, "rvs", "cube", 8, where=f"{build} n_v={n_v}")
