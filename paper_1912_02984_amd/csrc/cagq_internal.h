@@ -184,12 +184,6 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
     return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
 }
 
-__device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int m) {
-    int lo = __shfl_xor((int)(uint32_t)v, m, kWave);
-    int hi = __shfl_xor((int)(uint32_t)(v >> 32), m, kWave);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
-}
-
 __device__ __forceinline__ uint64_t shfl_up64(uint64_t v, int d) {
     int lo = __shfl_up((int)(uint32_t)v, d, kWave);
     int hi = __shfl_up((int)(uint32_t)(v >> 32), d, kWave);
