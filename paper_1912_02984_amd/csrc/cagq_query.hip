@@ -699,6 +699,22 @@ __device__ __forceinline__ void clean16(uint64_t& k, uint32_t& p, int lg) {
     for (int j = 8; j > 0; j >>= 1) gcx(k, p, j, (lg & j) == 0);
 }
 
+// Adds to `r` how many of the row's 16 lanes hold a `k` below `mine`.
+template <int G, int J>
+__device__ __forceinline__ void count_below(uint32_t k, uint32_t mine, uint32_t& r) {
+    if constexpr (J < G) {
+        r += row_lane<J>(k) < mine ? 1u : 0u;
+        count_below<G, J + 1>(k, mine, r);
+    }
+}
+
+template <int N>
+__device__ __forceinline__ uint64_t row_shr64(uint64_t v) {
+    return ((uint64_t)dpp_row_shr<N>((uint32_t)(v >> 32)) << 32) | dpp_row_shr<N>((uint32_t)v);
+}
+
+constexpr int32_t kRankMin = 8192;  // centers of a launch above which k_query_r2 ranks a block's centers
+
 // K <= 32, Cube Query or k-NN: 16 lanes per center (four per wave).
 //   1. Each group probes the (2r+1)^2 grid rows of its center's block, one
 //      lane per row: a row segment of the block holds consecutive slots,
@@ -721,22 +737,6 @@ __device__ __forceinline__ void clean16(uint64_t& k, uint32_t& p, int lg) {
 //   4. Lane l of the group writes slots l and l + 16; slots k >= n repeat slot
 //      0. The center's pairwise sum runs strides 1..8 inside each half, then
 //      node 16 into node 0 -- the order of the single-register tree.
-// Adds to `r` how many of the row's 16 lanes hold a `k` below `mine`.
-template <int G, int J>
-__device__ __forceinline__ void count_below(uint32_t k, uint32_t mine, uint32_t& r) {
-    if constexpr (J < G) {
-        r += row_lane<J>(k) < mine ? 1u : 0u;
-        count_below<G, J + 1>(k, mine, r);
-    }
-}
-
-template <int N>
-__device__ __forceinline__ uint64_t row_shr64(uint64_t v) {
-    return ((uint64_t)dpp_row_shr<N>((uint32_t)(v >> 32)) << 32) | dpp_row_shr<N>((uint32_t)v);
-}
-
-constexpr int32_t kRankMin = 8192;  // centers of a launch above which k_query_r2 ranks a block's centers
-
 template <int MODE, int RAD, bool UP>
 __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
     const uint32_t* __restrict__ Wt, int32_t N, int32_t M, int32_t K, int32_t total, QGrid g,
@@ -1200,21 +1200,26 @@ void launch_r2(const Layout& L, const QGrid& g, void* ws, const QueryIO& io, int
 template <int MODE, bool UP>
 void launch_mode(const Layout& L, const QGrid& g, int32_t rad, int32_t n_v, void* ws, const QueryIO& io, int32_t M,
                  int32_t K, uint64_t seed, hipStream_t s) {
-    if (MODE != kRing && K <= 32) {
-        // 16 lanes per center
-        if (rad == 1)
-            launch_r2<MODE, 1, UP>(L, g, ws, io, M, K, seed, n_v, s);
-        else if (rad == 2)
-            launch_r2<MODE, 2, UP>(L, g, ws, io, M, K, seed, n_v, s);
+    // K <= 32: 16 lanes per center, but for the ring queries, which keep a
+    // node per lane
+    if constexpr (MODE != kRing) {
+        if (K <= 32) {
+            if (rad == 1)
+                launch_r2<MODE, 1, UP>(L, g, ws, io, M, K, seed, n_v, s);
+            else if (rad == 2)
+                launch_r2<MODE, 2, UP>(L, g, ws, io, M, K, seed, n_v, s);
+            else
+                launch_r2<MODE, 3, UP>(L, g, ws, io, M, K, seed, n_v, s);
+            return;
+        }
+    } else if (K <= 32) {
+        if (K <= 16)
+            launch_r<MODE, 16, UP>(L, g, rad, ws, io, M, K, seed, s);
         else
-            launch_r2<MODE, 3, UP>(L, g, ws, io, M, K, seed, n_v, s);
+            launch_r<MODE, 32, UP>(L, g, rad, ws, io, M, K, seed, s);
         return;
     }
-    if (K <= 16)
-        launch_r<MODE, 16, UP>(L, g, rad, ws, io, M, K, seed, s);
-    else if (K <= 32)
-        launch_r<MODE, 32, UP>(L, g, rad, ws, io, M, K, seed, s);
-    else if (K <= 64)
+    if (K <= 64)
         launch_r<MODE, 64, UP>(L, g, rad, ws, io, M, K, seed, s);
     else
         launch_r<MODE, 64, UP, 2>(L, g, rad, ws, io, M, K, seed, s);
