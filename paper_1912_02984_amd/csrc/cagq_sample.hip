@@ -443,9 +443,14 @@ __global__ __launch_bounds__(T) void k_sel_one(int32_t N, const int32_t* __restr
         const bool lt = (blt[u] >> lane) & 1ull, eq = (beq[u] >> lane) & 1ull;
         if (lt || (eq && neq < need)) {
             const uint32_t pos = nlt + (neq < need ? neq : need);
-            for (int64_t j = (int64_t)pos; j < M; j += m) out[j] = (int32_t)ln[u];
+            out[pos] = (int32_t)ln[u];
         }
     }
+    if (m == M) return;
+    // the padding repeats the m chosen (by the whole workgroup: few occupied
+    // voxels would leave it to few lanes)
+    __syncthreads();
+    for (int32_t j = m + tid; j < M; j += T) out[j] = out[j % m];
 }
 
 // ---- many-block selection (large clouds): two launches.
