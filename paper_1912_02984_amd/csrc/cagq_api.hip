@@ -113,7 +113,7 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->berr = take(4 * (size_t)B);
     L->sel_ghist = take(4 * (size_t)B * kSelBins);
     L->sel_cnt = take(4 * (size_t)B);
-    L->ctx_tiles = ((int64_t)BN + kScanThreads - 1) / kScanThreads;
+    L->ctx_tiles = ((int64_t)BN + kScanThreads - 1) / kScanThreads + kCtxTiles;
     L->ctx_desc = take(8 * (size_t)L->ctx_tiles);
     L->clear_small = off;
     L->desc_h = take(8 * ((BQ + 63) / 64));

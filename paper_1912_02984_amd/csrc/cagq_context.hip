@@ -52,8 +52,8 @@ struct CtxGrid {
     }
 };
 
-// A thread takes `items` centers in a row (one, unless M > N: the tile
-// descriptors are one per kScanThreads points), whose rows' loads go out
+// A thread takes `items` centers in a row (one, unless there are more
+// than the points' and kCtxTiles tiles' descriptors hold), whose rows' loads go out
 // together. The descriptors, the ticket and the count of tiles that have
 // finished their look-back start at zero: every build clears them, and the
 // last tile to finish clears them again for the next call, so that the call is
@@ -223,9 +223,9 @@ hipError_t launch_context_offsets(const Layout& L, const cagq_grid_desc& d, void
                                   int32_t M, int64_t* ctx_off, hipStream_t s) {
     const CtxGrid g(d, M);
     const int64_t total = (int64_t)L.B * M;
-    const int64_t items = ((int64_t)M + L.N - 1) / L.N;
+    const int64_t items = (total + L.ctx_tiles * kScanThreads - 1) / (L.ctx_tiles * kScanThreads);
     const int64_t tiles = (total + items * kScanThreads - 1) / (items * kScanThreads);
-    if (tiles > L.ctx_tiles) return hipErrorInvalidValue;  // unreachable: M <= items * N
+    if (tiles > L.ctx_tiles) return hipErrorInvalidValue;  // unreachable by the choice of items
     auto go = [&](auto kern) {
         kern<<<(unsigned)tiles, kScanThreads, 0, s>>>(L.N, M, total, (int32_t)items, L.W, g,
                                                       at<uint64_t>(ws, L.bitmap), at<uint32_t>(ws, L.word_rank),

@@ -108,8 +108,8 @@ def test_cas_past_full_coverage(N, radius):
 def test_context_offsets_again_and_again(N, dims, radius):
     """The context lists of several sets of centers of one grid, call after
     call (each leaves the scan's state ready for the next): one center, tiles
-    just full, one more, and more centers than points (several a thread); on
-    grids of all three builds, some centers empty or repeated."""
+    just full, one more, more centers than points, and many more (several a
+    thread); on grids of all three builds, some centers empty or repeated."""
     rng = np.random.default_rng(N + radius)
     B, V = 2, dims[0] * dims[1] * dims[2]
     lin = rng.integers(0, min(V, 4 * N), (B, N))
@@ -117,7 +117,8 @@ def test_context_offsets_again_and_again(N, dims, radius):
     spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 5, radius)
     ot = oracle.Table(P, oracle.grid_from_spec(spec))
     g = cagq.build_grid(torch.from_numpy(P).to("cuda:0"), cagq.desc_from_spec(spec))
-    for M in (1, 128, 129, 256, 500, N, N + 1, 3 * N + 5):
+    many = (140000,) if N == 700 and radius == 1 else ()
+    for M in (1, 128, 129, 256, 500, N, N + 1, 3 * N + 5, *many, 300):
         cl = np.where(rng.random((B, M)) < 0.8, lin[:, rng.integers(0, N, M)], rng.integers(0, V, (B, M)))
         cl = cl.astype(np.int32)
         off_o, list_o = ot.context_list(cl)
