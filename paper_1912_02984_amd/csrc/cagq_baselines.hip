@@ -377,8 +377,8 @@ __global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restric
     }
 }
 
-// Larger clouds: every thread keeps PER distances in registers, and every
-// pick reads the cloud again.
+// Larger and smaller clouds, and few picks: every thread keeps PER distances
+// in registers, and every pick reads the cloud again.
 template <int PER>
 __global__ __launch_bounds__(kSelThreads) void k_fps(const float* __restrict__ points, int32_t N, int32_t M,
                                                      int32_t* __restrict__ center_idx) {
@@ -538,6 +538,13 @@ __global__ __launch_bounds__(1024) void k_cov_count(int32_t N, const int32_t* __
 
 }  // namespace
 
+// Picks and points from which k_fps_runs is used: its sort costs 15 to 30 us,
+// and a pick over up to 2048 points gains nothing from it. 4 clouds of 12000
+// points, 32 picks: 80 us by k_fps, 91 by k_fps_runs; 48 picks 118 and 117;
+// 2048 points, 128 picks: 123 and 125; 4096 points: 170 and 141.
+constexpr int32_t kRunsMinN = 2049;
+constexpr int32_t kRunsMinM = 48;
+
 hipError_t launch_sample_points(const float* points, int32_t B, int32_t N, int32_t M, int32_t mode, uint64_t seed,
                                 int32_t* center_idx, hipStream_t s) {
     if (mode == 0) {
@@ -545,16 +552,18 @@ hipError_t launch_sample_points(const float* points, int32_t B, int32_t N, int32
     } else {
         const int32_t per = (N + kSelThreads - 1) / kSelThreads;
         // points in registers, sorted into runs, up to 16384 of them (the
-        // most a workgroup's registers hold); the fewest waves (a power of
-        // two, which divides the sort's cells) for up to 4096
-        int waves = 1;
-        while (waves < kSelThreads / kWave && waves * 4 * kWave < N) waves *= 2;
-        if (per <= 4)
-            k_fps_runs<4><<<B, waves * kWave, 0, s>>>(points, N, M, center_idx);
-        else if (per <= 8)
+        // most a workgroup's registers hold)
+        const bool runs = per <= 16 && N >= kRunsMinN && M >= kRunsMinM;
+        if (runs && per <= 4)
+            k_fps_runs<4><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
+        else if (runs && per <= 8)
             k_fps_runs<8><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
-        else if (per <= 16)
+        else if (runs)
             k_fps_runs<16><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
+        else if (per <= 4)
+            k_fps<4><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
+        else if (per <= 16)
+            k_fps<16><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
         else if (per <= 40)
             k_fps<40><<<B, kSelThreads, 0, s>>>(points, N, M, center_idx);
         else

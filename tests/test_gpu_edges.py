@@ -44,10 +44,11 @@ def test_brick_sizes(words, depth, order):
 
 
 @pytest.mark.parametrize("N,M", [(1, 1), (64, 64), (255, 40), (256, 256), (257, 60), (1025, 300), (4096, 200),
-                                 (4097, 200), (8192, 300), (8193, 100), (16384, 100), (16385, 20)])
+                                 (4097, 200), (8192, 300), (8193, 100), (16384, 100), (16385, 20), (2048, 60),
+                                 (2049, 60), (2500, 47), (9000, 47), (9000, 48)])
 def test_fps_sizes(N, M):
-    """Farthest Point Sampling where its workgroup and its points per lane
-    change: a spread cloud, one of many equal points (ties go to the lowest
+    """Farthest Point Sampling where its kernel and its points per lane change
+    (with the points and with the picks): a spread cloud, one of many equal points (ties go to the lowest
     index, at last with every distance 0), a flat one, and one with points
     that are not finite, which stay infinitely far."""
     rng = np.random.default_rng(N)
