@@ -325,18 +325,24 @@ __device__ __forceinline__ uint32_t wave_sort32(uint32_t v) {
     return v;
 }
 
+// The half-cleaners at distances J, J / 2, ..., 1: sorts a bitonic sequence.
+// A recursion over the distance, which the lane exchanges need at compile
+// time: as a loop inside its callers' loops the compiler kept it rolled, with a
+// choice between the exchanges' forms at every step.
+template <int J>
+__device__ __forceinline__ uint32_t wave_clean32(uint32_t v, int lane) {
+    const uint32_t o = xlane(v, J);
+    v = (lane & J) == 0 ? (o < v ? o : v) : (o < v ? v : o);
+    if constexpr (J > 1) v = wave_clean32<J / 2>(v, lane);
+    return v;
+}
+
 // `best` and `add` each sorted ascending over the wave: returns the 64
 // smallest keys of their union, sorted ascending.
 __device__ __forceinline__ uint32_t wave_merge_low32(uint32_t best, uint32_t add) {
     const int lane = lane_id();
     const uint32_t rev = (uint32_t)__shfl((int)add, kWave - 1 - lane, kWave);
-    uint32_t v = rev < best ? rev : best;  // bitonic: the 64 smallest of the union
-#pragma unroll
-    for (int j = kWave >> 1; j > 0; j >>= 1) {
-        const uint32_t o = xlane(v, j);
-        v = (lane & j) == 0 ? (o < v ? o : v) : (o < v ? v : o);
-    }
-    return v;
+    return wave_clean32<kWave / 2>(rev < best ? rev : best, lane);  // bitonic: the 64 smallest of the union
 }
 
 // Agent-scope atomics for the cross-workgroup scan descriptors (the 8 XCDs
