@@ -715,6 +715,28 @@ __device__ __forceinline__ uint64_t row_shr64(uint64_t v) {
 
 constexpr int32_t kRankMin = 8192;  // centers of a launch above which k_query_r2 ranks a block's centers
 
+// Contexts of more than kDefer points go to one wave each, by a launch of their
+// own, when the grid can hold contexts of more than kBigGrid points ((2r+1)^3
+// n_v): a 16-lane group works through a long context chunk after chunk, one
+// load latency each. With K <= 16 only in clouds whose contexts are long at
+// large. A wave of 64 lanes sorts 64 keys at a time, about twice the work a
+// point of the 16-lane chunks with one result register, and its launch adds
+// 6 us for the first context it is given, so that a cloud whose contexts hold
+// up to ~400 points is faster done whole by the 16-lane kernel, and a mixed
+// one (each wave's or each context's own size as the rule) slower than either.
+// The rule is one for the launch: of 64 voxels, spread over the clouds and
+// over each cloud's, the stored points of a voxel as its points see it (sum of
+// squares over sum) times (2r+1)^3, against kLongCtx. Measured, K = 16 (every
+// context above kDefer deferred / none, as before K <= 16 took this kernel /
+// this rule): 4 x 1700 centers, k-NN, contexts of ~108 points (r = 1) 20.8 /
+// 13.9 / 13.5 us, ~125 (r = 2) 23.7 / 18.7 / 14.7, ~250 32.2 / 26.2 / 20.2, ~500
+// 36.8 / 41.7 / 35.7; 2^20-point sweep, cube, r = 2 78 / 260 / 77, r = 1 49 / 98 /
+// 46. What is left: contexts of ~27 points on a grid that could hold longer
+// ones, 9.5 / 8.6 / 9.5 us, the launch that finds nothing to do.
+constexpr uint32_t kDefer = 128;
+constexpr int64_t kBigGrid = 1024;
+constexpr uint32_t kLongCtx = 448;
+
 // K <= 32, Cube Query or k-NN: 16 lanes per center (four per wave).
 //   1. Each group probes the (2r+1)^2 grid rows of its center's block, one
 //      lane per row: a row segment of the block holds consecutive slots,
@@ -733,11 +755,13 @@ constexpr int32_t kRankMin = 8192;  // centers of a launch above which k_query_r
 //      later one is merged in: the 16 smallest of b1 and the chunk (elementwise
 //      minimum against the chunk reversed, then half-cleaners), then b0 and
 //      that merged the same way into the new b0 (smaller half) and b1 (larger
-//      half). Either way the nodes end up in LDS by slot.
+//      half); with K <= 16 b0 alone, with half the merge's work. Either way the
+//      nodes end up in LDS by slot.
 //   4. Lane l of the group writes slots l and l + 16; slots k >= n repeat slot
 //      0. The center's pairwise sum runs strides 1..8 inside each half, then
 //      node 16 into node 0 -- the order of the single-register tree.
-template <int MODE, int RAD, bool UP>
+// LOW: K <= 16, which needs b0 only; otherwise 16 < K <= 32.
+template <int MODE, int RAD, bool UP, bool LOW>
 __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
     const uint32_t* __restrict__ Wt, int32_t N, int32_t M, int32_t K, int32_t total, QGrid g,
     int64_t W, const uint64_t* __restrict__ bitmap, const uint32_t* __restrict__ word_rank,
@@ -745,7 +769,7 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
     const float* __restrict__ center_pts, uint64_t seed, int32_t* __restrict__ node_idx,
     float* __restrict__ node_xyz, int32_t* __restrict__ n_valid, float* __restrict__ center_xyz,
     uint32_t* __restrict__ center_w, int32_t* __restrict__ ctx_count, int32_t* __restrict__ lin_out,
-    int* __restrict__ status, uint32_t defer) {
+    int* __restrict__ status, uint32_t defer, int32_t B, const int32_t* __restrict__ nvox) {
     constexpr int G = 16, GPB = kQueryThreads / G;
     constexpr int S = 2 * RAD + 1, NR = S * S;
     __shared__ uint32_t s_st[GPB][NR];
@@ -760,6 +784,18 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
     const int lg = lane & (G - 1);
     const int gb = threadIdx.x / G;
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
+
+    // the stored points of the lane's sampled voxel (see kLongCtx): lanes
+    // spread over the clouds, and evenly over each cloud's voxels
+    const bool sampled = LOW && defer != ~0u;
+    uint32_t vc = 0;
+    if (sampled) {
+        const uint64_t at = (uint64_t)lane * (uint32_t)B;
+        const int32_t vb = (int32_t)(at >> 6);
+        const uint64_t part = (at + (uint64_t)vb * 29) & 63;  // of the cloud's voxels, in 64ths
+        const uint32_t* vo = vox_off + (size_t)vb * (N + 1) + ((part * (uint32_t)nvox[vb]) >> 6);
+        vc = vo[1] - vo[0];
+    }
 
     // 1. this group's own center
     {
@@ -834,7 +870,11 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
         }
         // a context above `defer` points is left to the one-wave-per-center
         // pass: here it counts as empty, and its n_valid is marked -1
-        const bool def = live && c > defer;
+        bool def = live && c > defer;
+        if (sampled) {
+            const uint32_t sum = wave_sum_u32(vc), sum2 = wave_sum_u32(vc * vc);
+            def = def && (uint32_t)(S * S * S) * sum2 > kLongCtx * sum;
+        }
         if (lg == 0) {
             s_pre[gb][NR] = c;
             s_def[gb] = def ? 1u : 0u;
@@ -1007,6 +1047,8 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
         if (e0 == 0) {
             b0k = key;
             b0p = pos;
+        } else if constexpr (LOW) {
+            gmerge_low<G>(b0k, b0p, key, pos, lg);
         } else {
             // the 16 smallest of b1 and the chunk
             uint64_t rk = mirror64(key);
@@ -1028,7 +1070,7 @@ __global__ __launch_bounds__(kQueryThreads) void k_query_r2(
             clean16(b1k, b1p, lg);
         }
         // the K-th best key so far, rank K-1 (~0 while fewer than K are held)
-        kth = K > G ? gshfl64<G>(b1k, K - 1 - G) : gshfl64<G>(b0k, K - 1);
+        kth = LOW ? gshfl64<G>(b0k, K - 1) : gshfl64<G>(b1k, K - 1 - G);
     }
     // the nodes' points, read again, to their slots
 #pragma unroll
@@ -1175,26 +1217,29 @@ void launch_r(const Layout& L, const QGrid& g, int32_t rad, void* ws, const Quer
         launch_g<MODE, G, 3, UP, NR>(L, g, ws, io, M, K, seed, s);
 }
 
-// Contexts of more points than this go to one wave each when the grid can
-// hold contexts of more than kBigGrid points ((2r+1)^3 n_v): a 16-lane group
-// works through a long context chunk after chunk, one load latency each.
-constexpr uint32_t kDefer = 128;
-constexpr int64_t kBigGrid = 1024;
-
-template <int MODE, int RAD, bool UP>
-void launch_r2(const Layout& L, const QGrid& g, void* ws, const QueryIO& io, int32_t M, int32_t K, uint64_t seed,
+template <int MODE, int RAD, bool UP, bool LOW>
+void launch_r2_k(const Layout& L, const QGrid& g, void* ws, const QueryIO& io, int32_t M, int32_t K, uint64_t seed,
                int32_t n_v, hipStream_t s) {
     constexpr int GPB = kQueryThreads / 16;
     const int32_t total = L.B * M;
     const unsigned blocks = (unsigned)((total + GPB - 1) / GPB);
     constexpr int64_t side = 2 * RAD + 1;
     const bool big = side * side * side * (int64_t)n_v > kBigGrid;
-    k_query_r2<MODE, RAD, UP><<<blocks, kQueryThreads, 0, s>>>(
+    k_query_r2<MODE, RAD, UP, LOW><<<blocks, kQueryThreads, 0, s>>>(
         io.weights, L.N, M, K, total, g, L.W, at<uint64_t>(ws, L.bitmap), at<uint32_t>(ws, L.word_rank),
         at<uint32_t>(ws, L.vox_off), at<float4>(ws, L.pt4), io.center_lin, io.center_pts, seed, io.node_idx,
         io.node_xyz, io.n_valid, io.center_xyz, io.center_w, io.ctx_count, io.lin_out, at<int>(ws, L.status),
-        big ? kDefer : 0xFFFFFFFFu);
+        big ? kDefer : 0xFFFFFFFFu, L.B, at<int32_t>(ws, L.nvox));
     if (big) launch_g<MODE, 64, RAD, UP, 1, true, 6>(L, g, ws, io, M, K, seed, s);
+}
+
+template <int MODE, int RAD, bool UP>
+void launch_r2(const Layout& L, const QGrid& g, void* ws, const QueryIO& io, int32_t M, int32_t K, uint64_t seed,
+               int32_t n_v, hipStream_t s) {
+    if (K <= 16)
+        launch_r2_k<MODE, RAD, UP, true>(L, g, ws, io, M, K, seed, n_v, s);
+    else
+        launch_r2_k<MODE, RAD, UP, false>(L, g, ws, io, M, K, seed, n_v, s);
 }
 
 template <int MODE, bool UP>

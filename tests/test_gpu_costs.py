@@ -1,0 +1,50 @@
+"""Calls whose cost must follow the work they do: each is timed against a like
+call on the same card, and the bound lies far from both the ratio expected and
+the one a wrong choice of kernel or path shows (stated at each test)."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1912_02984_amd import cagq
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _us(fn, calls=8):
+    """Time of a call in a captured graph of several, the least of seven replays."""
+    fn()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(calls):
+            fn()
+    best = float("inf")
+    for _ in range(8):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        g.replay()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / calls * 1e6)
+    return best
+
+
+@pytest.mark.parametrize("r,n_v,small", [(1, 64, 32), (2, 16, 8)])
+def test_low_k_query_of_contexts_around_128(r, n_v, small):
+    """K = 16, contexts of about 110 points, some above 128: a cap n_v that
+    would allow longer contexts changes no context here and must not send the
+    few above 128 to a launch of their own (1.5x and 1.6x when it did, 1.05 to
+    1.1x now)."""
+    side, per = 12, 4 if r == 1 else 1
+    rng = np.random.default_rng(1)
+    P = torch.from_numpy(rng.random((4, per * side ** 3, 3), dtype=np.float32)).to(DEV)
+    us = []
+    for cap in (small, n_v):
+        g = cagq.build_grid(P, cagq.make_desc((0,) * 3, (1.0 / side,) * 3, (side,) * 3, cap, r))
+        cl, _ = cagq.sample_centers(g, 1000, "rvs", 3)
+        out = cagq.alloc_query_outputs(4, 1000, 16, DEV)
+        us.append(_us(lambda: cagq.query_context(g, cl, 16, "knn", 3, out=out)))
+    assert us[1] < 1.3 * us[0], us

@@ -243,3 +243,42 @@ def test_larger_voxels(build, n_v):
     P = np.stack([_points_in(lin, dims, rng)[rng.permutation(N)], _points_in(np.sort(lin)[::-1].copy(), dims, rng)])
     spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, n_v, 2)
     run_both(P, spec, 200, 32, "rvs", "cube", 8, where=f"{build} n_v={n_v}")
+
+
+@pytest.mark.parametrize("K", [1, 8, 16])
+@pytest.mark.parametrize("case,r,n_v,deferred", [("dense corner", 2, 64, True), ("even, longer contexts", 1, 64, False),
+                                                 ("even, long contexts", 2, 16, True), ("70 clouds", 2, 32, True),
+                                                 ("70 thin clouds", 2, 32, False)])
+def test_low_k_long_contexts(case, r, n_v, deferred, K):
+    """K <= 16 on grids whose contexts may be long ((2r+1)^3 n_v > 1024): on
+    both sides of the rule that leaves contexts of more than 128 points to a
+    wave each (64 sampled voxels' points, over one cloud or more clouds than
+    lanes), with contexts below and above 128 in the same launch, weights, and
+    the upsampling query on the same grid."""
+    rng = np.random.default_rng(K + r)
+    if case.startswith("70"):
+        B, N, side = 70, 1200 if case == "70 clouds" else 500, 8
+        P = rng.random((B, N, 3), dtype=np.float32) ** (3 if case == "70 clouds" else 1)
+    else:
+        B, side = 2, 12
+        N = {"dense corner": 6000, "even, longer contexts": 4 * side ** 3, "even, long contexts": 8 * side ** 3}[case]
+        P = rng.random((B, N, 3), dtype=np.float32) ** (4 if case == "dense corner" else 1)
+    P = P.astype(np.float32)
+    spec = W.GridSpec((0.0,) * 3, (1.0 / side,) * 3, (side,) * 3, n_v, r)
+    ot = oracle.Table(P, oracle.grid_from_spec(spec))
+    # the rule: the sampled voxels' mean points, weighted by their points
+    at = np.arange(64) * B
+    slot = (at + at // 64 * 29) % 64 * np.asarray(ot.nvox, np.int64)[at // 64] // 64
+    cnt = np.array([int(ot.vox_off[b, s + 1]) - int(ot.vox_off[b, s]) for b, s in zip(at // 64, slot)])
+    assert ((2 * r + 1) ** 3 * (cnt ** 2).sum() > 448 * cnt.sum()) == deferred
+    wts = rng.integers(1, 50, (B, N)).astype(np.uint32)
+    for q in ("knn", "cube"):
+        qo = run_both(P, spec, 160, K, "rvs", q, 3, weights=wts, where=f"{case} K={K} {q}")
+        assert qo["ctx_count"].max() > 128
+        assert qo["ctx_count"].min() < 128 or case == "even, long contexts"  # there every context is deferred
+        g = cagq.build_grid(torch.from_numpy(P).to("cuda:0"), cagq.desc_from_spec(spec))
+        C = np.ascontiguousarray(P[:, :150] + np.float32(0.01))
+        a = cagq.query_points(g, torch.from_numpy(C).to("cuda:0"), K, q, 5)
+        b = ot.query_points(C, K, q, 5)
+        for name in ("ctx_count", "n_valid", "node_idx"):
+            assert np.array_equal(a[name].cpu().numpy(), b[name]), (case, K, q, name)
