@@ -140,7 +140,7 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->htot = take(4 * H * bv);
     L->hso = take(4 * H * bv);
     L->sorted = take(L->bricks ? 16 * BN : 0);
-    L->svox = take(L->bricks ? 2 * BN : 0);
+    L->svox = take(L->bricks && N > (1 << kPackBits) ? 2 * BN : 0);
     L->full_off = take(L->bricks ? 0 : 4 * (size_t)B * (N + 1));
     L->bucket = take(L->bricks ? 0 : 4 * BN);
     L->pt4 = take(16 * BN);

@@ -416,6 +416,8 @@ struct BrickLists {
     BrickItem* item;
     uint32_t* hfirst;  // per heavy brick: the count row of its first part
     uint32_t* hparts;  //                  its parts
+    uint32_t* pcnt;    // the count rows, nvx (voxels per brick) entries each
+    uint32_t nvx;
     int* status;
 };
 
@@ -439,34 +441,40 @@ __device__ __forceinline__ void list_big(const BrickLists& o, bool valid, uint32
         if (one) o.item[base + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1))] = BrickItem{g, start, tot - 1, -1};
     }
     if (!valid || tot <= (uint32_t)kBrickCap) return;
-    // calls f(part, first position, points) for each part
-    auto walk = [&](auto f) {
-        constexpr int kU = 32;  // column entries in flight
-        uint32_t part = 0, p0 = start, acc = 0;
-        for (int32_t t0 = tf; t0 <= tl; t0 += kU) {
-            uint32_t x[kU];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) x[u] = hist[(size_t)(t0 + u <= tl ? t0 + u : tl) * BQ + g];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const uint32_t v = t0 + u <= tl ? x[u] : 0u;
-                if (acc + v > (uint32_t)kBrickCap) {
-                    f(part++, p0, acc);
-                    p0 += acc;
-                    acc = 0;
-                }
-                acc += v;
-            }
-        }
-        f(part++, p0, acc);
-        return part;
-    };
-    const uint32_t parts = walk([](uint32_t, uint32_t, uint32_t) {});
+    // count rows for as many parts as there can be (two in a row hold more than
+    // kBrickCap points), which keep the parts until their number is known, so
+    // that one walk over the column lists them
     const int32_t hb = atomicAdd(&o.status[kStHeavy], 1);
+    const uint32_t row = (uint32_t)atomicAdd(&o.status[kStRows], (int)(2ull * tot / kBrickCap) + 1);
+    uint32_t* keep = o.pcnt + (size_t)row * o.nvx;
+    constexpr int kU = 16;  // column entries in flight
+    uint32_t parts = 0, p0 = start, acc = 0;
+    auto put = [&]() {
+        keep[(size_t)parts * o.nvx] = p0;
+        keep[(size_t)parts * o.nvx + 1] = acc;
+        ++parts;
+    };
+    for (int32_t t0 = tf; t0 <= tl; t0 += kU) {
+        uint32_t x[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) x[u] = hist[(size_t)(t0 + u <= tl ? t0 + u : tl) * BQ + g];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint32_t v = t0 + u <= tl ? x[u] : 0u;
+            if (acc + v > (uint32_t)kBrickCap) {
+                put();
+                p0 += acc;
+                acc = 0;
+            }
+            acc += v;
+        }
+    }
+    put();
     const uint32_t e = (uint32_t)atomicAdd(&o.status[kStItems], (int)parts);
-    o.hfirst[hb] = (uint32_t)atomicAdd(&o.status[kStRows], (int)parts);
+    o.hfirst[hb] = row;
     o.hparts[hb] = parts;
-    walk([&](uint32_t part, uint32_t p0, uint32_t n) { o.item[e + part] = BrickItem{g, p0, (part << 12) | (n - 1), hb}; });
+    for (uint32_t i = 0; i < parts; ++i)
+        o.item[e + i] = BrickItem{g, keep[(size_t)i * o.nvx], (i << 12) | (keep[(size_t)i * o.nvx + 1] - 1), hb};
 }
 
 // Sorted positions and work items: bstart[g] = points of the bricks before g
@@ -561,64 +569,109 @@ __device__ __forceinline__ uint32_t sort_excl_scan(uint32_t v, uint32_t* s_wave,
     return off + incl - v;
 }
 
+// Column sums of the histogram for brick `col` over the tiles [tf, tl]: the
+// brick's points (tot) and those in the tiles before t (pre), kU loads in
+// flight per thread.
+template <int kU>
+__device__ __forceinline__ void brick_column(const uint32_t* __restrict__ hist, int32_t BQ, size_t col, int32_t tf,
+                                             int32_t tl, int32_t t, uint32_t& tot, uint32_t& pre) {
+    tot = pre = 0;
+    for (int32_t t0 = tf; t0 <= tl; t0 += kU) {
+        uint32_t x[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) x[u] = hist[(size_t)(t0 + u <= tl ? t0 + u : tl) * BQ + col];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint32_t v = t0 + u <= tl ? x[u] : 0u;
+            tot += v;
+            pre += t0 + u < t ? v : 0u;
+        }
+    }
+}
+
 // The first sorted position of tile t's points in each brick of the clouds
 // it holds points of, into s_o (indexed by brick): per brick, the column of
 // the histogram over the cloud's tiles gives the points of the tiles before
 // t and the brick's total, and an exclusive scan of the totals over the
 // cloud's bricks (clouds hold N sorted positions each) gives the brick's
-// first position. The cloud's first tile also writes those (bstart) and
-// lists the bricks of more than kWavePts points.
+// first position.
 __device__ __forceinline__ void tile_columns(int32_t t, int32_t N, int32_t BN, int32_t Q, int32_t BQ,
-                                             const uint32_t* __restrict__ hist, uint32_t* s_o, uint32_t* s_wave,
-                                             uint32_t* __restrict__ bstart, const BrickLists& lists) {
-    constexpr int kU = 32;  // column loads in flight per thread (a cloud of up to 126976 points: all of them)
-    const int tid = threadIdx.x;
+                                             const uint32_t* __restrict__ hist, uint32_t* s_o, uint32_t* s_wave) {
     const int32_t p0 = t * kSortTile, p1 = p0 + kSortTile < BN ? p0 + kSortTile : BN;
     for (int32_t b = p0 / N; b <= (p1 - 1) / N; ++b) {
         const int32_t tf = (int32_t)((int64_t)b * N / kSortTile);
         const int32_t tl = (int32_t)((((int64_t)b + 1) * N - 1) / kSortTile);
         uint32_t carry = (uint32_t)b * (uint32_t)N;
         for (int32_t q0 = 0; q0 < Q; q0 += kSortT) {
-            const int32_t q = q0 + tid;
-            const size_t col = (size_t)b * Q + (q < Q ? q : 0);
-            uint32_t pre = 0, tot = 0;
-            for (int32_t t0 = tf; t0 <= tl; t0 += kU) {
-                uint32_t x[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u) x[u] = hist[(size_t)(t0 + u <= tl ? t0 + u : tl) * BQ + col];
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    const uint32_t v = t0 + u <= tl ? x[u] : 0u;
-                    tot += v;
-                    pre += t0 + u < t ? v : 0u;
-                }
-            }
+            const int32_t q = q0 + (int32_t)threadIdx.x;
+            uint32_t tot, pre;
+            // (32: all of a cloud's, up to 126976 points)
+            brick_column<32>(hist, BQ, (size_t)b * Q + (q < Q ? q : 0), tf, tl, t, tot, pre);
             if (q >= Q) tot = 0;
             uint32_t sum;
             const uint32_t start = carry + sort_excl_scan(tot, s_wave, &sum);
             carry += sum;
-            const int32_t gg = b * Q + q;
-            if (q < Q) s_o[gg] = start + pre;
-            if (t != tf) continue;  // the same for the whole block
-            if (q < Q) bstart[gg] = start;
-            list_big(lists, q < Q, (uint32_t)gg, start, tot, hist, BQ, tf, tl);
+            if (q < Q) s_o[b * Q + q] = start + pre;
         }
     }
 }
 
-// One lane per point: (x, y, z, index), and its voxel within the brick, at the
-// next free position of its brick within the tile's range. With SCAN the tile finds its ranges from
-// the histogram columns itself (tile_columns); otherwise k_hscan has
-// rewritten row t of the histogram into them.
+// Cloud b's bricks: their first sorted positions (bstart), and the list of
+// those of more than kWavePts points. It runs beside the tiles' blocks and ends
+// before them; with 16 column loads in flight, not the tiles' 32, it fits in
+// their registers.
+__device__ __forceinline__ void cloud_columns(int32_t b, int32_t N, int32_t Q, int32_t BQ,
+                                              const uint32_t* __restrict__ hist, uint32_t* s_wave,
+                                              uint32_t* __restrict__ bstart, const BrickLists& lists) {
+    const int32_t tf = (int32_t)((int64_t)b * N / kSortTile);
+    const int32_t tl = (int32_t)((((int64_t)b + 1) * N - 1) / kSortTile);
+    uint32_t carry = (uint32_t)b * (uint32_t)N;
+    for (int32_t q0 = 0; q0 < Q; q0 += kSortT) {
+        const int32_t q = q0 + (int32_t)threadIdx.x, gg = b * Q + q;
+        uint32_t tot, pre;
+        brick_column<16>(hist, BQ, (size_t)b * Q + (q < Q ? q : 0), tf, tl, tf, tot, pre);
+        if (q >= Q) tot = 0;
+        uint32_t sum;
+        const uint32_t start = carry + sort_excl_scan(tot, s_wave, &sum);
+        carry += sum;
+        if (q < Q) bstart[gg] = start;
+        list_big(lists, q < Q, (uint32_t)gg, start, tot, hist, BQ, tf, tl);
+    }
+}
+
+// A sorted point's index and its voxel within the brick: both in one word for
+// clouds of at most kPackN points (svox null), else the voxel in svox.
+constexpr int32_t kPackN = 1 << kPackBits;
+static_assert(kBrickV <= 1 << (32 - kPackBits), "a voxel fits beside the index");
+
+// One lane per point: (x, y, z, index and voxel within the brick) at the next
+// free position of its brick within the tile's range. With SCAN the tile finds its ranges from the
+// histogram columns itself (tile_columns), and one more block per cloud, before
+// the tiles', writes the bricks' starts and lists the larger ones
+// (cloud_columns); otherwise k_hscan has done so and rewritten row t of the
+// histogram into the ranges. Bound by the tile's chain of columns, scan, LDS
+// atomics and stores. With the listing in each cloud's first tile and a second
+// store per point (its voxel) the launch took 10.2 us for one cloud of 20000
+// points, 11.4 for two of 81920 and 55.5 for one of 2^20, now 8.7, 9.7 and 43;
+// either alone cost nearly as much as both. Computing the voxels again in the
+// passes over the bricks instead costs those 1 to 6 us more.
 template <bool SCAN>
 __global__ __launch_bounds__(kSortT) void k_bscatter(const float* __restrict__ P, int32_t N, int32_t BN, GridArgs g,
-                                                     int32_t Q, int32_t BQ, int32_t vshift, const uint32_t* __restrict__ hist,
+                                                     int32_t Q, int32_t BQ, int32_t vshift, int32_t clouds,
+                                                     const uint32_t* __restrict__ hist,
                                                      float4* __restrict__ sorted, uint16_t* __restrict__ svox,
-                                                     uint32_t* __restrict__ bstart, BrickLists lists, int* __restrict__ status) {
+                                                     uint32_t* __restrict__ bstart, BrickLists lists,
+                                                     int* __restrict__ status) {
     __shared__ uint32_t s_o[kMaxBricks];
     __shared__ uint32_t s_wave[kSortT / kWave];
     const int tid = threadIdx.x;
-    const int32_t t = (int32_t)blockIdx.x;
+    const int32_t t = (int32_t)blockIdx.x - clouds;
+    if constexpr (SCAN) {
+        if (__builtin_expect(t < 0, 0)) {
+            cloud_columns((int32_t)blockIdx.x, N, Q, BQ, hist, s_wave, bstart, lists);
+            return;
+        }
+    }
     // the points' coordinates first, all loads in flight together
     float c[kSortIPT][3];
 #pragma unroll
@@ -629,7 +682,7 @@ __global__ __launch_bounds__(kSortT) void k_bscatter(const float* __restrict__ P
         for (int a = 0; a < 3; ++a) c[k][a] = p[a];
     }
     if constexpr (SCAN) {
-        tile_columns(t, N, BN, Q, BQ, hist, s_o, s_wave, bstart, lists);
+        tile_columns(t, N, BN, Q, BQ, hist, s_o, s_wave);
     } else {
         const uint32_t* row = hist + (size_t)t * BQ;
         for (int32_t i = tid; i < BQ; i += kSortT) s_o[i] = row[i];
@@ -644,8 +697,9 @@ __global__ __launch_bounds__(kSortT) void k_bscatter(const float* __restrict__ P
         const uint32_t lin = voxel_lin(x, y, z, g, bad);
         const int32_t b = gid / N;
         const uint32_t pos = atomicAdd(&s_o[b * Q + (int32_t)(lin >> vshift)], 1u);
-        sorted[pos] = make_float4(x, y, z, __uint_as_float((uint32_t)(gid - b * N)));
-        svox[pos] = (uint16_t)(lin & ((1u << vshift) - 1));
+        const uint32_t v = lin & ((1u << vshift) - 1), i = (uint32_t)(gid - b * N);
+        sorted[pos] = make_float4(x, y, z, __uint_as_float(svox ? i : i | v << kPackBits));
+        if (svox) svox[pos] = (uint16_t)v;
     }
     if (bad) raise_error(status, CAGQ_ERR_NONFINITE_INPUT);
 }
@@ -663,7 +717,7 @@ struct BrickArgs {
     const uint32_t* hfirst;
     const uint32_t* hparts;
     const float4* sorted;
-    const uint16_t* svox;
+    const uint16_t* svox;  // null: packed with the points' indices
     uint64_t* bitmap;
     uint32_t* word_rank;
     uint32_t* vox_lin;
@@ -757,18 +811,28 @@ __device__ __forceinline__ Brick brick_at(const BrickArgs& a, int32_t g) {
 template <int IPT>
 __device__ __forceinline__ void brick_voxels(const BrickArgs& a, uint32_t p0, uint32_t n, uint32_t first,
                                              uint32_t stride, uint32_t (&v)[IPT]) {
+    if (a.svox) {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) {
+            const uint32_t i = first + j * stride;
+            v[j] = a.svox[p0 + (i < n ? i : 0u)];
+        }
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
         const uint32_t i = first + j * stride;
-        v[j] = a.svox[p0 + (i < n ? i : 0u)];
+        v[j] = __float_as_uint(a.sorted[p0 + (i < n ? i : 0u)].w);
     }
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) v[j] >>= kPackBits;
 }
 
-// The points themselves, in the same way.
+// The points and their voxels, in the same way.
 template <int IPT>
 __device__ __forceinline__ void brick_points(const BrickArgs& a, uint32_t p0, uint32_t n, uint32_t first,
                                              uint32_t stride, float (&x)[IPT], float (&y)[IPT], float (&z)[IPT],
-                                             uint32_t (&idx)[IPT]) {
+                                             uint32_t (&idx)[IPT], uint32_t (&v)[IPT]) {
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
         const uint32_t i = first + j * stride;
@@ -777,6 +841,15 @@ __device__ __forceinline__ void brick_points(const BrickArgs& a, uint32_t p0, ui
         y[j] = e.y;
         z[j] = e.z;
         idx[j] = __float_as_uint(e.w);
+    }
+    if (a.svox) {
+        brick_voxels<IPT>(a, p0, n, first, stride, v);
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+        v[j] = idx[j] >> kPackBits;
+        idx[j] &= (uint32_t)kPackN - 1;
     }
 }
 
@@ -977,8 +1050,7 @@ __device__ __forceinline__ void brick_by_wave(const BrickArgs& a, WaveLists& s, 
     uint32_t v[kWaveIPT], idx[kWaveIPT];
     float x[kWaveIPT], y[kWaveIPT], z[kWaveIPT];
     if (k.cnt) {
-        brick_voxels<kWaveIPT>(a, k.start, k.cnt, (uint32_t)lane, kWave, v);
-        brick_points<kWaveIPT>(a, k.start, k.cnt, (uint32_t)lane, kWave, x, y, z, idx);
+        brick_points<kWaveIPT>(a, k.start, k.cnt, (uint32_t)lane, kWave, x, y, z, idx, v);
     }
     const uint32_t wr = brick_put_words(s.w, word);
     if (lane < nw && (int64_t)k.q * nw + lane < a.W)
@@ -1075,8 +1147,7 @@ __device__ __forceinline__ void brick_by_block(const BrickArgs& a, BlockLists& s
     // the points' loads go out first
     uint32_t v[kBrickIPT], idx[kBrickIPT];
     float x[kBrickIPT], y[kBrickIPT], z[kBrickIPT];
-    brick_voxels<kBrickIPT>(a, p.p0, p.n, (uint32_t)tid, kBrickT, v);
-    brick_points<kBrickIPT>(a, p.p0, p.n, (uint32_t)tid, kBrickT, x, y, z, idx);
+    brick_points<kBrickIPT>(a, p.p0, p.n, (uint32_t)tid, kBrickT, x, y, z, idx, v);
     if (wv == 0) {
         const uint32_t wr = brick_put_words(s.w, word);
         if (p.part == 0 && lane < nw && (int64_t)k.q * nw + lane < a.W)
@@ -1515,15 +1586,17 @@ hipError_t launch_build(const float* points, const Layout& L, const cagq_grid_de
         uint32_t* hist = at<uint32_t>(ws, L.hist);
         int* status_w = at<int>(ws, L.status);
         const BrickLists lists{at<BrickItem>(ws, L.item), at<uint32_t>(ws, L.hfirst), at<uint32_t>(ws, L.hparts),
-                               status_w};
+                               at<uint32_t>(ws, L.pcnt), 64u << L.wshift, status_w};
         k_bhist<<<(unsigned)L.T, kSortT, 0, s>>>(points, N, BN, g, L.Q, BQ, L.wshift + 6, L.T, L.tile_scan, hist,
                                                  at<uint4>(ws, L.status), (int64_t)(L.clear_brick - L.status) / 16);
         if (!L.tile_scan)
             k_hscan<<<(unsigned)((BQ + kHGroup - 1) / kHGroup), kScanThreads, 0, s>>>(
                 hist, N, L.Q, BQ, L.T, at<uint32_t>(ws, L.bstart), lists, at<uint64_t>(ws, L.desc_h), status_w);
-        (L.tile_scan ? k_bscatter<true> : k_bscatter<false>)<<<(unsigned)L.T, kSortT, 0, s>>>(
-            points, N, BN, g, L.Q, BQ, L.wshift + 6, hist, at<float4>(ws, L.sorted), at<uint16_t>(ws, L.svox), at<uint32_t>(ws, L.bstart),
-            lists, status_w);
+        uint16_t* svox = N <= kPackN ? nullptr : at<uint16_t>(ws, L.svox);
+        const int32_t clouds = L.tile_scan ? B : 0;  // blocks before the tiles' (see k_bscatter)
+        (L.tile_scan ? k_bscatter<true> : k_bscatter<false>)<<<(unsigned)(L.T + clouds), kSortT, 0, s>>>(
+            points, N, BN, g, L.Q, BQ, L.wshift + 6, clouds, hist, at<float4>(ws, L.sorted), svox,
+            at<uint32_t>(ws, L.bstart), lists, status_w);
         BrickArgs a;
         a.P = points;
         a.N = N;
@@ -1540,7 +1613,7 @@ hipError_t launch_build(const float* points, const Layout& L, const cagq_grid_de
         a.hfirst = lists.hfirst;
         a.hparts = lists.hparts;
         a.sorted = at<float4>(ws, L.sorted);
-        a.svox = at<uint16_t>(ws, L.svox);
+        a.svox = svox;
         a.bitmap = at<uint64_t>(ws, L.bitmap);
         a.word_rank = at<uint32_t>(ws, L.word_rank);
         a.vox_lin = at<uint32_t>(ws, L.vox_lin);

@@ -28,6 +28,7 @@ constexpr int kSelChunk = 4096;         // slots per chunk of the many-block sel
 constexpr int kBrickW = 32;             // most occupancy words per brick of the brick build
 constexpr int kBrickV = kBrickW * 64;   // most voxels per brick (a run of consecutive linear ids)
 constexpr int kMinBrickW = 4;           // fewest words per brick
+constexpr int kPackBits = 21;           // bits of a sorted point's index; the other 11 hold its voxel in the brick
 constexpr int32_t kMaxBricks = 8192;    // bricks over the batch the brick build's histograms hold
 constexpr int kSortTile = 4096;         // points per tile of the brick histogram and scatter
 constexpr int kBrickT = 512;            // threads of a block of the brick passes
@@ -101,8 +102,9 @@ struct Layout {
     size_t hdone;         // u32 [heavy_max] parts of each heavy brick that have counted their points
     size_t htot;          // u32 [heavy_max][voxels per brick] their points per voxel
     size_t hso;           // u32 [heavy_max][voxels per brick] exclusive prefix of min(points, n_v)
-    size_t sorted;        // float4 [B*N] x, y, z, bits(index) grouped by brick
-    size_t svox;          // u16 [B*N] their voxels within the brick
+    size_t sorted;        // float4 [B*N] x, y, z, bits(index) grouped by brick; with at most 2^kPackBits points a
+                          // cloud the index's upper bits hold the voxel within the brick
+    size_t svox;          // u16 [B*N] their voxels within the brick (larger clouds only)
     size_t full_off;      // u32 [B][N+1] exclusive prefix of the full counts
     size_t bucket;        // u32 [B][N] every point index grouped by slot (arrival order; not with bricks)
     size_t pt4;           // float4 [B][N] stored points grouped by slot: x, y, z, bits(index)

@@ -7,7 +7,7 @@ import torch
 import oracle
 from paper_1912_02984_amd import cagq
 from paper_1912_02984_amd import workloads as W
-from tests.test_gpu_parity import run_both
+from tests.test_gpu_parity import assert_table, run_both
 
 pytestmark = pytest.mark.gpu
 
@@ -41,6 +41,31 @@ def test_brick_sizes(words, depth, order):
     for n_v in (1, 64):
         spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, n_v, 1)
         run_both(P, spec, 500, 32, "rvs", "knn", 3, where=f"words={words} n_v={n_v} {order}")
+
+
+@pytest.mark.parametrize("N,side,scan", [(1 << 21, 48, True), ((1 << 21) + 1, 48, True), ((1 << 21) + 1, 64, False),
+                                         (9000, 48, True), (300000, 48, True)])
+def test_brick_lists(N, side, scan):
+    """The table of brick builds whose bricks are heavy (more than 4096 points):
+    with the voxel packed beside the point's index (up to 2^21 points) and
+    beside it, the bricks listed by the scatter's blocks for the clouds or by
+    the launch that scans the columns, whole sort tiles in one brick next to
+    nearly empty ones (parts of one tile, of half a tile and of many), and two
+    clouds that share a tile."""
+    rng = np.random.default_rng(N + side)
+    B = 1 if N > 1 << 20 else 2
+    tiles, Q = (N + 4095) // 4096, (side ** 3 // 64 + 31) // 32
+    assert ((tiles + 1) * Q <= 1 << 16) == scan  # (tiles of a cloud + 1) times its bricks
+    V = side ** 3
+    lin = np.concatenate([np.full(5000, 3), np.full(3000, V - 1), rng.integers(0, 200, min(N // 3, 400000))])
+    lin = np.concatenate([lin, rng.integers(0, V, max(0, N - len(lin)))])[:N]
+    g = np.stack([lin % side, lin // side % side, lin // side ** 2], -1)
+    P = np.stack([((g + rng.uniform(0.1, 0.9, g.shape)) * 0.1).astype(np.float32) for _ in range(B)])
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, (side,) * 3, 16, 1)
+    ot = oracle.Table(P, oracle.grid_from_spec(spec))
+    d = cagq.build_grid(torch.from_numpy(P).to("cuda:0"), cagq.desc_from_spec(spec))
+    assert cagq.get_device_status(d) == 0
+    assert_table(d, ot, f"N={N} side={side}")
 
 
 @pytest.mark.parametrize("N,M", [(1, 1), (64, 64), (255, 40), (256, 256), (257, 60), (1025, 300), (4096, 200),
