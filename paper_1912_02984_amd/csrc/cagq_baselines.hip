@@ -125,6 +125,68 @@ __device__ __forceinline__ float wave_fmin(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
 }
 
+// Maximum and minimum over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_umax(uint32_t m) {
+    m = max(m, dpp_row_shr<1>(m));
+    m = max(m, dpp_row_shr<2>(m));
+    m = max(m, dpp_row_shr<4>(m));
+    m = max(m, dpp_row_shr<8>(m));
+    return max(max((uint32_t)__builtin_amdgcn_readlane((int)m, 15), (uint32_t)__builtin_amdgcn_readlane((int)m, 31)),
+               max((uint32_t)__builtin_amdgcn_readlane((int)m, 47), (uint32_t)__builtin_amdgcn_readlane((int)m, 63)));
+}
+
+__device__ __forceinline__ uint32_t wave_umin(uint32_t v) { return ~wave_umax(~v); }
+
+// One halving of run_reduce: of N values per lane the lane keeps half, by bit
+// BIT of its lane id, and takes the partner's part of them (DPP control C, a
+// permutation of the row's 16 lanes that flips that bit).
+template <int N, int BIT, int C, typename F>
+__device__ __forceinline__ void reduce_half(uint32_t (&u)[N], bool hi, F op, uint32_t (&r)[N / 2]) {
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+        const uint32_t keep = hi ? u[i + N / 2] : u[i], give = hi ? u[i] : u[i + N / 2];
+        r[i] = op(keep, (uint32_t)__builtin_amdgcn_mov_dpp((int)give, C, 0xF, 0xF, true));
+    }
+}
+
+template <int C, typename F>
+__device__ __forceinline__ uint32_t reduce_dpp(uint32_t v, F op) {
+    return op(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, C, 0xF, 0xF, true));
+}
+
+// Reduces PER values per lane over the wave, all of them together: lane l gets
+// the reduction of value l % PER. PER - 1 exchanges inside the rows of 16
+// lanes and two between them, where a reduction of each value takes six and
+// reads it back through the scalar unit.
+template <int PER, typename F>
+__device__ __forceinline__ uint32_t run_reduce(uint32_t (&u)[PER], F op) {
+    static_assert(PER == 4 || PER == 8 || PER == 16, "runs per wave");
+    const int lane = lane_id();
+    uint32_t a[PER / 2], b[PER / 4], v;
+    if constexpr (PER == 16) {
+        uint32_t c[2], d[1];
+        reduce_half<16, 3, 0x140>(u, lane & 8, op, a);  // row_mirror
+        reduce_half<8, 2, 0x141>(a, lane & 4, op, b);   // row_half_mirror
+        reduce_half<4, 1, 0x1B>(b, lane & 2, op, c);    // quad_perm 3,2,1,0
+        reduce_half<2, 0, 0xB1>(c, lane & 1, op, d);    // quad_perm 1,0,3,2
+        v = d[0];
+    } else if constexpr (PER == 8) {
+        uint32_t c[1];
+        reduce_half<8, 2, 0x141>(u, lane & 4, op, a);
+        reduce_half<4, 1, 0x1B>(a, lane & 2, op, b);
+        reduce_half<2, 0, 0xB1>(b, lane & 1, op, c);
+        v = reduce_dpp<0x128>(c[0], op);  // row_ror:8
+    } else {
+        reduce_half<4, 1, 0x1B>(u, lane & 2, op, a);
+        reduce_half<2, 0, 0xB1>(a, lane & 1, op, b);
+        v = reduce_dpp<0x128>(reduce_dpp<0x124>(b[0], op), op);  // row_ror:4, row_ror:8
+    }
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = op((uint32_t)p[0], (uint32_t)p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return op((uint32_t)q[0], (uint32_t)q[1]);
+}
+
 // Farthest Point Sampling of clouds of at most 1024 * PER points: one
 // workgroup per cloud, every point's coordinates and distance in registers.
 // The picks are a serial chain; what a pick costs is what its slowest wave
@@ -140,8 +202,19 @@ __device__ __forceinline__ float wave_fmin(float v) {
 // not finite are left out of the boxes: their distance to any center is
 // infinite or not a number, so they keep the infinity they start with, as
 // does every point against a center that is not finite.
-// Measured: 4 clouds of 8192 points, 1024 picks: 1.99 -> 1.08 ms (a pick re-reading
-// and updating every point: 1.95 us, now 1.05).
+// Measured: 4 clouds of 8192 points, 1024 picks: 1.99 -> 1.00 ms (a pick re-reading
+// and updating every point: 1.95 us, now 0.95).
+// Runs of a wave that a pick updates one by one, each with its own reduction;
+// when it reaches more, it updates every run, with one reduction for all of
+// them (PER / 2 instead of PER / 4: 4 x 8192 points of a room, 1024 picks 1.02
+// -> 1.08 ms). So that a cloud whose runs are no neighbours (one point far from
+// the rest takes the whole of the sort's grid, or most points do not differ)
+// costs a pick no more than k_fps does: 4 x 16384 points and an outlier, 2048
+// picks: k_fps 6.0 ms, one by one 6.7, now 4.0; points that are not numbers 6.0,
+// 9.3 and 1.5.
+template <int PER>
+constexpr int kFewRuns = PER / 4;
+
 template <int PER>
 __global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restrict__ points, int32_t N, int32_t M,
                                                           int32_t* __restrict__ center_idx) {
@@ -255,16 +328,24 @@ __global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restric
         y[k] = p[1];
         z[k] = p[2];
         dm[k] = in ? inf : 0.0f;
-        const bool fin = in && isfinite(x[k]) && isfinite(y[k]) && isfinite(z[k]);
-        const float c3[3] = {x[k], y[k], z[k]};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float l = wave_fmin(fin ? c3[a] : inf), h = -wave_fmin(fin ? -c3[a] : inf);
-            bl[a] = lane == k ? l : bl[a];
-            bh[a] = lane == k ? h : bh[a];
-        }
         const bool any = __ballot(in) != 0;
         rmax = lane == k && any ? __float_as_uint(inf) : rmax;
+    }
+    const auto least = [](uint32_t p, uint32_t q) {
+        return __float_as_uint(fminf(__uint_as_float(p), __uint_as_float(q)));
+    };
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        uint32_t l[PER], h[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const bool fin = isfinite(x[k]) && isfinite(y[k]) && isfinite(z[k]);  // false past the end
+            const float c = a == 0 ? x[k] : a == 1 ? y[k] : z[k];
+            l[k] = __float_as_uint(fin ? c : inf);
+            h[k] = __float_as_uint(fin ? -c : inf);
+        }
+        bl[a] = __uint_as_float(run_reduce<PER>(l, least));
+        bh[a] = -__uint_as_float(run_reduce<PER>(h, least));
     }
 
     // the wave's farthest point: key (bits(d^2) << 32) | ~index, coordinates
@@ -292,10 +373,7 @@ __global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restric
         }
         uint64_t who = __ballot(ci != 0xFFFFFFFFu);
         if (who & (who - 1)) {  // a tie between lanes: the lowest index
-            uint32_t mn = ci;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) mn = min(mn, (uint32_t)__shfl_xor((int)mn, d, kWave));
-            who = __ballot(ci == mn);
+            who = __ballot(ci == wave_umin(ci));
         }
         if (!who) return;  // a wave without points keeps key 0
         const int l = __ffsll((unsigned long long)who) - 1;
@@ -318,26 +396,30 @@ __global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restric
         const float gxx = gx * gx, gyy = gy * gy, gzz = gz * gz;
         const float gxy = gxx + gyy;
         const float gap = gxy + gzz;
-        const uint64_t need = __ballot(lane < PER && gap < __uint_as_float(rmax));
+        // (none when it is not finite)
+        const bool fin = isfinite(cx) && isfinite(cy) && isfinite(cz);
+        const uint64_t need = __ballot(fin && lane < PER && gap < __uint_as_float(rmax));
         if (need) {
+            auto update = [&](int k) {
+                const float dx = x[k] - cx, dy = y[k] - cy, dz = z[k] - cz;
+                const float xx = dx * dx, yy = dy * dy, zz = dz * dz;
+                const float sxy = xx + yy;
+                const float d = sxy + zz;
+                dm[k] = d < dm[k] ? d : dm[k];
+                return __float_as_uint(dm[k]);  // distances order as their bits
+            };
+            if (__popcll(need) > kFewRuns<PER>) {
+                uint32_t u[PER];
 #pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                if ((need >> k) & 1ull) {
-                    const float dx = x[k] - cx, dy = y[k] - cy, dz = z[k] - cz;
-                    const float xx = dx * dx, yy = dy * dy, zz = dz * dz;
-                    const float sxy = xx + yy;
-                    const float d = sxy + zz;
-                    dm[k] = d < dm[k] ? d : dm[k];
-                    uint32_t m = __float_as_uint(dm[k]);  // distances order as their bits
-                    m = max(m, dpp_row_shr<1>(m));
-                    m = max(m, dpp_row_shr<2>(m));
-                    m = max(m, dpp_row_shr<4>(m));
-                    m = max(m, dpp_row_shr<8>(m));
-                    m = max(max((uint32_t)__builtin_amdgcn_readlane((int)m, 15),
-                                (uint32_t)__builtin_amdgcn_readlane((int)m, 31)),
-                            max((uint32_t)__builtin_amdgcn_readlane((int)m, 47),
-                                (uint32_t)__builtin_amdgcn_readlane((int)m, 63)));
-                    rmax = lane == k ? m : rmax;
+                for (int k = 0; k < PER; ++k) u[k] = update(k);
+                rmax = run_reduce<PER>(u, [](uint32_t p, uint32_t q) { return max(p, q); });
+            } else {
+#pragma unroll
+                for (int k = 0; k < PER; ++k) {
+                    if ((need >> k) & 1ull) {
+                        const uint32_t m = wave_umax(update(k));
+                        rmax = lane == k ? m : rmax;
+                    }
                 }
             }
             find_best();
@@ -538,10 +620,10 @@ __global__ __launch_bounds__(1024) void k_cov_count(int32_t N, const int32_t* __
 
 }  // namespace
 
-// Picks and points from which k_fps_runs is used: its sort costs 15 to 30 us,
-// and a pick over up to 2048 points gains nothing from it. 4 clouds of 12000
-// points, 32 picks: 80 us by k_fps, 91 by k_fps_runs; 48 picks 118 and 117;
-// 2048 points, 128 picks: 123 and 125; 4096 points: 170 and 141.
+// Picks and points from which k_fps_runs is used: its sort and its runs' boxes
+// cost about 20 us, and a pick over up to 2048 points gains little from it.
+// 4 clouds, 48 picks: 2049 points 48 us by k_fps, 45 by k_fps_runs; 8193 points
+// 96 and 78; 16384 points 143 and 100.
 constexpr int32_t kRunsMinN = 2049;
 constexpr int32_t kRunsMinM = 48;
 

@@ -88,6 +88,22 @@ def test_fps_sizes(N, M):
         assert np.array_equal(c.cpu().numpy(), oracle.sample_points(P, M, "fps")), (N, M)
 
 
+@pytest.mark.parametrize("N", [2049, 4096, 4097, 8192, 8193, 16384])
+def test_fps_without_neighbourhoods(N):
+    """Farthest Point Sampling, 4, 8 and 16 runs a wave, where a pick reaches few
+    runs of a wave and where it reaches all: one point far from the rest (the
+    others share a cell of the sort), clusters far apart, and a coarse lattice
+    (many equal distances in every wave)."""
+    rng = np.random.default_rng(N)
+    far = rng.random((N, 3), dtype=np.float32)
+    far[N // 2] = 1000.0
+    apart = (rng.random((N, 3)) + 500.0 * rng.integers(0, 2, (N, 3))).astype(np.float32)
+    lattice = rng.integers(0, 12, (N, 3)).astype(np.float32)
+    P = np.stack([far, apart, lattice])
+    c = cagq.sample_points(torch.from_numpy(P).to("cuda:0"), 150, "fps")
+    assert np.array_equal(c.cpu().numpy(), oracle.sample_points(P, 150, "fps"))
+
+
 @pytest.mark.parametrize("case", ["one incumbent", "three incumbents", "last batch of one", "every voxel",
                                   "wide axis", "more state than the workgroup kernel holds"])
 def test_cas_swap_edges(case):
