@@ -21,6 +21,13 @@ constexpr int kFillG = 16;  // lanes per center in the fill
 constexpr int kFillU = 4;   // entries a lane loads at once (one at a time: 10.1 us at 4 x 8192 centers, four: 8.1)
 constexpr int kFillThreads = 256;
 
+// Most centers of a launch with one center per thread (k_ctx_count): four take
+// a thread's loads four times, which grow with the rows, and save three of four
+// tiles' atomics. One / four: r = 1, 65536 centers 15.7 / 21.6 us, 98304 24.4 /
+// 22.5, 2^20 192 / 124; r = 2, 100000 33 / 43; r = 3, 100000 49 / 73.
+constexpr int64_t ctx_one(int rad) { return (int64_t)(2 + rad) << 15; }
+
+
 // The grid, and the launch's divisions by multiply and shift (a division by a
 // kernel argument, 64-bit ones above all, costs more instructions than the
 // rest of a center's set-up).
@@ -52,16 +59,19 @@ struct CtxGrid {
     }
 };
 
-// A thread takes `items` centers in a row (one, unless there are more
-// than the points' and kCtxTiles tiles' descriptors hold), whose rows' loads go out
-// together. The descriptors, the ticket and the count of tiles that have
-// finished their look-back start at zero: every build clears them, and the
-// last tile to finish clears them again for the next call, so that the call is
-// one launch. Bound by its chain of loads (center, rows, offsets) and the
-// look-back: 4 x 8192 centers, 0.05 voxels: 9 us in tiles of 256 centers,
-// against 21 us in tiles of 1024 and 26 us with the launches that cleared and
-// unflagged the descriptors in the offsets array.
-template <int RAD>
+// A thread takes `items` centers in a row, whose rows' loads go out together:
+// one, or four (KEEP of them, their counts kept in registers), or more where
+// there are more centers than the points' and kCtxTiles tiles' descriptors hold
+// (then each is counted twice). The descriptors, the ticket and the count of
+// tiles that have finished their look-back start at zero: every build clears
+// them, and the last tile to finish clears them again for the next call, so
+// that the call is one launch. Bound by its chain of loads (center, rows,
+// offsets) and the look-back: 4 x 8192 centers, 0.05 voxels: 9 us in tiles of
+// 256 centers, against 21 us in tiles of 1024 and 26 us with the launches that
+// cleared and unflagged the descriptors in the offsets array. Every tile takes
+// two atomics on one line, ~20 ns each, which bind from some 400 tiles on: four
+// centers a thread then (ctx_one), 4 x 81920 centers 63 -> 49 us.
+template <int RAD, int KEEP>
 __global__ __launch_bounds__(kScanThreads) void k_ctx_count(int32_t N, int32_t M, int64_t total, int32_t items,
                                                             int64_t W, CtxGrid g,
                                                             const uint64_t* __restrict__ bitmap,
@@ -111,19 +121,24 @@ __global__ __launch_bounds__(kScanThreads) void k_ctx_count(int32_t N, int32_t M
         return c;
     };
     uint64_t sum = 0;
-    uint32_t c0 = 0;
-    for (int32_t i = 0; i < items; ++i) {
-        const uint32_t c = count(j0 + i);
-        c0 = i == 0 ? c : c0;
-        sum += c;
+    uint32_t kept[KEEP];
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+        kept[i] = count(j0 + i);
+        sum += kept[i];
     }
+    for (int32_t i = KEEP; i < items; ++i) sum += count(j0 + i);
     uint64_t agg;
     const uint64_t excl = block_excl_scan(sum, s_wave, &agg);
     uint64_t run = tile_lookback(desc, tile, agg, &s_prefix) + excl;
     if (j0 == 0) off[0] = 0;
-    for (int32_t i = 0; i < items; ++i) {
-        if (j0 + i >= total) break;
-        run += i == 0 ? c0 : count(j0 + i);
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+        run += kept[i];
+        if (j0 + i < total) off[j0 + i + 1] = (int64_t)run;
+    }
+    for (int32_t i = KEEP; i < items && j0 + i < total; ++i) {
+        run += count(j0 + i);
         off[j0 + i + 1] = (int64_t)run;
     }
     // past the look-back (its barrier): this tile reads no descriptor any
@@ -223,7 +238,9 @@ hipError_t launch_context_offsets(const Layout& L, const cagq_grid_desc& d, void
                                   int32_t M, int64_t* ctx_off, hipStream_t s) {
     const CtxGrid g(d, M);
     const int64_t total = (int64_t)L.B * M;
-    const int64_t items = (total + L.ctx_tiles * kScanThreads - 1) / (L.ctx_tiles * kScanThreads);
+    int64_t items = (total + L.ctx_tiles * kScanThreads - 1) / (L.ctx_tiles * kScanThreads);
+    const bool four = items > 1 || total > ctx_one(d.radius);
+    if (four && items < 4) items = 4;
     const int64_t tiles = (total + items * kScanThreads - 1) / (items * kScanThreads);
     if (tiles > L.ctx_tiles) return hipErrorInvalidValue;  // unreachable by the choice of items
     auto go = [&](auto kern) {
@@ -233,11 +250,11 @@ hipError_t launch_context_offsets(const Layout& L, const cagq_grid_desc& d, void
                                                       at<uint64_t>(ws, L.ctx_desc), at<int>(ws, L.status));
     };
     if (d.radius == 1)
-        go(k_ctx_count<1>);
+        four ? go(k_ctx_count<1, 4>) : go(k_ctx_count<1, 1>);
     else if (d.radius == 2)
-        go(k_ctx_count<2>);
+        four ? go(k_ctx_count<2, 4>) : go(k_ctx_count<2, 1>);
     else
-        go(k_ctx_count<3>);
+        four ? go(k_ctx_count<3, 4>) : go(k_ctx_count<3, 1>);
     return hipGetLastError();
 }
 

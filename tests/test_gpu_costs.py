@@ -71,3 +71,18 @@ def test_fps_of_clouds_without_neighbourhoods(case):
         t = torch.from_numpy(P).to(DEV)
         us.append(_us(lambda: cagq.sample_points(t, 512, "fps", out=out), 2))
     assert us[1] < (1.35 if case == "two clusters" else 1.9) * us[0], us
+
+
+def test_context_offsets_of_many_centers():
+    """The offsets of 2^20 centers against those of 2^15, 32 times fewer: 10.7x when
+    every tile of 256 centers took its two atomics on one line (more time than
+    the tiles of 1024 before), 6.9x now."""
+    rng = np.random.default_rng(3)
+    P = torch.from_numpy(rng.random((4, 81920, 3), dtype=np.float32)).to(DEV)
+    g = cagq.build_grid(P, cagq.make_desc((0,) * 3, (0.02,) * 3, (50,) * 3, 8, 1))
+    us = []
+    for M in (1 << 13, 1 << 18):
+        cl = torch.from_numpy(rng.integers(0, 50 ** 3, (4, M)).astype(np.int32)).to(DEV)
+        off = torch.empty(4 * M + 1, dtype=torch.int64, device=DEV)
+        us.append(_us(lambda: cagq.context_offsets(g, cl, out=off), 4))
+    assert us[1] < 8.7 * us[0], us

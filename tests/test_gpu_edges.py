@@ -159,7 +159,9 @@ def test_context_offsets_again_and_again(N, dims, radius):
     spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, dims, 5, radius)
     ot = oracle.Table(P, oracle.grid_from_spec(spec))
     g = cagq.build_grid(torch.from_numpy(P).to("cuda:0"), cagq.desc_from_spec(spec))
-    many = (140000,) if N == 700 and radius == 1 else ()
+    # past one center a thread (M over (2 + radius) * 2^14 of the two clouds'), and past
+    # four (over 4 * 256 of the descriptors', 1029)
+    many = (49152, 49153, 140000, 526900) if N == 700 and radius == 1 else (81921,) if N == 700 else ()
     for M in (1, 128, 129, 256, 500, N, N + 1, 3 * N + 5, *many, 300):
         cl = np.where(rng.random((B, M)) < 0.8, lin[:, rng.integers(0, N, M)], rng.integers(0, V, (B, M)))
         cl = cl.astype(np.int32)
