@@ -13,8 +13,9 @@
 // (about one in eight is accepted on the indoor scenes), so they are decided
 // ahead and again only when a swap before them may have changed them.
 // With r = 1 a workgroup per cloud does so (k_cas_swap_wg, below). With r >= 2,
-// and for clouds whose state leaves no room for that kernel's batches in LDS,
-// one wave per cloud decides 64 challenges at a time, one per lane (k_cas_swap):
+// for clouds whose state leaves no room for that kernel's batches in LDS, and
+// for many clouds at once, one wave per cloud decides 64 challenges at a time,
+// one per lane (k_cas_swap):
 // * every lane loads the grid rows of pi(C) and pi(I) for its challenge once
 //   and evaluates both heuristics against the current coverage counts;
 // * a sweep walks the accepted lanes in challenge order; an accepted lane
@@ -315,6 +316,14 @@ __global__ __launch_bounds__(kWave) void k_cas_swap(int32_t N, int64_t W, GridDi
 // Measured, two rooms of 30011 points with M = 3001: 4.9 -> 1.3 ms against one wave
 // per cloud that decides 64 challenges a lane each and sweeps again from the
 // first stale one.
+// Most clouds of a launch (in all, and of less than 2048 points) that take a
+// workgroup each: two of them fill a CU, and beyond that the launch grows with
+// the clouds, while the one-wave kernel holds thousands at once. Workgroups /
+// waves: 300 points, 704 clouds 101 / 87 us, 4000 507 / 187; 1024 points, 512
+// clouds 189 / 250, 768 273 / 249, 1536 533 / 296; 4096 points, 768 clouds 943 /
+// 1170, 1024 1248 / 1184; 20000 points, 1024 clouds 6343 / 6110.
+constexpr int32_t kSwapWgClouds = 928;
+constexpr int32_t kSwapWgSmall = 600;
 constexpr int kSwapT = 1024;
 constexpr int kSwapWaves = kSwapT / kWave;
 constexpr int kSwapHelpers = kSwapWaves - 1;
@@ -662,7 +671,7 @@ hipError_t launch_cas_swap(const Layout& L, const cagq_grid_desc& d, void* ws, i
     for (int a = 0; a < 3; ++a) g.D[a] = d.dims[a];
     const size_t bytes = swap_lds_bytes(L.N, M, d.radius);
     const size_t wg = sizeof(SwapLds) + bytes;
-    if (d.radius == 1 && wg + kSwapLdsStatic <= kSwapLdsLimit) {
+    if (d.radius == 1 && wg + kSwapLdsStatic <= kSwapLdsLimit && L.B <= (L.N < 2048 ? kSwapWgSmall : kSwapWgClouds)) {
         e = hipFuncSetAttribute((const void*)k_cas_swap_wg, hipFuncAttributeMaxDynamicSharedMemorySize, (int)wg);
         if (e != hipSuccess) return e;
         const SwapGrid sg{g, make_magic((uint32_t)g.D[0]), make_magic((uint32_t)g.D[0] * (uint32_t)g.D[1])};

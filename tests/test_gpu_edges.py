@@ -127,6 +127,14 @@ def test_cas_swap_edges(case):
         run_both(P, spec, M, 8, "cas_swap", "cube", 11, beta_q16=beta, where=f"{case} beta={beta}")
 
 
+@pytest.mark.parametrize("B,N", [(600, 120), (601, 120)])
+def test_cas_swap_many_clouds(B, N):
+    """The most clouds that take a workgroup each, and one more (a wave each)."""
+    P = np.random.default_rng(B).random((B, N, 3), dtype=np.float32)
+    spec = W.GridSpec((0.0,) * 3, (0.1,) * 3, (10,) * 3, 8, 1)
+    run_both(P, spec, 20, 8, "cas_swap", "cube", 11, beta_q16=500, where=f"B={B}")
+
+
 @pytest.mark.parametrize("N,radius", [(1500, 1), (1500, 2), (6000, 1), (20000, 1)])
 def test_cas_past_full_coverage(N, radius):
     """Greedy CAS whose picks run out of uncovered voxels: the last centers
