@@ -319,11 +319,11 @@ __global__ __launch_bounds__(kWave) void k_cas_swap(int32_t N, int64_t W, GridDi
 // Most clouds of a launch (in all, and of less than 2048 points) that take a
 // workgroup each: two of them fill a CU, and beyond that the launch grows with
 // the clouds, while the one-wave kernel holds thousands at once. Workgroups /
-// waves: 300 points, 704 clouds 101 / 87 us, 4000 507 / 187; 1024 points, 512
-// clouds 189 / 250, 768 273 / 249, 1536 533 / 296; 4096 points, 768 clouds 943 /
+// waves: 300 points, 600 clouds 99 / 87 us, 4000 507 / 187; 1024 points, 512
+// clouds 189 / 250, 600 262 / 250, 1536 533 / 296; 4096 points, 768 clouds 943 /
 // 1170, 1024 1248 / 1184; 20000 points, 1024 clouds 6343 / 6110.
-constexpr int32_t kSwapWgClouds = 928;
-constexpr int32_t kSwapWgSmall = 600;
+constexpr int32_t kSwapWgClouds = 896;
+constexpr int32_t kSwapWgSmall = 512;
 constexpr int kSwapT = 1024;
 constexpr int kSwapWaves = kSwapT / kWave;
 constexpr int kSwapHelpers = kSwapWaves - 1;

@@ -127,7 +127,7 @@ def test_cas_swap_edges(case):
         run_both(P, spec, M, 8, "cas_swap", "cube", 11, beta_q16=beta, where=f"{case} beta={beta}")
 
 
-@pytest.mark.parametrize("B,N", [(600, 120), (601, 120)])
+@pytest.mark.parametrize("B,N", [(512, 120), (513, 120)])
 def test_cas_swap_many_clouds(B, N):
     """The most clouds that take a workgroup each, and one more (a wave each)."""
     P = np.random.default_rng(B).random((B, N, 3), dtype=np.float32)
