@@ -128,9 +128,11 @@ __device__ __forceinline__ void cover(uint32_t* cov_w, const Occ& o, const Hood<
     });
 }
 
-__device__ __forceinline__ bool near(int32_t ax, int32_t ay, int32_t az, int32_t bx, int32_t by, int32_t bz,
-                                     int32_t d) {
-    return (abs(ax - bx) <= d) & (abs(ay - by) <= d) & (abs(az - bz) <= d);
+// Whether two voxels lie within Chebyshev distance d, 0 or 1 (an int, so that
+// tests are combined without branches).
+__device__ __forceinline__ int near(int32_t ax, int32_t ay, int32_t az, int32_t bx, int32_t by, int32_t bz,
+                                    int32_t d) {
+    return int(abs(ax - bx) <= d) & int(abs(ay - by) <= d) & int(abs(az - bz) <= d);
 }
 
 template <int RAD, typename CT>
@@ -382,7 +384,7 @@ __device__ __forceinline__ bool window_voxel(const SwapGrid& sg, uint32_t lin, c
 // keeps its bit 9 when the difference is not negative. Coordinates are below
 // kPackDim, so that no field borrows or carries.
 constexpr int32_t kPackDim = 510;
-__device__ __forceinline__ bool near_packed(uint32_t p, uint32_t q) {
+__device__ __forceinline__ int near_packed(uint32_t p, uint32_t q) {
     constexpr uint32_t kOnes = 1u | 1u << 10 | 1u << 20, kBias = 514u * kOnes, kSign = 512u * kOnes;
     return ((p + (kBias - q)) & ((q + kBias) - p) & kSign) == kSign;
 }
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(kSwapT) void k_cas_swap_wg(int32_t N, int64_t W, Sw
                                ai = (uint32_t)__builtin_amdgcn_readlane((int)ip, a);
                 const bool after = live && lane > a;
                 const bool same = after && j == ja;
-                bool touch;
+                int touch;
                 if (packed) {
                     touch = near_packed(cp, ac) | near_packed(cp, ai) | near_packed(ip, ac) | near_packed(ip, ai);
                 } else {  // here cp and ip are the linear ids
@@ -612,7 +614,7 @@ __global__ __launch_bounds__(kSwapT) void k_cas_swap_wg(int32_t N, int64_t W, Sw
                             near(x[1], y[1], z[1], x[2], y[2], z[2], 2) | near(x[1], y[1], z[1], x[3], y[3], z[3], 2);
                 }
                 reload = reload || same;
-                stale = stale || same || (after && touch);
+                stale = stale || same || (after && touch != 0);
                 todo = __ballot(after && (acc || stale));
             }
             __builtin_amdgcn_s_setprio(0);
