@@ -124,26 +124,26 @@ def test_capped_and_big_voxels(N):
 @pytest.mark.parametrize("case", ["brick-capacity", "ragged-bricks", "wide-bricks", "scan-launch",
                                   "grid-too-large-for-bricks"])
 def test_brick_build_edges(case):
-    """The brick build of larger clouds: bricks of 2048 consecutive voxels
-    holding exactly the 2048 points one work item takes and one more (then
-    split into two parts that meet in memory), voxels of more than 64 points
-    in both, a last brick cut short by the grid; 1280 bricks per cloud (the
-    scatter tiles scan the bricks' totals in two passes); clouds whose tiles
-    times bricks exceed 2^16 (the histogram columns are scanned by a launch
-    of their own), with a brick of 3000 points and tiles holding points of
-    two clouds; and a grid with more bricks than the build holds, which
-    takes the seven-kernel build."""
+    """The brick build of larger clouds: bricks holding exactly the 4096 points
+    one part takes and one more (then split into two parts that meet in
+    memory), voxels of more than 64 points in both, a last brick cut short by
+    the grid; 1280 bricks per cloud (the scatter scans the bricks' totals in two
+    passes); clouds whose tiles times bricks exceed 2^16 (the histogram columns
+    are scanned by a launch of their own, which also lists the bricks), with a
+    heavy brick in each cloud and tiles holding points of two clouds; and a grid
+    with more bricks than the build holds, which takes the seven-kernel
+    build."""
     rng = np.random.default_rng(11)
     if case == "brick-capacity":
-        # 64 x 32 voxels per z-slice: brick q is slice z = q
-        B, N, dims, n_v = 2, 10000, (64, 32, 64), 16
-        P = rng.random((B, N, 3), dtype=np.float32) * np.float32([6.4, 3.2, 6.4])
-        P[:, 4197:, 2] = np.float32(0.3) + rng.random((B, N - 4197), dtype=np.float32) * np.float32(6.0)
-        P[:, :1948, 2] = np.float32(0.05)                 # brick 0: 1948 spread points
-        P[:, 1948:2048] = np.float32([0.33, 0.47, 0.05])  # and 100 in one voxel: 2048
-        P[:, 2048:3997, 2] = np.float32(0.15)             # brick 1: 1949 spread points
-        P[:, 3997:4097] = np.float32([0.33, 0.47, 0.15])  # and 100 in one voxel: 2049
-        P[:, 4097:4197] = np.float32([0.33, 0.47, 0.25])  # 100 in one voxel of brick 2
+        # bricks of 256 voxels: four rows of 64 along x of one z-slice
+        B, N, dims, n_v = 2, 12000, (64, 32, 64), 16
+        P = rng.random((B, N, 3), dtype=np.float32) * np.float32([6.4, 0.4, 0.1])
+        P[:, 3996:4096] = np.float32([0.33, 0.17, 0.05])   # brick 0: 3996 spread points and 100 in one voxel
+        P[:, 4096:8193, 1] += np.float32(0.4)              # brick 1: 3997 spread points
+        P[:, 8093:8193] = np.float32([0.33, 0.57, 0.05])   # and 100 in one voxel: 4097
+        P[:, 8193:8293] = np.float32([0.33, 0.47, 0.25])   # 100 in one voxel of another
+        P[:, 8293:] *= np.float32([1.0, 8.0, 60.0])
+        P[:, 8293:, 2] += np.float32(0.3)
         P = P[:, rng.permutation(N)]
         spec = _spec((0, 0, 0), (0.1,) * 3, dims, n_v)
     elif case == "ragged-bricks":
@@ -159,8 +159,11 @@ def test_brick_build_edges(case):
         # (ceil(N / 4096) + 1) * Q = 26 * 2560 > 2^16
         B, N, dims, n_v = 2, 100000, (256, 256, 80), 8
         P = rng.random((B, N, 3), dtype=np.float32) * np.float32([2.56, 2.56, 0.8])
-        # brick 0 (x < 2.56, y < 0.08, z < 0.01): 3000 points, two work items
-        P[:, :3000] = rng.random((B, 3000, 3), dtype=np.float32) * np.float32([2.55, 0.079, 0.0099])
+        # brick 0 (x < 2.56, y < 0.08, z < 0.01): 9000 points, 5000 of them in two
+        # voxels, three parts or more (their 25 tiles' points come in any order)
+        P[:, :9000] = rng.random((B, 9000, 3), dtype=np.float32) * np.float32([2.55, 0.079, 0.0099])
+        P[:, :2000] = np.float32([0.015, 0.015, 0.005])
+        P[:, 2000:5000] = np.float32([2.015, 0.055, 0.005])
         P = P[:, rng.permutation(N)]
         spec = _spec((0, 0, 0), (0.01,) * 3, dims, n_v)
     else:
@@ -711,11 +714,12 @@ def test_coverage_matches_oracle(name):
 
 
 @pytest.mark.parametrize("r", [1, 2, 3])
-@pytest.mark.parametrize("K", [17, 32])
+@pytest.mark.parametrize("K", [1, 8, 16, 17, 32])
 def test_sixteen_lane_query_with_large_contexts(r, K):
     """Contexts from empty to several hundred points in one block of 16
-    centers (the query sorts the block's centers by context size), weights,
-    K between 17 and 32: several chunks merged into two result registers."""
+    centers, weights: several chunks merged into one result register (K <= 16)
+    or two, and, for r = 2 and 3, contexts above 128 points that are left to a
+    wave each beside others that are not."""
     rng = np.random.default_rng(7 * r + K)
     B, N = 2, 6000
     P = (rng.random((B, N, 3), dtype=np.float32) ** 4).astype(np.float32)
@@ -724,6 +728,8 @@ def test_sixteen_lane_query_with_large_contexts(r, K):
     for q in ("knn", "cube"):
         qo = run_both(P, spec, 333, K, "rvs", q, 3, weights=wts, where=f"r={r} K={K} {q}")
     assert qo["ctx_count"].max() > 64 and qo["ctx_count"].min() < 16
+    if r > 1:
+        assert qo["ctx_count"].max() > 128 and ((qo["ctx_count"] > 32) & (qo["ctx_count"] <= 128)).any()
 
 
 @pytest.mark.parametrize("r", [1, 2, 3])
