@@ -260,13 +260,15 @@ def test_rvs_selection_sizes(N):
             assert np.array_equal(cl.cpu().numpy(), ocl), (N, M, seed)
 
 
-@pytest.mark.parametrize("B,N,dims,sample", [(3, 3000, (512, 512, 40), "rvs"), (70, 300, (64, 64, 64), "rvs"),
-                                             (3, 9001, (40, 40, 40), "cas"), (66, 4100, (24, 24, 24), "cas")])
+@pytest.mark.parametrize("B,N,dims,sample", [(3, 3000, (512, 512, 40), "rvs"), (70, 3000, (128, 128, 64), "rvs"),
+                                             (70, 300, (64, 64, 64), "rvs"), (3, 9001, (40, 40, 40), "cas"), (66, 4100, (24, 24, 24), "cas")])
 def test_tiles_of_many_clouds(B, N, dims, sample):
-    """The build of grids too large for bricks (its ranks over tiles and groups
-    of tiles, its offsets over the tiles with slots) and the compaction of
-    many-kernel CAS, with a few clouds and with more than a wave of them, their
-    occupied voxels from a handful to all points', on both sides of a tile."""
+    """Scans over the tiles with slots, of a few clouds and of more than a wave of
+    them, their occupied voxels from a handful to all points', on both sides of
+    a tile: the build of grids too large for bricks (the first two: ranks over
+    tiles and groups of tiles, offsets over the tiles with slots) and the
+    compaction of many-kernel CAS (the last two, on a brick build and on the
+    one-workgroup build); the third case takes the one-workgroup build."""
     rng = np.random.default_rng(B)
     V = dims[0] * dims[1] * dims[2]
     lin = np.empty((B, N), np.int64)
