@@ -115,7 +115,6 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->sel_cnt = take(4 * (size_t)B);
     L->ctx_tiles = ((int64_t)BN + kScanThreads - 1) / kScanThreads + kCtxTiles;
     L->ctx_desc = take(8 * (size_t)L->ctx_tiles);
-    L->clear_small = off;
     L->desc_h = take(8 * ((BQ + 63) / 64));
     L->hdone = take(4 * H);
     L->clear_brick = off;
@@ -127,7 +126,7 @@ bool make_layout(int32_t B, int32_t N, const cagq_grid_desc* d, Layout* L) {
     L->clear_end = off;
     L->bitmap = take(8 * (size_t)B * L->W);
     L->word_rank = take(4 * (size_t)B * L->W);
-    L->pt_slot = take(4 * BN);
+    L->pt_slot = take(L->bricks ? 0 : 4 * BN);
     L->pt_pos = take(L->bricks ? 0 : 4 * BN);
     L->hist = take(4 * hist_n);
     L->bstart = take(4 * BQ);

@@ -218,7 +218,7 @@ constexpr int kFewRuns = PER / 4;
 template <int PER>
 __global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restrict__ points, int32_t N, int32_t M,
                                                           int32_t* __restrict__ center_idx) {
-    constexpr int kW = kSelThreads / kWave;  // most waves of the workgroup
+    constexpr int kW = kSelThreads / kWave;
     constexpr int kCells = 4096;
     static_assert(PER <= 16 && kW == 16, "a wave's runs, and the waves, fit in 16 lanes");
     __shared__ uint32_t s_cell[kCells];
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kSelThreads) void k_fps_runs(const float* __restric
     __shared__ float4 s_xyz[2][kW];
     const int32_t b = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
-    const int nt = blockDim.x, nw = nt / kWave;
+    constexpr int nt = kSelThreads, nw = kW;
     const float* P = points + (size_t)b * N * 3;
     int32_t* out = center_idx + (size_t)b * M;
     const float inf = __builtin_inff();

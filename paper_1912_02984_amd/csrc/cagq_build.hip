@@ -1349,11 +1349,11 @@ __device__ __forceinline__ uint64_t small_excl_scan(uint64_t v, uint64_t* s_wave
 size_t small_lds_bytes(int32_t N, int64_t W) { return (size_t)12 * W + (size_t)4 * (2 * (size_t)N + 1); }
 
 __global__ __launch_bounds__(kSmallT) void k_build_small(
-    const float* __restrict__ P, int32_t N, GridArgs g, int64_t W, uint32_t n_v, uint32_t* __restrict__ pt_slot,
-    uint64_t* __restrict__ bitmap, uint32_t* __restrict__ word_rank, uint32_t* __restrict__ vox_lin,
-    uint32_t* __restrict__ vox_count, int32_t* __restrict__ nvox, uint32_t* __restrict__ vox_off,
-    uint32_t* __restrict__ pt_list, float4* __restrict__ pt4, int* __restrict__ status, int* __restrict__ berr,
-    uint64_t* __restrict__ ctx_desc, int32_t ctx_tiles) {
+    const float* __restrict__ P, int32_t N, GridArgs g, int64_t W, uint32_t n_v, uint64_t* __restrict__ bitmap,
+    uint32_t* __restrict__ word_rank, uint32_t* __restrict__ vox_lin, uint32_t* __restrict__ vox_count,
+    int32_t* __restrict__ nvox, uint32_t* __restrict__ vox_off, uint32_t* __restrict__ pt_list,
+    float4* __restrict__ pt4, int* __restrict__ status, int* __restrict__ berr, uint64_t* __restrict__ ctx_desc,
+    int32_t ctx_tiles) {
     extern __shared__ __align__(16) unsigned char lds[];
     uint64_t* s_bm = reinterpret_cast<uint64_t*>(lds);   // [W] occupancy words
     uint32_t* s_wr = reinterpret_cast<uint32_t*>(s_bm + W);  // [W] ranks
@@ -1450,7 +1450,6 @@ __global__ __launch_bounds__(kSmallT) void k_build_small(
         const uint32_t sl = s_wr[w] + (uint32_t)__popcll(s_bm[w] & ((1ull << (lin[k] & 63)) - 1));
         const uint32_t pos = atomicAdd(&s_off[sl], 1u);
         sp[k] = (sl << 16) | pos;
-        pt_slot[pb + i] = sl;
         if (pos == 0) s_bk[sl] = lin[k];
     }
     lds_barrier();
@@ -1572,9 +1571,9 @@ hipError_t launch_build(const float* points, const Layout& L, const cagq_grid_de
         hipError_t e = hipFuncSetAttribute((const void*)k_build_small, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)bytes);
         if (e != hipSuccess) return e;
-        k_build_small<<<B, kSmallT, bytes, s>>>(points, N, g, L.W, (uint32_t)d.n_v, at<uint32_t>(ws, L.pt_slot),
-                                                at<uint64_t>(ws, L.bitmap), at<uint32_t>(ws, L.word_rank),
-                                                at<uint32_t>(ws, L.vox_lin), at<uint32_t>(ws, L.vox_count),
+        k_build_small<<<B, kSmallT, bytes, s>>>(points, N, g, L.W, (uint32_t)d.n_v, at<uint64_t>(ws, L.bitmap),
+                                                at<uint32_t>(ws, L.word_rank), at<uint32_t>(ws, L.vox_lin),
+                                                at<uint32_t>(ws, L.vox_count),
                                                 at<int32_t>(ws, L.nvox), at<uint32_t>(ws, L.vox_off),
                                                 at<uint32_t>(ws, L.pt_list), at<float4>(ws, L.pt4), status,
                                                 at<int>(ws, L.berr), at<uint64_t>(ws, L.ctx_desc),

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kFillThreads) void k_ctx_fill(int32_t N, int32_t M,
                                                            int* __restrict__ status) {
     constexpr int S = 2 * RAD + 1;
     constexpr int GPB = kFillThreads / kFillG;
-    __shared__ uint32_t s_pre[GPB][kFillG + 1];
+    __shared__ uint32_t s_pre[GPB][kFillG];
     __shared__ uint32_t s_st[GPB][kFillG];
     const int gb = threadIdx.x / kFillG, lg = threadIdx.x & (kFillG - 1);
     const int64_t j = (int64_t)xcd_block(blockIdx.x, gridDim.x) * GPB + gb;
@@ -199,7 +199,6 @@ __global__ __launch_bounds__(kFillThreads) void k_ctx_fill(int32_t N, int32_t M,
         s_pre[gb][lg] = incl - len;
         s_st[gb][lg] = st;
         const uint32_t tot = (uint32_t)__shfl((int)incl, kFillG - 1, kFillG);
-        if (lg == kFillG - 1) s_pre[gb][kFillG] = tot;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

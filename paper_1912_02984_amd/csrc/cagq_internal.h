@@ -81,15 +81,15 @@ struct Layout {
     size_t status;        // int32[kStSlots]
     size_t berr;          // int32[B] per cloud: the one-workgroup build's error code (0 = none)
     size_t desc_h;        // u64 [blocks of the column scan] scan descriptors (brick totals)
-    size_t clear_brick;   // [status, clear_brick) is zeroed by the brick build (status, tickets,
-                          // descriptors, hdone)
+    size_t clear_brick;   // [status, clear_brick) is zeroed by the brick build; the one-workgroup build
+                          // zeroes the status words and ctx_desc and writes berr
     size_t desc_w;        // u32 [B][tiles_w] occupied voxels per tile, u32 [B][tiles_w / kRankGroup + 1] per
                           // group of tiles
     size_t desc_s;        // u64 [B][tiles_s] scan descriptors (offsets)
     size_t bytemap;       // u8  [B][64 W] one byte per voxel, 1 when a point lies in it
     size_t bitmap;        // u64 [B][W] occupancy bits, bit (lin & 63) of word lin >> 6
     size_t word_rank;     // u32 [B][W] occupied voxels before word w (the slot of its first bit)
-    size_t pt_slot;       // u32 [B][N] per point: linear id, then slot
+    size_t pt_slot;       // u32 [B][N] per point: linear id, then slot (not with bricks)
     size_t pt_pos;        // u32 [B][N] per point: arrival position inside its voxel (not with bricks)
     size_t hist;          // u32 [T][B*Q] points of tile t in brick g, then the first sorted position of them
     size_t bstart;        // u32 [B*Q] first sorted position of each brick
@@ -127,10 +127,9 @@ struct Layout {
     size_t sel_bins;      // u32 [B][chunks][kSelBins] end of each 11-bit bin in its sorted chunk
     size_t sel_base;      // u32 [B][chunks] first output position of each chunk's chosen slots
     size_t sel_take;      // u32 [B][chunks] ties at the bound each chunk takes
-    size_t clear_small;   // [status, clear_small) is zeroed by every build
     size_t cov_mark;      // u8  [B][N] coverage metric: 1 when the slot holds a node point (in pt_pos's
                           // place where the layout has that: the build is done with it)
-    size_t clear_end;     // [status, clear_end) is zeroed at the start of every build
+    size_t clear_end;     // [status, clear_end) is zeroed by the many-kernel build
 };
 
 // CAS control block, placed at Layout::cas_ctl: per round buffer (a round
@@ -633,40 +632,6 @@ __device__ __forceinline__ void decode_lin(uint32_t lin, const GridDims& g, int3
     x = (int32_t)(lin % (uint32_t)g.D[0]);
     y = (int32_t)((lin / (uint32_t)g.D[0]) % (uint32_t)g.D[1]);
     z = (int32_t)(lin / ((uint32_t)g.D[0] * (uint32_t)g.D[1]));
-}
-
-// Calls f(slot) for every occupied voxel within Chebyshev distance `rad` of
-// grid cell (x, y, z), in ascending linear id, one occupancy word per grid
-// row segment; stops early (returning false) when f returns false.
-template <typename F>
-__device__ __forceinline__ bool for_each_neighbour(const uint64_t* __restrict__ bm,
-                                                   const uint32_t* __restrict__ wr, const int32_t* D,
-                                                   int32_t x, int32_t y, int32_t z, int32_t rad, F f) {
-    const int32_t x0 = x - rad < 0 ? 0 : x - rad;
-    const int32_t x1 = x + rad > D[0] - 1 ? D[0] - 1 : x + rad;
-    const int32_t z0 = z - rad < 0 ? 0 : z - rad, z1 = z + rad > D[2] - 1 ? D[2] - 1 : z + rad;
-    const int32_t y0 = y - rad < 0 ? 0 : y - rad, y1 = y + rad > D[1] - 1 ? D[1] - 1 : y + rad;
-    for (int32_t zz = z0; zz <= z1; ++zz) {
-        for (int32_t yy = y0; yy <= y1; ++yy) {
-            const uint32_t base = (uint32_t)D[0] * ((uint32_t)yy + (uint32_t)D[1] * (uint32_t)zz);
-            const uint32_t l0 = base + (uint32_t)x0, l1 = base + (uint32_t)x1;
-            for (uint32_t w = l0 >> 6; w <= (l1 >> 6); ++w) {
-                const uint64_t bits = bm[w];
-                const uint32_t lo = w == (l0 >> 6) ? (l0 & 63) : 0u;
-                const uint32_t hi = w == (l1 >> 6) ? (l1 & 63) : 63u;
-                const uint64_t upto = hi == 63 ? ~0ull : ((1ull << (hi + 1)) - 1);
-                uint64_t m = bits & upto & ~((1ull << lo) - 1);
-                if (!m) continue;
-                const uint32_t rb = wr[w];
-                while (m) {
-                    const int bit = __ffsll((unsigned long long)m) - 1;
-                    if (!f(rb + (uint32_t)__popcll(bits & ((1ull << bit) - 1)))) return false;
-                    m &= m - 1;
-                }
-            }
-        }
-    }
-    return true;
 }
 
 // ------------------------------------------------------------------ host launchers
